@@ -544,6 +544,13 @@ def test_add_variants(B, ctx, n, C, a_bits, b_bits):
     assert np.all(gb[:, wds] == np.uint64(0xFFFFFFFFFFFFFFFF))
 
 
+@pytest.mark.parametrize("n,C", [(3, 2), (130, 3), (65, 4), (33, 5), (64, 63), (17, 67), (9, 1100)])
+def test_add_edges_of_the_four_channel_lanes(B, ctx, n, C):
+    """Rows shorter than a lane's 4 channels, rows that end inside them, more tiles than rows."""
+    for bits in ((False, False), (True, True), (False, True)):
+        test_add_variants(B, ctx, n, C, *bits)
+
+
 def test_add_merges_a_sage_layer_like_the_concatenated_form(B, ctx):
     """ADD.FFF on the two scaled products of a GraphSAGE layer, binarized: the bits of the
     library's concatenated layer."""
