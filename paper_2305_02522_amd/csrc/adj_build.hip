@@ -126,6 +126,23 @@ __global__ void degree_kernel(const uint32_t *__restrict__ rowptr, uint32_t N,
     atomicMax(max_deg, (int)d);
 }
 
+// thread k < 32: rows with at least 2^k neighbours, by binary search in the degree order
+__global__ void degree_counts_kernel(const int32_t *__restrict__ order,
+                                     const int32_t *__restrict__ deg, uint32_t N,
+                                     uint32_t *__restrict__ n_ge)
+{
+    const uint32_t k = threadIdx.x;
+    uint32_t lo = 0, hi = N;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if ((uint32_t)deg[order[mid]] >= (1u << k))
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    n_ge[k] = lo;
+}
+
 __global__ void rank_kernel(const int32_t *__restrict__ order, uint32_t N,
                             int32_t *__restrict__ rank)
 {
@@ -311,12 +328,16 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     BG_REQUIRE(ctx, h_err == 0, BITGNN_ERR_INDEX_RANGE,
                "bitgnn_adj_build: an edge endpoint is outside [0, %lld)", (long long)N);
 
-    DevBuf rowptr, col, deg, order;
+    DevBuf rowptr, col, deg, order, n_ge;
+    uint32_t h_n_ge[32];
+    BG_HIP(ctx, n_ge.alloc(sizeof(h_n_ge)));
     BG_HIP(ctx, rowptr.alloc(((size_t)N + 1) * 4));
     BG_HIP(ctx, col.alloc((size_t)nnz * 4));
     BG_HIP(ctx, deg.alloc((size_t)N * 4));
     BG_HIP(ctx, order.alloc((size_t)N * 4));
-    if (nnz > 0)
+    if (nnz == 0) // kernels may read (not use) the first column of an empty graph
+        BG_HIP(ctx, hipMemsetAsync(col.p, 0, 4, s));
+    else
         split_keys_kernel<<<blocks_for(nnz, 256), 256, 0, s>>>(sorted, nnz, cb, col.as<int32_t>());
     rowptr_kernel<<<blocks_for(N + 1, 256), 256, 0, s>>>(sorted, nnz, cb, (uint32_t)N,
                                                         rowptr.as<uint32_t>());
@@ -330,7 +351,10 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
         radix_sort(oa, ob, (uint32_t)N, 64, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     order_from_keys_kernel<<<blocks_for(N, 256), 256, 0, s>>>(osorted, (uint32_t)N,
                                                              order.as<int32_t>());
+    degree_counts_kernel<<<1, 32, 0, s>>>(order.as<int32_t>(), deg.as<int32_t>(), (uint32_t)N,
+                                          n_ge.as<uint32_t>());
     BG_LAUNCH_CHECK(ctx, "order");
+    BG_HIP(ctx, hipMemcpyAsync(h_n_ge, n_ge.p, sizeof(h_n_ge), hipMemcpyDeviceToHost, s));
     int h_maxdeg = 0;
     BG_HIP(ctx, hipMemcpyAsync(&h_maxdeg, d_maxdeg, sizeof(int), hipMemcpyDeviceToHost, s));
     BG_HIP(ctx, hipStreamSynchronize(s));
@@ -341,6 +365,7 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     adj->n = N;
     adj->nnz = nnz;
     adj->max_degree = h_maxdeg;
+    memcpy(adj->n_ge, h_n_ge, sizeof(h_n_ge));
     adj->device_bytes = ((size_t)N + 1) * 4 + (size_t)nnz * 4 + (size_t)N * 8;
     adj->rowptr = (uint32_t *)rowptr.release();
     adj->col = (int32_t *)col.release();

@@ -76,13 +76,97 @@ __global__ __launch_bounds__(256) void bspmm_seed_kernel(const int32_t *__restri
     seed_word_vote((int)(blockIdx.x * blockDim.x + threadIdx.x), 2 * P * W32, T, C, W32, P, table);
 }
 
+// Two more epilogues behind bitgnn_spmm_f32 on +-1 rows without factors: y = r[i] * (float)S,
+// stored as floats or binarized with float thresholds.
+enum { kEpiScaledF32 = 16, kEpiScaledBits = 17 };
+struct ScaledEpi {
+    const float *r;   // [n] or null (= 1)
+    const float *tau; // [C], bits only
+};
+
+// The thresholds of kEpiScaledBits in LDS, [bit of the word][word], so that lanes on
+// neighbouring words read neighbouring addresses (from memory, a load per channel touched a
+// line per word: 20 us of a 500-channel aggregation of 89 K rows).  Every thread of the
+// workgroup must call.
+constexpr int kMaxChannels = 2048;
+template <int EPI>
+__device__ __forceinline__ const float *stage_tau(const ScaledEpi &se, int32_t C, int32_t W32)
+{
+    if constexpr (EPI == kEpiScaledBits) {
+        __shared__ float s_tau[kMaxChannels];
+        for (int c = threadIdx.x; c < C; c += blockDim.x)
+            s_tau[(c & 31) * W32 + (c >> 5)] = se.tau[c];
+        __syncthreads();
+        return s_tau;
+    }
+    return nullptr;
+}
+
+template <int P, int EPI>
+__device__ __forceinline__ void scaled_epilogue(const uint32_t (&acc)[P], uint32_t deg,
+                                                uint32_t row, int w, int32_t W32, int32_t C,
+                                                const ScaledEpi &se, const float *s_tau,
+                                                void *__restrict__ out, int64_t out_stride)
+{
+    const uint32_t tail = (uint32_t)C - 32u * (uint32_t)w; // channels from this word on
+    // planes that any row of the wavefront can fill
+    int np = 0;
+    while (np < P && __ballot((deg >> np) != 0u) != 0ull)
+        ++np;
+    const float ri = se.r ? se.r[row] : 1.0f;
+    const float fdeg = (float)deg; // below 2^24, like every integer here: exact
+    uint32_t ge = 0;
+    float *o = (float *)out + (int64_t)row * out_stride + 32 * w;
+    // Eight channels at a time (all 32 at once took 40 more registers, and the neighbour walk
+    // of the kernel paid for them in wavefronts).
+#pragma unroll 1
+    for (uint32_t b0 = 0; b0 < 32u && b0 < tail; b0 += 8) {
+        uint32_t cnt[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+            cnt[b] = 0u;
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (p < np) { // wave-uniform
+                const uint32_t a = acc[p] >> b0;
+#pragma unroll
+                for (int b = 0; b < 8; ++b)
+                    cnt[b] |= ((a >> b) & 1u) << p;
+            }
+        uint32_t byte = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const float y = ri * __builtin_fmaf(2.0f, (float)cnt[b], -fdeg);
+            if (EPI == kEpiScaledBits) // (bits past the row's end are cleared below)
+                byte |= y >= s_tau[(b0 + b) * W32 + w] ? 1u << b : 0u;
+            else if (b0 + b < tail)
+                o[b0 + b] = y;
+        }
+        ge |= byte << b0;
+    }
+    if (EPI == kEpiScaledBits) {
+        if (tail < 32u)
+            ge &= (1u << tail) - 1u;
+        uint32_t *ob = (uint32_t *)out + (int64_t)row * out_stride * 2;
+        ob[w] = ge;
+        if (w == W32 - 1 && (W32 & 1))
+            ob[W32] = 0u; // upper half of the last 64-bit word
+    }
+}
+
 // Epilogue of one (node, 32-channel word): `acc` holds the bit-sliced count (plus
 // the seed for THRESH_BITS) as an ordinary binary number in P planes.
 template <int P, int EPI>
 __device__ __forceinline__ void bspmm_epilogue(const uint32_t (&acc)[P], uint32_t deg, uint32_t row,
                                                int w, int32_t W32, int32_t C,
-                                               void *__restrict__ out, int64_t out_stride)
+                                               void *__restrict__ out, int64_t out_stride,
+                                               const ScaledEpi &se = ScaledEpi{},
+                                               const float *s_tau = nullptr)
 {
+    if constexpr (EPI == kEpiScaledF32 || EPI == kEpiScaledBits) {
+        scaled_epilogue<P, EPI>(acc, deg, row, w, W32, C, se, s_tau, out, out_stride);
+        return;
+    }
     const uint32_t tail = (uint32_t)C - 32u * (uint32_t)w; // channels from this word on
     if (EPI == BITGNN_EPI_THRESH_BITS) {
         // bit-sliced (value >= R), R = BIAS + deg/2, scanned from the low plane up
@@ -134,8 +218,9 @@ __global__ __launch_bounds__(kBlock) void bspmm_kernel(
     const uint32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ order, uint32_t N, const uint32_t *__restrict__ h32,
     int64_t h_stride32, int32_t C, int32_t W32, const uint32_t *__restrict__ seeds,
-    void *__restrict__ out, int64_t out_stride, RowSegments seg)
+    void *__restrict__ out, int64_t out_stride, RowSegments seg, ScaledEpi se)
 {
+    const float *s_tau = stage_tau<EPI>(se, C, W32);
     const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     const uint64_t v = t / (uint32_t)W32; // virtual row
     const int w = (int)(t - v * (uint32_t)W32);
@@ -245,7 +330,7 @@ __global__ __launch_bounds__(kBlock) void bspmm_kernel(
                 seg.partial[((size_t)v * seg.planes + p) * W32 + w] = acc[p];
         return;
     }
-    bspmm_epilogue<P, EPI>(acc, deg, row, w, W32, C, out, out_stride);
+    bspmm_epilogue<P, EPI>(acc, deg, row, w, W32, C, out, out_stride, se, s_tau);
 }
 
 // Long rows: the bit-sliced counts of a row's segments (and the threshold seed) are added
@@ -271,8 +356,9 @@ template <int P, int EPI>
 __global__ __launch_bounds__(kBlock) void bspmm_long_rows_kernel(
     const uint32_t *__restrict__ rowptr, const int32_t *__restrict__ order, int32_t C, int32_t W32,
     const uint32_t *__restrict__ seeds, void *__restrict__ out, int64_t out_stride,
-    RowSegments seg)
+    RowSegments seg, ScaledEpi se)
 {
+    const float *s_tau = stage_tau<EPI>(se, C, W32);
     const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     const int q = (int)(t % kMergeLanes);
     const uint64_t g = t / kMergeLanes; // (row, word); its lanes sit side by side in a wavefront
@@ -313,7 +399,7 @@ __global__ __launch_bounds__(kBlock) void bspmm_long_rows_kernel(
             sd[p] = seeds[((deg & 1u) * P + p) * W32 + w];
         planes_add<P>(acc, sd);
     }
-    bspmm_epilogue<P, EPI>(acc, deg, row, w, W32, C, out, out_stride);
+    bspmm_epilogue<P, EPI>(acc, deg, row, w, W32, C, out, out_stride, se, s_tau);
 }
 
 // Rows longer than a segment are split as in bspmm_kernel: a segment leaves its int32 sums
@@ -481,25 +567,26 @@ template <int P>
 void launch_bspmm_p(hipStream_t s, unsigned grid, int epilogue, const bitgnn_adj *adj,
                     const int32_t *col, const uint32_t *h32, int64_t h_stride32, int32_t C,
                     int32_t W32, const uint32_t *seeds, void *out, int64_t out_stride,
-                    const RowSegments &seg)
+                    const RowSegments &seg, const ScaledEpi &se)
 {
     const unsigned grid_long =
         (unsigned)(((uint64_t)seg.n_long * (uint32_t)W32 * kMergeLanes + kBlock - 1) / kBlock);
-    if (epilogue == BITGNN_EPI_THRESH_BITS) {
-        bspmm_kernel<P, BITGNN_EPI_THRESH_BITS><<<grid, kBlock, 0, s>>>(
-            adj->rowptr, col, adj->order, (uint32_t)adj->n, h32, h_stride32, C, W32, seeds, out,
-            out_stride, seg);
-        if (grid_long)
-            bspmm_long_rows_kernel<P, BITGNN_EPI_THRESH_BITS><<<grid_long, kBlock, 0, s>>>(
-                adj->rowptr, adj->order, C, W32, seeds, out, out_stride, seg);
-    } else {
-        bspmm_kernel<P, BITGNN_EPI_RAW_I32><<<grid, kBlock, 0, s>>>(
-            adj->rowptr, col, adj->order, (uint32_t)adj->n, h32, h_stride32, C, W32, seeds, out,
-            out_stride, seg);
-        if (grid_long)
-            bspmm_long_rows_kernel<P, BITGNN_EPI_RAW_I32><<<grid_long, kBlock, 0, s>>>(
-                adj->rowptr, adj->order, C, W32, seeds, out, out_stride, seg);
+#define BG_BSPMM_P(E)                                                                             \
+    do {                                                                                          \
+        bspmm_kernel<P, E><<<grid, kBlock, 0, s>>>(adj->rowptr, col, adj->order,                  \
+                                                   (uint32_t)adj->n, h32, h_stride32, C, W32,     \
+                                                   seeds, out, out_stride, seg, se);              \
+        if (grid_long)                                                                            \
+            bspmm_long_rows_kernel<P, E><<<grid_long, kBlock, 0, s>>>(                            \
+                adj->rowptr, adj->order, C, W32, seeds, out, out_stride, seg, se);                \
+    } while (0)
+    switch (epilogue) {
+    case BITGNN_EPI_THRESH_BITS: BG_BSPMM_P(BITGNN_EPI_THRESH_BITS); break;
+    case kEpiScaledBits: BG_BSPMM_P(kEpiScaledBits); break;
+    case kEpiScaledF32: BG_BSPMM_P(kEpiScaledF32); break;
+    default: BG_BSPMM_P(BITGNN_EPI_RAW_I32); break;
     }
+#undef BG_BSPMM_P
 }
 
 // rows in degree order, W32 words each, no padding
@@ -1019,8 +1106,9 @@ __global__ __launch_bounds__(kBlock) void bspmm_merge_kernel(
     const uint32_t *__restrict__ partial32, const uint32_t *__restrict__ row_vptr,
     const int32_t *__restrict__ order,
     const int32_t *__restrict__ deg, uint32_t n, int win, int32_t C, int32_t W32,
-    const uint32_t *__restrict__ seeds, void *__restrict__ out, int64_t out_stride)
+    const uint32_t *__restrict__ seeds, void *__restrict__ out, int64_t out_stride, ScaledEpi se)
 {
+    const float *s_tau = stage_tau<EPI>(se, C, W32);
     const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
     const uint32_t slot = t >> 2;
     const int q = t & 3;
@@ -1034,7 +1122,7 @@ __global__ __launch_bounds__(kBlock) void bspmm_merge_kernel(
     for (int p = 0; p < P; ++p)
         acc[p] = (EPI == BITGNN_EPI_THRESH_BITS) ? seeds[((d & 1u) * P + p) * W32 + w] : 0u;
     add_parts<P, PP>(acc, partial32, row_vptr[slot], row_vptr[slot + 1], q);
-    bspmm_epilogue<P, EPI>(acc, d, row, w, W32, C, out, out_stride);
+    bspmm_epilogue<P, EPI>(acc, d, row, w, W32, C, out, out_stride, se, s_tau);
 }
 
 // Output layer in aggregate-then-transform order, fused with the merge:
@@ -1236,33 +1324,36 @@ __global__ __launch_bounds__(kProjWaves * 64, NB <= 2 ? 8 : 4) void bspmm_merge_
 template <int P, int PP>
 void launch_merge_pp(hipStream_t s, int epilogue, const bitgnn_adj *adj, const uint32_t *partial32,
                      uint32_t rows, int win, int32_t C, int32_t W32, const uint32_t *seeds,
-                     void *out, int64_t out_stride)
+                     void *out, int64_t out_stride, const ScaledEpi &se)
 {
     const bitgnn_blocked *b = adj->blk;
     const unsigned grid = (unsigned)(((uint64_t)rows * 4 + kBlock - 1) / kBlock);
     if (grid == 0)
         return;
-    if (epilogue == BITGNN_EPI_THRESH_BITS)
-        bspmm_merge_kernel<P, BITGNN_EPI_THRESH_BITS, PP><<<grid, kBlock, 0, s>>>(
-            partial32, b->row_vptr, adj->order, adj->deg, rows, win, C, W32, seeds, out,
-            out_stride);
-    else
-        bspmm_merge_kernel<P, BITGNN_EPI_RAW_I32, PP><<<grid, kBlock, 0, s>>>(
-            partial32, b->row_vptr, adj->order, adj->deg, rows, win, C, W32, seeds, out,
-            out_stride);
+#define BG_MERGE_PP(E)                                                                            \
+    bspmm_merge_kernel<P, E, PP><<<grid, kBlock, 0, s>>>(partial32, b->row_vptr, adj->order,      \
+                                                         adj->deg, rows, win, C, W32, seeds, out, \
+                                                         out_stride, se)
+    switch (epilogue) {
+    case BITGNN_EPI_THRESH_BITS: BG_MERGE_PP(BITGNN_EPI_THRESH_BITS); break;
+    case kEpiScaledBits: BG_MERGE_PP(kEpiScaledBits); break;
+    case kEpiScaledF32: BG_MERGE_PP(kEpiScaledF32); break;
+    default: BG_MERGE_PP(BITGNN_EPI_RAW_I32); break;
+    }
+#undef BG_MERGE_PP
 }
 
 template <int P>
 void launch_merge_p(hipStream_t s, int epilogue, const bitgnn_adj *adj, const uint32_t *partial32,
                     uint32_t rows, int win, int32_t C, int32_t W32, const uint32_t *seeds,
-                    void *out, int64_t out_stride)
+                    void *out, int64_t out_stride, const ScaledEpi &se)
 {
     if (part_planes_for(adj->blk) == 8)
         launch_merge_pp<P, 8>(s, epilogue, adj, partial32, rows, win, C, W32, seeds, out,
-                              out_stride);
+                              out_stride, se);
     else
         launch_merge_pp<P, 10>(s, epilogue, adj, partial32, rows, win, C, W32, seeds, out,
-                               out_stride);
+                               out_stride, se);
 }
 
 // The aggregation kernel proper; `partial` receives PP planes of 16 bytes per part.
@@ -1382,9 +1473,10 @@ static int launch_seeds(bitgnn_ctx *ctx, hipStream_t s, int epilogue, const int3
     return BITGNN_OK;
 }
 
-int bg_launch_bspmm_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
-                            const uint64_t *hbits, int32_t C, int64_t h_stride, int epilogue,
-                            const int32_t *T, void *out, int64_t out_stride)
+static int launch_bspmm_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
+                                const uint64_t *hbits, int32_t C, int64_t h_stride, int epilogue,
+                                const int32_t *T, void *out, int64_t out_stride,
+                                const ScaledEpi &se)
 {
     const bitgnn_blocked *b = adj->blk;
     const int32_t W32 = (C + 31) / 32;
@@ -1438,19 +1530,19 @@ int bg_launch_bspmm_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *ad
         switch (P) {
         case 12:
             launch_merge_p<12>(s, epilogue, adj, (const uint32_t *)partial, merge_rows, win, C,
-                               W32, seeds, out, out_stride);
+                               W32, seeds, out, out_stride, se);
             break;
         case 16:
             launch_merge_p<16>(s, epilogue, adj, (const uint32_t *)partial, merge_rows, win, C,
-                               W32, seeds, out, out_stride);
+                               W32, seeds, out, out_stride, se);
             break;
         case 20:
             launch_merge_p<20>(s, epilogue, adj, (const uint32_t *)partial, merge_rows, win, C,
-                               W32, seeds, out, out_stride);
+                               W32, seeds, out, out_stride, se);
             break;
         default:
             launch_merge_p<26>(s, epilogue, adj, (const uint32_t *)partial, merge_rows, win, C,
-                               W32, seeds, out, out_stride);
+                               W32, seeds, out, out_stride, se);
             break;
         }
         BG_LAUNCH_CHECK(ctx, "bspmm_merge");
@@ -1588,7 +1680,8 @@ bool bg_prefer_blocked(const bitgnn_adj *adj, int passes, int64_t bytes_per_nnz,
 // 1 = CSR kernel, 2 = column-blocked kernel (the caller has checked that the form exists)
 static int launch_bspmm_path(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
                              const uint64_t *hbits, int32_t C, int64_t h_stride, int epilogue,
-                             const int32_t *T, void *out, int64_t out_stride, int force)
+                             const int32_t *T, void *out, int64_t out_stride, int force,
+                             const ScaledEpi &se = ScaledEpi{})
 {
     const int passes = (C + 127) / 128;
     bool blocked;
@@ -1602,8 +1695,8 @@ static int launch_bspmm_path(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *a
                                         ? adj->max_degree
                                         : (int64_t)adj->seg_len);
     if (blocked)
-        return bg_launch_bspmm_blocked(ctx, s, adj, hbits, C, h_stride, epilogue, T, out,
-                                       out_stride);
+        return launch_bspmm_blocked(ctx, s, adj, hbits, C, h_stride, epilogue, T, out, out_stride,
+                                    se);
     const int32_t W32 = (C + 31) / 32;
     const int P = planes_for(adj);
     const uint32_t *seeds;
@@ -1645,19 +1738,19 @@ static int launch_bspmm_path(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *a
     switch (P) {
     case 12:
         launch_bspmm_p<12>(s, (unsigned)grid, epilogue, adj, col, h32, hs32, C, W32, seeds, out,
-                           out_stride, seg);
+                           out_stride, seg, se);
         break;
     case 16:
         launch_bspmm_p<16>(s, (unsigned)grid, epilogue, adj, col, h32, hs32, C, W32, seeds, out,
-                           out_stride, seg);
+                           out_stride, seg, se);
         break;
     case 20:
         launch_bspmm_p<20>(s, (unsigned)grid, epilogue, adj, col, h32, hs32, C, W32, seeds, out,
-                           out_stride, seg);
+                           out_stride, seg, se);
         break;
     default:
         launch_bspmm_p<26>(s, (unsigned)grid, epilogue, adj, col, h32, hs32, C, W32, seeds, out,
-                           out_stride, seg);
+                           out_stride, seg, se);
         break;
     }
     bg_time_end(ctx, s);
@@ -1670,6 +1763,15 @@ int bg_launch_bspmm(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const
                     int64_t out_stride)
 {
     return launch_bspmm_path(ctx, s, adj, hbits, C, h_stride, epilogue, T, out, out_stride, 0);
+}
+
+int bg_launch_bspmm_scaled(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
+                           const uint64_t *hbits, int32_t C, int64_t h_stride, const float *r,
+                           const float *tau, void *out, int64_t out_stride)
+{
+    return launch_bspmm_path(ctx, s, adj, hbits, C, h_stride,
+                             tau ? kEpiScaledBits : kEpiScaledF32, nullptr, out, out_stride, 0,
+                             ScaledEpi{r, tau});
 }
 
 namespace {

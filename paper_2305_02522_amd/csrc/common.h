@@ -121,6 +121,7 @@ struct bitgnn_adj {
     int32_t *col;     // [nnz]
     int32_t *deg;     // [n]
     int32_t *order;   // [n] rows by decreasing degree
+    uint32_t n_ge[32]; // rows with at least 2^k neighbours (the first n_ge[k] of `order`)
     int32_t *col_slot; // [nnz] column indices as degree-order slots (large CSR-only graphs:
                        // gathers from a degree-ordered copy keep the hubs' rows together)
     // Row segments of the CSR bit-SpMM: a row longer than seg_len neighbours is walked by
@@ -193,6 +194,11 @@ int bg_launch_bgemm(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, int64
 int bg_launch_bspmm(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const uint64_t *hbits,
                     int32_t C, int64_t h_stride, int epilogue, const int32_t *T, void *out,
                     int64_t out_stride);
+// The bit aggregation with a float row factor: y = r[i] * (float)S (r null: 1), stored as floats
+// (tau null) or as the bits y >= tau[c].
+int bg_launch_bspmm_scaled(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
+                           const uint64_t *hbits, int32_t C, int64_t h_stride, const float *r,
+                           const float *tau, void *out, int64_t out_stride);
 int bg_launch_spmm_i32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const int32_t *Z,
                        int32_t M, int64_t z_stride, const float *alpha, void *out,
                        int64_t out_stride);
@@ -204,9 +210,6 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
                          const float *alpha, void *out, int64_t out_stride);
 int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj);
 void bg_free_blocked(bitgnn_blocked *b);
-int bg_launch_bspmm_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
-                            const uint64_t *hbits, int32_t C, int64_t h_stride, int epilogue,
-                            const int32_t *T, void *out, int64_t out_stride);
 int bg_ws_need(bitgnn_ctx *ctx, size_t bytes, const char *who);
 int bg_static_scratch_init(bitgnn_ctx *ctx);
 // Bytes of context workspace the aggregations on `adj` need for up to C aggregated

@@ -10,192 +10,463 @@
 // re-association.  A value is therefore reproducible bit for bit, which matters where it
 // decides an output bit.
 //
-// One wavefront per row (rows by decreasing degree, so the long ones start first), lanes
-// across channels: a neighbour's row is read as whole 256-byte segments.  The column ids
-// and factors of 64 neighbours (and, for bit rows, their words) are fetched with one load
-// each, two blocks / one block ahead, and handed out by lane reads; 16 neighbours' rows are
-// in flight per wavefront.  What bounds it (232,965 nodes, 110.6 M non-zeros): wide float
-// rows by the gathered bytes, nnz * 4 C, which the caches deliver at ~9.4 TB/s (C = 128:
-// 6.0 ms) -- the price of full-precision aggregation that the bit path avoids; rows of 128
-// bytes or less by the rate of gather requests (~1.7-2.0 ms whatever the width).  The output
-// of a BMM is therefore aggregated from its raw integers in int16 (XKIND 2: half the bytes,
-// C = 128: 3.2 ms) with the scale applied here.
+// Two forms:
+//  * teams: 16 lanes walk one row for a window of 16 V channels, V per lane, so a gather
+//    instruction serves four rows.  A team's 16 lanes hold the ids (as byte offsets) and
+//    factors of 16 neighbours and hand them out with DPP row broadcasts, which the address
+//    add and the multiply take as an operand: no scalar work per neighbour.
+//  * hubs: the sum of a row has a fixed order, so its adds are a serial chain, and on a
+//    power-law graph the longest row's chain is longer than everything else together.  Rows
+//    of at least hub_deg neighbours get a workgroup per 64 channels in which seven wavefronts
+//    gather and multiply (that has no order) and leave the products in LDS, and one wavefront
+//    does nothing but read and add them.
 #include "common.h"
+
+#include <type_traits>
 
 namespace {
 
-// a * b rounded to float by itself: the empty asm makes the product a value of its own,
-// so the compiler cannot contract it with the add that follows into a fused multiply-add
+constexpr int kSpBlock = 256;          // threads of a workgroup; of a launch with hubs:
+constexpr int kHubBlock = 512;
+constexpr int kTeam = 16;              // lanes of a team: one DPP row
+constexpr int kHubProd = 7;            // producer wavefronts of a hub workgroup
+constexpr int kHubPer = 16;            // neighbours a producer takes per stage (4 per team)
+constexpr int kHubStage = kHubProd * kHubPer;
+constexpr size_t kHubLds = 2ull * kHubStage * 64 * sizeof(float); // two stages of products
+
+// One rounded multiply, one rounded add: contraction is off, so the pair is never fused.
 __device__ __forceinline__ float mul_rounded(float a, float b)
 {
-    float p = a * b;
-    asm volatile("" : "+v"(p));
-    return p;
+#pragma clang fp contract(off)
+    return a * b;
+}
+__device__ __forceinline__ float add_rounded(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a + b;
 }
 
-// kTiles: 64-channel tiles a lane accumulates per walk of the row (1, 2 or 4: the smallest
-// that covers C, so that no register waits for a tile the row does not have).
-// kAhead: neighbours whose rows are in flight together.  The gathers are served by the
-// caches at a latency of microseconds, so what a wavefront keeps in flight sets the rate:
-// with 4 neighbours the kernel ran at the same speed on half the bytes.
+// Lane K of the caller's row of 16 lanes, to all 16 of them.
+template <int K> __device__ __forceinline__ uint32_t row_bcast(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + K, 0xF, 0xF, true);
+}
+template <int K> __device__ __forceinline__ float row_bcast_f(float v)
+{
+    return __int_as_float((int)row_bcast<K>((uint32_t)__float_as_int(v)));
+}
 
+template <int I> struct const_int {
+    static constexpr int value = I;
+};
+template <int B, int E, class F> __device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(const_int<B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
+// V consecutive values of a row of x as a lane loads them.
 // XKIND: 0 float rows, 1 packed +-1 rows, 2 int16 rows with a per-channel scale (the raw
 // integers of a BMM and its SCL: the value alpha_c * (float)z is formed here, with the same
 // single rounding as the BMM's own scale epilogue, from half the gathered bytes)
-template <int XKIND, bool BITS_OUT, int kTiles>
-__global__ __launch_bounds__(256) void spmm_f32_kernel(
-    const uint32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ order, uint32_t n, const void *__restrict__ xv, int64_t ldx,
-    const float *__restrict__ xscale, int32_t C, const float *__restrict__ r,
-    const float *__restrict__ f, const float *__restrict__ tau, void *__restrict__ outv,
-    int64_t ldo)
-{
-    constexpr bool XBITS = XKIND == 1;
-    constexpr int kAhead = kTiles == 4 ? 8 : 16;
-    // wave-uniform on purpose: row bounds, neighbour ids and row addresses then live in
-    // scalar registers and the loads take a scalar base plus a 32-bit lane offset
-    const uint32_t slot =
-        blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t lane = threadIdx.x & 63;
-    if (slot >= n) // wave-uniform
-        return;
-    const uint32_t i = (uint32_t)order[slot];
-    const uint32_t beg = rowptr[i], end = rowptr[i + 1];
-    const float ri = r ? r[i] : 1.0f;
-    const uint64_t *xb = (const uint64_t *)xv;
+template <int XKIND, int V> struct x_piece;
+template <int V> struct x_piece<0, V> {
+    float v[V];
+};
+template <int V> struct x_piece<1, V> {
+    uint32_t v;
+};
+template <int V> struct x_piece<2, V> {
+    int16_t v[V];
+};
 
-    for (int32_t c0 = 0; c0 < C; c0 += 64 * kTiles) {
-        float acc[kTiles], sc[kTiles];
-        uint32_t cc[kTiles];  // this lane's channel of every tile, clamped into the row
-        uint32_t off[kTiles]; // ... as a byte offset into a row of x
-        bool live[kTiles];
-#pragma unroll
-        for (int u = 0; u < kTiles; ++u) {
-            acc[u] = 0.0f;
-            const int32_t c = c0 + 64 * u + (int32_t)lane;
-            live[u] = c < C;
-            cc[u] = (uint32_t)(live[u] ? c : C - 1);
-            off[u] = cc[u] * (XKIND == 2 ? 2u : 4u);
-            sc[u] = XKIND == 2 ? xscale[cc[u]] : 1.0f;
+struct SpmmArgs {
+    const uint32_t *rowptr;
+    const int32_t *col;
+    const int32_t *order;
+    uint32_t n;
+    const void *x;
+    int64_t row_bytes; // bytes from one row of x to the next
+    const float *xscale;
+    int32_t C;
+    const float *r, *f, *tau;
+    void *out;
+    int64_t ldo;
+    uint32_t n_hub;       // rows (the first of the degree order) that take the hub form
+    uint32_t hub_tiles;   // 64-channel tiles of a hub row
+    uint32_t windows;      // channel windows of a row
+    uint32_t window_major; // order of the teams
+    uint32_t team_blocks;  // window_major: workgroups per window
+};
+
+// The sign a packed bit gives f: bit set -> +f, clear -> -f.  `inv` holds the inverted bit at
+// position 31 - sh.
+__device__ __forceinline__ float signed_f(uint32_t inv, uint32_t sh, float f)
+{
+    return __int_as_float((int)(((inv << sh) & 0x80000000u) ^ (uint32_t)__float_as_int(f)));
+}
+
+// What a lane reads of a row of x: V channels, nominally from c on.  At the end of a float or
+// integer row the lane is moved back to end with the row (it then shares channels with its
+// neighbour lane, which computes the same values); of a packed row it reads the 32-bit word
+// that holds its V bits.
+template <int XKIND, int V> struct x_lane {
+    int32_t cs;       // first channel read
+    uint32_t off;     // byte offset in the row
+    uint32_t bsh;     // packed rows: bit position of channel c in the word
+    static __device__ __forceinline__ int32_t first(const SpmmArgs &a, int32_t c)
+    {
+        return XKIND == 1 ? c : (c < a.C - V ? c : a.C - V);
+    }
+    __device__ __forceinline__ x_lane(const SpmmArgs &a, int32_t c) : cs(first(a, c)), bsh(0)
+    {
+        if (XKIND == 1) {
+            const int32_t dw = c >> 5, last = 2 * ((a.C + 63) / 64) - 1;
+            off = (uint32_t)(dw < last ? dw : last) * 4u;
+            bsh = (uint32_t)(c & 31);
+        } else {
+            off = (uint32_t)cs * (XKIND == 2 ? 2u : 4u);
         }
-        // The column ids of a block of 64 neighbours are requested two blocks ahead and
-        // their factors one block ahead, so that a block waits for its rows only.
-        auto ids_of = [&](uint32_t k) -> uint32_t { // lane's id in the block starting at k
-            if (k >= end)
-                return 0u;
-            const uint32_t c = end - k < 64u ? end - k : 64u;
-            return (uint32_t)col[k + (lane < c ? lane : c - 1)];
-        };
-        uint32_t jl = ids_of(beg);
-        uint32_t jl_next = ids_of(beg + 64);
-        float fl = f ? f[jl] : 1.0f;
-        for (uint32_t k0 = beg; k0 < end; k0 += 64) {
-            const uint32_t cnt = end - k0 < 64u ? end - k0 : 64u;
-            const float fl_next = f ? f[jl_next] : 1.0f; // node 0 past the end: never used
-            const uint32_t jl_after = ids_of(k0 + 128);
-            if (XBITS) {
-                // Bit rows: every lane fetches the words of its own neighbour (one gather
-                // per tile for 64 neighbours); a neighbour's word is then read from its
-                // lane and, being the same for all lanes, serves as a lane mask.
-                uint32_t wlo[kTiles], whi[kTiles];
+    }
+    // the piece of neighbour number K of the 16 whose ids the team's lanes hold
+    template <int K, bool BIG>
+    __device__ __forceinline__ x_piece<XKIND, V> load(const SpmmArgs &a, uint32_t id) const
+    {
+        typedef typename std::conditional<BIG, uint64_t, uint32_t>::type ofs_t;
+        const ofs_t rofs = (ofs_t)id * (ofs_t)a.row_bytes;
+        ofs_t o;
+        if constexpr (BIG)
+            o = ((uint64_t)row_bcast<K>((uint32_t)((uint64_t)rofs >> 32)) << 32) |
+                row_bcast<K>((uint32_t)rofs);
+        else
+            o = row_bcast<K>((uint32_t)rofs);
+        x_piece<XKIND, V> x;
+        __builtin_memcpy(&x, (const char *)a.x + (ofs_t)(o + off), sizeof(x));
+        return x;
+    }
+    template <bool HASF>
+    __device__ __forceinline__ void products(const x_piece<XKIND, V> &x, const float (&sc)[V],
+                                             float f, float (&p)[V]) const
+    {
+        if constexpr (XKIND == 1) {
+            const uint32_t inv = ~x.v >> bsh;
 #pragma unroll
-                for (int u = 0; u < kTiles; ++u) {
-                    uint64_t w = 0;
-                    if (c0 + 64 * u < C) // wave-uniform
-                        w = xb[(int64_t)jl * ldx + (c0 / 64 + u)];
-                    wlo[u] = (uint32_t)w;
-                    whi[u] = (uint32_t)(w >> 32);
-                }
-                // one neighbour: its factor and words are read from its lane; a word, being
-                // the same for all lanes, serves as the lane mask that picks +f or -f (a
-                // tile past the last channel sums zero words and is never stored)
-                auto add_neighbour = [&](int t) {
-                    const float fj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fl), t));
+            for (int v = 0; v < V; ++v)
+                p[v] = signed_f(inv, 31u - (uint32_t)v, f);
+        } else {
 #pragma unroll
-                    for (int u = 0; u < kTiles; ++u) {
-                        const uint64_t word =
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)wlo[u], t) |
-                            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)whi[u], t) << 32);
-                        const float x = __builtin_amdgcn_inverse_ballot_w64(word) ? 1.0f : -1.0f;
-                        acc[u] = acc[u] + mul_rounded(fj, x);
-                    }
-                };
-                uint32_t t = 0;
-                for (; t + 4 <= cnt; t += 4) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        add_neighbour((int)t + q);
-                }
-                for (; t < cnt; ++t)
-                    add_neighbour((int)t);
-            }
-            // The scalar unit is what limits narrow rows, so a neighbour costs it as little
-            // as possible: the 64-bit row offset is computed once per lane for the block's
-            // 64 neighbours and handed out by lane reads (lanes past the block's end repeat
-            // its last neighbour, so a turn needs no clamping), and a full turn adds its
-            // neighbours without asking whether each exists.
-            const uint64_t rofs = (uint64_t)jl * (uint64_t)(ldx * (XKIND == 2 ? 2 : 4));
-            const uint32_t rlo = (uint32_t)rofs, rhi = (uint32_t)(rofs >> 32);
-            for (uint32_t t = 0; !XBITS && t < cnt; t += kAhead) {
-                float fq[kAhead], xq[kAhead][kTiles];
-#pragma unroll
-                for (int q = 0; q < kAhead; ++q) {
-                    const int tt = (int)t + q; // < 64, wave-uniform
-                    const uint64_t ro =
-                        (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)rlo, tt) |
-                        ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)rhi, tt) << 32);
-                    fq[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fl), tt));
-                    const char *rowp = (const char *)xv + ro; // scalar
-#pragma unroll
-                    for (int u = 0; u < kTiles; ++u) {
-                        if (XKIND == 2)
-                            xq[q][u] = (float)*(const int16_t *)(rowp + off[u]);
-                        else
-                            xq[q][u] = *(const float *)(rowp + off[u]);
-                    }
-                }
-                if (cnt - t >= (uint32_t)kAhead) {
-#pragma unroll
-                    for (int q = 0; q < kAhead; ++q)
-#pragma unroll
-                        for (int u = 0; u < kTiles; ++u) {
-                            const float x =
-                                XKIND == 2 ? mul_rounded(sc[u], xq[q][u]) : xq[q][u];
-                            acc[u] = acc[u] + mul_rounded(fq[q], x);
-                        }
-                } else {
-#pragma unroll
-                    for (int q = 0; q < kAhead; ++q) {
-                        if (t + q < cnt) { // wave-uniform
-#pragma unroll
-                            for (int u = 0; u < kTiles; ++u) {
-                                const float x =
-                                    XKIND == 2 ? mul_rounded(sc[u], xq[q][u]) : xq[q][u];
-                                acc[u] = acc[u] + mul_rounded(fq[q], x);
-                            }
-                        }
-                    }
-                }
-            }
-            jl = jl_next;
-            jl_next = jl_after;
-            fl = fl_next;
-        }
-#pragma unroll
-        for (int u = 0; u < kTiles; ++u) {
-            if (c0 + 64 * u >= C)
-                continue;
-            const float y = mul_rounded(ri, acc[u]);
-            if (BITS_OUT) {
-                const bool bit = live[u] && y >= tau[cc[u]];
-                const uint64_t word = __ballot(bit);
-                if (lane == 0)
-                    ((uint64_t *)outv)[(int64_t)i * ldo + (c0 / 64 + u)] = word;
-            } else if (live[u]) {
-                ((float *)outv)[(int64_t)i * ldo + cc[u]] = y;
+            for (int v = 0; v < V; ++v) {
+                p[v] = (float)x.v[v];
+                if (XKIND == 2)
+                    p[v] = mul_rounded(sc[v], p[v]);
+                if (HASF)
+                    p[v] = mul_rounded(f, p[v]);
             }
         }
     }
+};
+
+// One hub row, one 64-channel tile.  Wavefront 0 adds; the others produce, each the products
+// of kHubPer neighbours per stage: a team of 16 lanes takes one neighbour at a time, V
+// channels per lane, as in the team form, so an instruction serves four neighbours.  LDS holds
+// two stages as [neighbour][64 channels].
+template <int XKIND, bool BITS_OUT, bool HASF, int V, bool BIG>
+__device__ __forceinline__ void spmm_hub_row(const SpmmArgs &a, uint32_t slot, uint32_t tile,
+                                             float *prod)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t i = (uint32_t)a.order[slot];
+    const uint32_t beg = a.rowptr[i], end = a.rowptr[i + 1], deg = end - beg; // deg > 0
+    // Stages come in blocks of four, whatever is left of the row: a loop exit in between would
+    // make the compiler wait there for every load in flight.
+    const uint32_t blocks = (deg + 4 * kHubStage - 1) / (4 * kHubStage);
+    const int32_t c0 = (int32_t)(tile * 64);
+    // (nothing is scheduled across: arithmetic hoisted over it would wait for its loads there)
+    auto barrier = [] {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (wave > 0) {
+        typedef x_piece<XKIND, V> piece;
+        const uint32_t p = (uint32_t)wave - 1, q = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15;
+        const x_lane<XKIND, V> xl(a, c0 + (int32_t)sub * V);
+        float sc[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            sc[v] = XKIND == 2 ? a.xscale[xl.cs + v] : 1.0f;
+        // A team's 16 lanes hold the ids of its neighbours of four stages (four per stage).
+        auto ids_of = [&](uint32_t b) -> uint32_t {
+            const uint32_t k =
+                (4 * b + (sub >> 2)) * kHubStage + p * kHubPer + 4 * (sub & 3) + q;
+            return (uint32_t)a.col[beg + (k < deg ? k : deg - 1)];
+        };
+        auto load = [&](uint32_t id, auto jj, piece (&x)[4]) {
+            constexpr int J = decltype(jj)::value;
+            static_for<0, 4>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                x[K] = xl.template load<4 * J + K, BIG>(a, id);
+            });
+        };
+        auto products = [&](auto jj, const piece (&x)[4], float fl) {
+            constexpr int J = decltype(jj)::value;
+            float *dst = prod + (J & 1) * (kHubStage * 64) + (p * kHubPer + q) * 64 + sub * V;
+            static_for<0, 4>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                const float fk = HASF ? row_bcast_f<4 * J + K>(fl) : 1.0f;
+                float v[V];
+                xl.template products<HASF>(x[K], sc, fk, v);
+                __builtin_memcpy(__builtin_assume_aligned(dst + 4 * K * 64, 4 * V), v, sizeof(v));
+            });
+        };
+        // Rows are requested three stages ahead, ids and factors a block of four stages ahead.
+        piece x[4][4];
+        uint32_t ida = ids_of(0), idb = ids_of(1);
+        float fa = HASF ? a.f[ida] : 1.0f;
+        __builtin_amdgcn_sched_barrier(0); // ids and factors stay older than the rows
+        load(ida, const_int<0>{}, x[0]);
+        load(ida, const_int<1>{}, x[1]);
+        load(ida, const_int<2>{}, x[2]);
+        for (uint32_t b = 0; b < blocks; ++b) {
+            const uint32_t idc = ids_of(b + 2);
+            const float fb = HASF ? a.f[idb] : 1.0f;
+            load(ida, const_int<3>{}, x[3]);
+            __builtin_amdgcn_sched_barrier(0);
+            products(const_int<0>{}, x[0], fa);
+            barrier();
+            load(idb, const_int<0>{}, x[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            products(const_int<1>{}, x[1], fa);
+            barrier();
+            load(idb, const_int<1>{}, x[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            products(const_int<2>{}, x[2], fa);
+            barrier();
+            load(idb, const_int<2>{}, x[2]);
+            __builtin_amdgcn_sched_barrier(0);
+            products(const_int<3>{}, x[3], fa);
+            barrier();
+            ida = idb;
+            idb = idc;
+            fa = fb;
+        }
+        return;
+    }
+    // the consumer: lane = channel, one add per neighbour in stored order
+    const int32_t c = c0 + lane;
+    const bool live = c < a.C;
+    const int32_t cc = live ? c : a.C - 1;
+    // the lane's place in a neighbour's 64 products (a producer lane at the end of the row
+    // holds V channels that end with the row)
+    const int32_t piece0 = (cc - c0) / V * V;
+    const int32_t at = piece0 + (cc - x_lane<XKIND, V>::first(a, c0 + piece0));
+    float acc = 0.0f;
+    for (uint32_t s = 0; s < 4 * blocks; ++s) {
+        barrier(); // the products of stage s are in LDS
+        const float *src = prod + (s & 1u) * (kHubStage * 64) + at;
+        const uint32_t done = s * kHubStage, left = deg > done ? deg - done : 0u;
+        if (left >= (uint32_t)kHubStage) {
+            // (three batches ahead: the adds of one batch take half of an LDS latency)
+            constexpr int kBatch = 16, kBatches = kHubStage / kBatch, kDeep = 3;
+            static_assert(kHubStage % kBatch == 0 && kBatches > kDeep, "whole batches");
+            float v[kDeep + 1][kBatch];
+#pragma unroll
+            for (int b = 0; b < kDeep; ++b)
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k)
+                    v[b][k] = src[(b * kBatch + k) * 64];
+#pragma unroll
+            for (int b = 0; b < kBatches; ++b) {
+                if (b + kDeep < kBatches)
+#pragma unroll
+                    for (int k = 0; k < kBatch; ++k)
+                        v[(b + kDeep) % (kDeep + 1)][k] = src[((b + kDeep) * kBatch + k) * 64];
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k)
+                    acc = add_rounded(acc, v[b % (kDeep + 1)][k]);
+            }
+        } else {
+            for (uint32_t k = 0; k < left; ++k)
+                acc = add_rounded(acc, src[k * 64]);
+        }
+    }
+    const float y = mul_rounded(a.r ? a.r[i] : 1.0f, acc);
+    if (BITS_OUT) {
+        const uint64_t word = __ballot(live && y >= a.tau[cc]);
+        if (lane == 0)
+            ((uint64_t *)a.out)[(int64_t)i * a.ldo + tile] = word;
+    } else if (live) {
+        ((float *)a.out)[(int64_t)i * a.ldo + c] = y;
+    }
+}
+
+// A team per row and channel window; tb: number of the workgroup among those of the teams.
+template <int XKIND, bool BITS_OUT, bool HASF, int V, bool BIG, int kThreads>
+__device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
+{
+    // window and row of this team: the windows of a row side by side (one instruction then
+    // covers adjacent pieces of a row), or one window of all rows after the other
+    const uint32_t team = tb * (kThreads / kTeam) + threadIdx.x / kTeam;
+    uint32_t window, team_row;
+    if (a.window_major) {
+        window = tb / a.team_blocks;
+        team_row = team - window * a.team_blocks * (kThreads / kTeam);
+    } else {
+        team_row = team / a.windows;
+        window = team - team_row * a.windows;
+    }
+    const uint32_t sub = threadIdx.x & 15;
+    const uint32_t slot = a.n_hub + team_row;
+    const bool has = slot < a.n;
+    const uint32_t i = has ? (uint32_t)a.order[slot] : 0u;
+    const uint32_t beg = has ? a.rowptr[i] : 0u, deg = has ? a.rowptr[i + 1] - beg : 0u;
+    // row lengths of the wavefront's four teams (scalar)
+    uint32_t dmin = (uint32_t)__builtin_amdgcn_readlane((int)deg, 0), dmax = dmin;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+        const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)deg, 16 * q);
+        dmin = d < dmin ? d : dmin;
+        dmax = d > dmax ? d : dmax;
+    }
+    const int32_t c = (int32_t)(window * (kTeam * V) + sub * V); // this lane's first channel
+    const x_lane<XKIND, V> xl(a, c);
+    float sc[V], acc[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        acc[v] = 0.0f;
+        sc[v] = XKIND == 2 ? a.xscale[xl.cs + v] : 1.0f;
+    }
+    typedef x_piece<XKIND, V> piece;
+    // rows in flight: two sets of 8 (4 where a piece is 16 bytes: two sets of 8 spill)
+    constexpr int kAhead = sizeof(piece) >= 16 ? 4 : 8;
+
+    // The lane's neighbour of the block at t; past the row's end its last one, of an empty row
+    // any (the first entry of the column array is always a valid node).
+    auto ids_of = [&](uint32_t t) -> uint32_t {
+        const uint32_t k = t + sub;
+        return (uint32_t)a.col[k < deg ? beg + k : deg ? beg + deg - 1 : 0u];
+    };
+    // kAhead neighbours (from the first'th on) of the block whose ids the team holds
+    auto load = [&](uint32_t id, auto first, piece (&x)[kAhead]) {
+        constexpr int K0 = decltype(first)::value;
+        static_for<0, kAhead>([&](auto kk) {
+            constexpr int K = decltype(kk)::value;
+            x[K] = xl.template load<K0 + K, BIG>(a, id);
+        });
+    };
+    auto consume = [&](float fl, auto first, const piece (&x)[kAhead], uint32_t t, auto full) {
+        constexpr int K0 = decltype(first)::value;
+        static_for<0, kAhead>([&](auto kk) {
+            constexpr int K = decltype(kk)::value;
+            const float fk = HASF ? row_bcast_f<K0 + K>(fl) : 1.0f;
+            if (decltype(full)::value || t + K0 + K < deg) {
+                float p[V];
+                xl.template products<HASF>(x[K], sc, fk, p);
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    acc[v] = add_rounded(acc[v], p[v]);
+            }
+        });
+    };
+    // The ids of a block of 16 neighbours are requested two blocks ahead, the factors one
+    // block ahead, the rows kAhead neighbours ahead.
+    uint32_t id0 = ids_of(0), id1 = ids_of(16);
+    float f0 = HASF ? a.f[id0] : 1.0f;
+    piece x[2][kAhead];
+    __builtin_amdgcn_sched_barrier(0); // ids and factors stay older than the rows
+    load(id0, const_int<0>{}, x[0]);
+    auto step = [&](uint32_t t, auto full) {
+        const float f1 = HASF ? a.f[id1] : 1.0f;
+        const uint32_t id2 = ids_of(t + 32);
+        static_for<0, 16 / kAhead>([&](auto qq) {
+            constexpr int Q = decltype(qq)::value;
+            if constexpr (Q + 1 < 16 / kAhead)
+                load(id0, const_int<(Q + 1) * kAhead>{}, x[(Q + 1) & 1]);
+            else
+                load(id1, const_int<0>{}, x[0]);
+            __builtin_amdgcn_sched_barrier(0); // the requests go out before the sums wait
+            consume(f0, const_int<Q * kAhead>{}, x[Q & 1], t, full);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        id0 = id1;
+        id1 = id2;
+        f0 = f1;
+    };
+    // First the blocks that are whole for all four teams.  No load stands behind a branch: the
+    // waits after it would have to be for every load in flight.
+    uint32_t t = 0;
+    for (; t + 16 <= dmin; t += 16)
+        step(t, std::true_type{});
+    for (; t < dmax; t += 16)
+        step(t, std::false_type{});
+    const float ri = (a.r && has) ? a.r[i] : 1.0f;
+    if (BITS_OUT) {
+        // the lane's V bits at their nominal positions (channels past C fall off), OR-ed over
+        // the lanes that share a 32-bit word
+        uint32_t bits = 0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int32_t cv = xl.cs + v;
+            const bool bit =
+                cv < a.C && mul_rounded(ri, acc[v]) >= a.tau[cv < a.C ? cv : a.C - 1];
+            bits |= bit ? (1u << v) : 0u;
+        }
+        const uint32_t back = (uint32_t)(c - xl.cs);
+        bits = back < (uint32_t)V ? bits >> back : 0u;
+        uint32_t w = bits << (c & 31);
+        w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);
+        w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xF, 0xF, false);
+        if (V <= 4)
+            w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x141, 0xF, 0xF, false);
+        if (V == 1)
+            w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x140, 0xF, 0xF, false);
+        // one lane per 32-bit word; V = 1 covers half a word, its team also clears the rest
+        const int32_t words32 = 2 * ((a.C + 63) / 64);
+        uint32_t *o = (uint32_t *)a.out + (int64_t)i * a.ldo * 2;
+        if (has && (c & 31) == 0 && (c >> 5) < words32)
+            o[c >> 5] = w;
+        if (V == 1 && has && sub == 1)
+            o[1] = 0u;
+    } else if (has) {
+        float y[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            y[v] = mul_rounded(ri, acc[v]);
+        float *o = (float *)a.out + (int64_t)i * a.ldo;
+        if (XKIND == 1) {
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (c + v < a.C)
+                    o[c + v] = y[v];
+        } else if (c < a.C) {
+            __builtin_memcpy(o + xl.cs, y, sizeof(y));
+        }
+    }
+}
+
+// V: channels per lane of a team.  BIG: the rows of x span 4 GiB or more (64-bit offsets).
+// HUBS: the launch starts with hub workgroups; their registers and LDS halve the wavefronts of the other rows,
+// so launches without hubs take a kernel of their own.
+template <int XKIND, bool BITS_OUT, bool HASF, int V, bool BIG, bool HUBS>
+__global__ __launch_bounds__(HUBS ? kHubBlock : kSpBlock, 4) void spmm_f32_kernel(
+    const SpmmArgs a)
+{
+    constexpr int kThreads = HUBS ? kHubBlock : kSpBlock;
+    uint32_t tb = blockIdx.x;
+    if constexpr (HUBS) {
+        extern __shared__ float prod[];
+        const uint32_t hub_blocks = a.n_hub * a.hub_tiles;
+        if (tb < hub_blocks) { // workgroup-uniform; the longest rows start first
+            spmm_hub_row<XKIND, BITS_OUT, HASF, V == 1 ? 1 : 4, BIG>(a, tb / a.hub_tiles,
+                                                                     tb % a.hub_tiles, prod);
+            return;
+        }
+        tb -= hub_blocks;
+    }
+    spmm_team_rows<XKIND, BITS_OUT, HASF, V, BIG, kThreads>(a, tb);
 }
 
 } // namespace
@@ -238,40 +509,101 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     if (adj->n == 0)
         return BITGNN_OK;
     const bool bits_out = epilogue == BITGNN_EPI_THRESH_BITS;
-    const unsigned grid = (unsigned)((adj->n + 3) / 4);
-#define BG_SPMM_F32T(XK, BO, TL)                                                                  \
-    spmm_f32_kernel<XK, BO, TL><<<grid, 256, 0, s>>>(adj->rowptr, adj->col, adj->order,          \
-                                                     (uint32_t)adj->n, x, ldx, xscale, C, r, f,   \
-                                                     tau, out, ldo)
-#define BG_SPMM_F32(XK, BO)                                                                       \
-    do {                                                                                          \
-        if (C <= 64)                                                                              \
-            BG_SPMM_F32T(XK, BO, 1);                                                              \
-        else if (C <= 128)                                                                        \
-            BG_SPMM_F32T(XK, BO, 2);                                                              \
-        else                                                                                      \
-            BG_SPMM_F32T(XK, BO, 4);                                                              \
-    } while (0)
+    // +-1 rows without factors: the float sum of a row is its integer sum, exact while partial
+    // sums stay below 2^24, so the bit aggregation's counters give it (89,250 nodes, 877 K
+    // non-zeros, 500 channels: 108 -> 41 us).  It needs the workspace; without it the floats
+    // are added here, and so they are on small graphs, where the bit aggregation's fixed cost
+    // (17-30 us with its long-row and merge launches) is what counts: 2,839 nodes, 260 K
+    // non-zeros, 64 channels 26 against 9 us, 512 channels 20 against 20; 20,000 nodes, 598 K
+    // non-zeros, 64 channels 13 against 9, 128 channels 10 against 14.
+    if (x_is_bits && !xscale && !f && C <= 2048 && adj->max_degree < (1ll << 24) &&
+        adj->nnz * (int64_t)C >= 48000000 &&
+        bg_adj_workspace_bytes(adj, C, 1) <= ctx->sc->ws_bytes)
+        return bg_launch_bspmm_scaled(ctx, s, adj, (const uint64_t *)x, C, ldx, r,
+                                      bits_out ? tau : nullptr, out, ldo);
+    SpmmArgs a;
+    a.rowptr = adj->rowptr;
+    a.col = adj->col;
+    a.order = adj->order;
+    a.n = (uint32_t)adj->n;
+    a.x = x;
+    a.row_bytes = ldx * (xscale ? 2 : x_is_bits ? 8 : 4);
+    a.xscale = xscale;
+    a.C = C;
+    a.r = r;
+    a.f = f;
+    a.tau = tau;
+    a.out = out;
+    a.ldo = ldo;
+    // Hub rows: those whose serial walk by a team (45-65 ns a neighbour) would last a good part
+    // of the launch, at least 2^9 neighbours, 2^11 with bit rows, whose team form takes fewer
+    // instructions per neighbour than the hub form.  Measured on an R-MAT graph (131,072 nodes,
+    // 3.86 M non-zeros, longest row 15,635) for thresholds 2^8 .. 2^12: int16 rows of 40
+    // channels 101 92 126 122 267 us (1,027 without hubs), float rows of 64 106 102 136 134 295
+    // (1,059), bit rows of 256 273 208 208 176 285 (1,188).
+    int k = x_is_bits && !xscale ? 11 : 9;
+    // They take wavefronts from the other rows and gather more slowly than teams do, so they are
+    // used only where the longest row's walk by a team would last more than half of the gathers
+    // (about 70 G cache lines a second).  232,965 nodes, 110.6 M non-zeros, longest row 9,735,
+    // int16 rows of 41 channels: 1,675 us without hubs, 2,063 with; 300,001 nodes, 14.7 M
+    // non-zeros, longest row 3,676, float rows of 64 channels: 397 without, 353 with.
+    const int lines = (C * (xscale ? 16 : x_is_bits ? 1 : 32) + 1023) / 1024;
+    a.n_hub = 2.0 * 65.0 * (double)adj->max_degree > (double)adj->nnz * lines / 70.0 ? adj->n_ge[k]
+                                                                                    : 0;
+    a.hub_tiles = ((uint32_t)C + 63) / 64;
+    // channels per lane: 16 bytes of a float row, 8 of an integer row, 4 or 8 bits; narrow
+    // rows spread over all lanes of a team
+    const int V = x_is_bits && !xscale ? (C <= 64 ? 4 : 8) : C <= 16 ? 1 : 4;
+    a.windows = ((uint32_t)C + kTeam * V - 1) / (kTeam * V);
+    const uint64_t rows = a.n - a.n_hub;
+    const uint32_t threads = a.n_hub ? kHubBlock : kSpBlock, kTeams = threads / kTeam;
+    a.team_blocks = (uint32_t)((rows + kTeams - 1) / kTeams);
+    // One window of all rows after the other keeps a smaller table hot in L2; it pays when the
+    // windows are whole cache lines and nothing but the rows is gathered (300,001 nodes, 128
+    // floats: 683 us against 769; with factors, which are gathered once per window, it loses).
+    a.window_major = a.windows > 1 && !f && !x_is_bits && a.row_bytes % 128 == 0 &&
+                     bg_aligned(x, 128) &&
+                     (uint64_t)adj->n * (uint64_t)a.row_bytes > (8u << 20);
+    const uint64_t grid = (uint64_t)a.n_hub * a.hub_tiles +
+                          (a.window_major ? (uint64_t)a.windows * a.team_blocks
+                                          : (rows * a.windows + kTeams - 1) / kTeams);
+    BG_REQUIRE(ctx, grid < (1ull << 31), BITGNN_ERR_UNSUPPORTED, "bitgnn_spmm_f32: N*C too large");
+    const bool big = (uint64_t)adj->n * (uint64_t)a.row_bytes >= (1ull << 32);
     bg_time_begin(ctx, s);
+    auto launch = [&](auto xk, auto v) {
+        constexpr int XK = decltype(xk)::value, VV = decltype(v)::value;
+        auto go = [&](auto bo, auto hf, auto bg) {
+            constexpr bool BO = decltype(bo)::value, HF = decltype(hf)::value,
+                           BG = decltype(bg)::value;
+            if (a.n_hub)
+                spmm_f32_kernel<XK, BO, HF, VV, BG, true>
+                    <<<(unsigned)grid, threads, kHubLds, s>>>(a);
+            else
+                spmm_f32_kernel<XK, BO, HF, VV, BG, false><<<(unsigned)grid, threads, 0, s>>>(a);
+        };
+        auto go2 = [&](auto bo, auto hf) {
+            big ? go(bo, hf, std::true_type{}) : go(bo, hf, std::false_type{});
+        };
+        auto go3 = [&](auto bo) { f ? go2(bo, std::true_type{}) : go2(bo, std::false_type{}); };
+        bits_out ? go3(std::true_type{}) : go3(std::false_type{});
+    };
     if (xscale) {
-        if (bits_out)
-            BG_SPMM_F32(2, true);
+        if (V == 1)
+            launch(const_int<2>{}, const_int<1>{});
         else
-            BG_SPMM_F32(2, false);
+            launch(const_int<2>{}, const_int<4>{});
     } else if (x_is_bits) {
-        if (bits_out)
-            BG_SPMM_F32(1, true);
+        if (V == 4)
+            launch(const_int<1>{}, const_int<4>{});
         else
-            BG_SPMM_F32(1, false);
+            launch(const_int<1>{}, const_int<8>{});
     } else {
-        if (bits_out)
-            BG_SPMM_F32(0, true);
+        if (V == 1)
+            launch(const_int<0>{}, const_int<1>{});
         else
-            BG_SPMM_F32(0, false);
+            launch(const_int<0>{}, const_int<4>{});
     }
     bg_time_end(ctx, s);
-#undef BG_SPMM_F32
-#undef BG_SPMM_F32T
     BG_LAUNCH_CHECK(ctx, "bitgnn_spmm_f32");
     return BITGNN_OK;
 }

@@ -493,6 +493,82 @@ def test_spmm_i16_scaled_integers(B, ctx, n, e, C, hubs):
     adj.close()
 
 
+@pytest.mark.parametrize("C", [1, 3, 16, 17, 40, 65, 130])
+def test_spmm_f32_long_rows(B, ctx, C):
+    """Rows around the lengths where the float aggregation changes form (hub workgroups from
+    512 neighbours, 2,048 with bit rows; 112 neighbours per stage, stages in fours), for every
+    operand type.  Order and roundings are fixed, so the values are compared bit for bit."""
+    n = 2600
+    lens = [0, 1, 15, 16, 17, 511, 512, 559, 560, 561, 671, 672, 673, 1007, 1008, 1009, 1120, 2047,
+            2048, 2128, 2129, 2600]
+    r = np.random.default_rng(500 + C)
+    src = np.repeat(np.arange(len(lens)), lens).astype(np.int32)
+    dst = np.concatenate([np.sort(r.permutation(n)[:k]) for k in lens]).astype(np.int32)
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, 0)
+    rp, col = orc.adjacency(src, dst, n, 0)
+    f = r.uniform(-1.5, 1.5, n).astype(np.float32)
+    rv = r.uniform(-1.0, 1.0, n).astype(np.float32)
+    alpha = r.uniform(0.5, 1.5, C).astype(np.float32)
+    tau = r.uniform(-0.5, 0.5, C).astype(np.float32)
+    cw = (C + 63) // 64
+    v, z = W.pm1(r, (n, C)), r.integers(-900, 901, size=(n, C)).astype(np.int16)
+    xf = r.standard_normal((n, C)).astype(np.float32)
+    out = torch.empty((n, C), dtype=torch.float32, device="cuda")
+    ob = torch.empty((n, cw), dtype=torch.int64, device="cuda")
+    ldz = C + (C & 1)
+    zd = dev(np.pad(z, ((0, 0), (0, ldz - C))))
+    for fv in (f, None):
+        fd = None if fv is None else dev(fv)
+        for kind, x in (("f32", xf), ("bits", v.astype(np.float32)),
+                        ("i16", orc.scale(z.astype(np.int64), alpha))):
+            want = orc.spmm_weighted_f32(rp, col, x, rv, fv)
+            for epi, t, o, ldo in ((B.EPI_SCALE_F32, None, out, C),
+                                   (B.EPI_THRESH_BITS, dev(tau), ob, cw)):
+                if kind == "i16":
+                    B.spmm_i16(ctx, adj, zd, C, ldz, dev(alpha), dev(rv), fd, epi, t, o, ldo)
+                else:
+                    xd = dev(xf) if kind == "f32" else _pack_host(v)
+                    B.spmm_f32(ctx, adj, xd, kind == "bits", C, C if kind == "f32" else cw,
+                               dev(rv), fd, epi, t, o, ldo)
+            torch.cuda.synchronize()
+            # +0 and -0 compare equal here: an empty row times a negative factor
+            assert np.array_equal(out.cpu().numpy(), want), (kind, fv is None)
+            assert np.array_equal(words_np(ob), orc.to_words(orc.rebin_f32(want, tau))), kind
+    adj.close()
+
+
+@pytest.mark.parametrize("C", [31, 64, 300])
+def test_spmm_f32_bits_without_factors(B, ctx, tuned, C):
+    """+-1 rows without factors go through the bit aggregation (both formats), or, on a context
+    whose workspace is too small for that, through the float sums: the same values."""
+    n = 900
+    adj, rp, col, r = _graph(B, ctx, n, 30000, W.ADJ_SYMMETRIZE, 70 + C, 2)
+    B.ctx_reserve(ctx, B.adj_workspace_bytes(ctx, adj, C, 1))
+    small = B.Context(0)
+    v = W.pm1(r, (n, C))
+    rv = r.uniform(-1.0, 1.0, n).astype(np.float32)
+    tau = r.uniform(-0.5, 0.5, C).astype(np.float32)
+    cw = (C + 63) // 64
+    for rr in (rv, None):
+        want = orc.spmm_weighted_f32(rp, col, v.astype(np.float32), rr, None)
+        for c in (ctx, small):
+            out = torch.full((n, C + 1), 7.0, dtype=torch.float32, device="cuda")
+            ob = torch.full((n, cw + 1), -1, dtype=torch.int64, device="cuda")
+            rd = None if rr is None else dev(rr)
+            B.spmm_f32(c, adj, _pack_host(v), True, C, cw, rd, None, B.EPI_SCALE_F32, None, out,
+                       C + 1)
+            B.spmm_f32(c, adj, _pack_host(v), True, C, cw, rd, None, B.EPI_THRESH_BITS, dev(tau),
+                       ob, cw + 1)
+            torch.cuda.synchronize()
+            got = out.cpu().numpy()
+            assert np.array_equal(got[:, :C], want) and np.all(got[:, C] == 7.0)
+            gb = words_np(ob)
+            assert np.array_equal(gb[:, :cw], orc.to_words(orc.rebin_f32(want, tau)))
+            assert np.all(gb[:, cw] == np.uint64(0xFFFFFFFFFFFFFFFF))
+    small.close()
+    adj.close()
+
+
 def test_spmm_f32_rejects_bad_arguments(B, ctx):
     adj, rp, col, r = _graph(B, ctx, 50, 200, SYM_LOOPS, 5)
     x = torch.zeros((50, 8), dtype=torch.float32, device="cuda")
