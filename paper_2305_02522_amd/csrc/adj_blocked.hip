@@ -77,11 +77,13 @@ __global__ void slot_kernel(const int32_t *__restrict__ order, const int32_t *__
         atomicAdd(n_multi, 1u);
 }
 
-// keys (row slot << cbits | column slot), one wavefront per row
+// keys (row slot << cbits | column slot), one wavefront per row.  A symmetric adjacency gives
+// the same set with the two exchanged, and then the keys are written in column order: only
+// the row bits are left to sort (18 of 36 bits on 232,965 nodes: three passes, not five).
 __global__ __launch_bounds__(256) void blocked_keys_kernel(
     const uint32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ order, const int32_t *__restrict__ rank,
-    const uint32_t *__restrict__ rp2, uint32_t n, int cbits, uint64_t *__restrict__ keys)
+    const uint32_t *__restrict__ rp2, uint32_t n, int cbits, bool sym, uint64_t *__restrict__ keys)
 {
     const uint32_t s = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -89,8 +91,10 @@ __global__ __launch_bounds__(256) void blocked_keys_kernel(
         return;
     const int32_t i = order[s];
     const uint32_t beg = rowptr[i], d = rowptr[i + 1] - beg, o = rp2[s];
-    for (uint32_t k = lane; k < d; k += 64)
-        keys[o + k] = ((uint64_t)s << cbits) | (uint32_t)rank[col[beg + k]];
+    for (uint32_t k = lane; k < d; k += 64) {
+        const uint32_t c = (uint32_t)rank[col[beg + k]];
+        keys[o + k] = sym ? ((uint64_t)c << cbits) | s : ((uint64_t)s << cbits) | c;
+    }
 }
 
 // part descriptors and their sort keys
@@ -374,8 +378,9 @@ void bg_free_blocked(bitgnn_blocked *b)
     free(b);
 }
 
-// Builds adj->blk from the CSR arrays of `adj` (already on the device).
-int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
+// Builds adj->blk from the CSR arrays of `adj` (already on the device); `sym`: the adjacency is
+// known to be symmetric.
+int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
 {
     const uint32_t n = (uint32_t)adj->n, nnz = (uint32_t)adj->nnz;
     const int cbn = ctx->cb_nodes, part_len = ctx->part_len;
@@ -388,18 +393,18 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
 
     DevBuf rank, deg_sorted, nparts, keys_a, keys_b, hist, scan_ws, multi;
     const uint32_t sort_n = nnz > n ? nnz : n;
-    const uint32_t sort_tiles = (sort_n + kSortTile - 1) / kSortTile;
+    // room for sorts of up to sort_max keys (sort_n in whole small tiles)
+    const uint32_t sort_max = (sort_n + kSortTileSmall - 1) / kSortTileSmall * kSortTileSmall;
+    const size_t hist_words = sort_hist_words(sort_max);
     BG_HIP(ctx, rank.alloc((size_t)n * 4));
     BG_HIP(ctx, deg_sorted.alloc(((size_t)n + 1) * 4));
     BG_HIP(ctx, nparts.alloc(((size_t)n + 1) * 4));
     BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8));
     BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8));
-    BG_HIP(ctx, hist.alloc((size_t)256 * sort_tiles * 4));
+    BG_HIP(ctx, hist.alloc(hist_words * 4));
     // one workspace for the scans of the sort histograms, of the n + 1 row counters and of
     // the slice counters (S + 1 <= sort_n / 32 + 2); the tile scan gets its own below
-    const uint64_t scan_max = (uint64_t)256 * sort_tiles > (uint64_t)n + 1
-                                  ? (uint64_t)256 * sort_tiles
-                                  : (uint64_t)n + 1;
+    const uint64_t scan_max = hist_words > (uint64_t)n + 1 ? hist_words : (uint64_t)n + 1;
     BG_HIP(ctx, scan_ws.alloc(scan_ws_words(scan_max) * 4));
 
     BG_HIP(ctx, multi.alloc(4));
@@ -413,11 +418,11 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     const uint32_t *rp2 = deg_sorted.as<uint32_t>();
     uint32_t *vptr = nparts.as<uint32_t>();
     blocked_keys_kernel<<<blocks_for(n, 4), 256, 0, s>>>(adj->rowptr, adj->col, adj->order,
-                                                        rank.as<int32_t>(), rp2, n, cbits,
+                                                        rank.as<int32_t>(), rp2, n, cbits, sym,
                                                         keys_a.as<uint64_t>());
     BG_LAUNCH_CHECK(ctx, "blocked_keys");
-    uint64_t *skeys = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nnz, 2 * cbits,
-                                 hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
+    uint64_t *skeys = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nnz,
+                                 sym ? cbits : 0, 2 * cbits, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     BG_LAUNCH_CHECK(ctx, "blocked radix_sort");
     uint32_t V = 0, n_multi = 0;
     BG_HIP(ctx, hipMemcpyAsync(&V, vptr + n, 4, hipMemcpyDeviceToHost, s));
@@ -439,10 +444,19 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     BG_LAUNCH_CHECK(ctx, "vrow");
     // V <= nnz + n, so the histogram buffers sized for sort_n suffice when V <= sort_n;
     // V can exceed sort_n only if n > nnz, i.e. never on the graphs that get here
-    if ((V + kSortTile - 1) / kSortTile > sort_tiles)
+    if (V > sort_max)
         return BITGNN_OK;
-    uint64_t *svkeys = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), V, 64,
+    // The parts are written in the order of their ids (bits 0-29) and a block number has as
+    // many bits as ncb - 1: two sorts skip the bits that are in order or zero (three passes
+    // instead of eight for 23 blocks).
+    int bb = 0;
+    while (((ncb - 1) >> bb) > 0)
+        ++bb;
+    uint64_t *svkeys = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), V, 30, 40 + bb,
                                   hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
+    svkeys = radix_sort(svkeys, svkeys == vk_a.as<uint64_t>() ? vk_b.as<uint64_t>()
+                                                              : vk_a.as<uint64_t>(),
+                        V, 52, 52 + bb, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
 
     // work items of 16 slices, or of 8 or 4 on graphs with too few slices to give every
     // compute unit an item of 16 (measured on the 131 K-node R-MAT graph: 126 us per
@@ -512,7 +526,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
                                                    sl_tile_base.as<uint32_t>(),
                                                    tile_group.as<uint32_t>(), S, W, spw, cbn,
                                                    vk_a.as<uint64_t>());
-    uint64_t *wsorted = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), W, 64,
+    uint64_t *wsorted = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), W, 32, 64,
                                    hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     wg_item_kernel<<<blocks_for(W, 256), 256, 0, s>>>(wsorted, W, wg_cb.as<uint32_t>(),
                                                      wg_item.as<uint2>());
