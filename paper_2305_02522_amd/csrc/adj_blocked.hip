@@ -192,6 +192,24 @@ struct cls16 {
     }
 };
 
+// column slots of the sorted entries
+__global__ void column_kernel(const uint64_t *__restrict__ skeys, uint32_t nnz, int cbits,
+                              uint32_t *__restrict__ cols)
+{
+    const uint32_t u = blockIdx.x * blockDim.x + threadIdx.x;
+    if (u < nnz)
+        cols[u] = (uint32_t)skeys[u] & ((1u << cbits) - 1);
+}
+
+// Entries 4q .. 4q + 7; chunks behind the last (qmax) repeat it.
+__device__ __forceinline__ void load_columns(const uint4 *__restrict__ cols, uint32_t q,
+                                             uint32_t qmax, uint32_t (&w)[8])
+{
+    const uint4 a = cols[min(q, qmax)], b = cols[min(q + 1, qmax)];
+    w[0] = a.x, w[1] = a.y, w[2] = a.z, w[3] = a.w;
+    w[4] = b.x, w[5] = b.y, w[6] = b.z, w[7] = b.w;
+}
+
 // per (slice, block) tile: steps = longest lane; FILL = false counts groups,
 // FILL = true writes the lane-interleaved ids.
 //
@@ -201,17 +219,21 @@ struct cls16 {
 // a row of class (L + k) mod 16: an id goes to the first free step of its class, ids whose
 // class has no step left take any free step, and padding steps address the all-zero row
 // of the wanted class (rows cbn .. cbn + 15 of the staged block are zero).
+//
+// Bound by the walks along each lane's entries: 64 lanes read 64 places, so every load is 64
+// requests and a memory latency.  They take eight 32-bit columns a step, two 16-byte loads,
+// instead of one 64-bit key.
 template <bool FILL>
 __global__ __launch_bounds__(64) void tile_kernel(
     const uint64_t *__restrict__ svkeys, uint32_t V, const uint32_t *__restrict__ v_beg,
-    const uint32_t *__restrict__ v_end, const uint64_t *__restrict__ skeys, int cbits, int cbn,
+    const uint32_t *__restrict__ v_end, const uint4 *__restrict__ cols, uint32_t nnz, int cbn,
     const uint32_t *__restrict__ sl_cb, const uint32_t *__restrict__ sl_tile_base,
     uint32_t *__restrict__ tile_group, uint16_t *__restrict__ idx16)
 {
     const uint32_t slice = blockIdx.x;
     const uint32_t lane = threadIdx.x;
     const uint32_t pos = slice * 64 + lane;
-    const uint64_t mask = (1ull << cbits) - 1;
+    const uint32_t qmax = (nnz - 1) >> 2;
     uint32_t ptr = 0, e = 0;
     if (pos < V) {
         const uint32_t v = (uint32_t)svkeys[pos] & kVidMask;
@@ -220,53 +242,97 @@ __global__ __launch_bounds__(64) void tile_kernel(
     }
     const uint32_t lo = sl_cb[slice] & 0xFFFFu, hi = sl_cb[slice] >> 16;
     const uint32_t t0 = sl_tile_base[slice];
+    // the eight entries from 4 wq on, 0 in front of the part and the largest value behind it, so
+    // that the number of them below a limit says where the part's entries below it end
+    const uint32_t beg = ptr;
+    uint32_t wq = beg >> 2;
+    uint32_t win[8];
+    auto load_window = [&]() {
+        load_columns(cols, wq, qmax, win);
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) {
+            const uint32_t at = wq * 4 + i;
+            win[i] = at >= e ? 0xFFFFFFFFu : (at < beg ? 0u : win[i]);
+        }
+    };
+    load_window();
     for (uint32_t cb = lo; cb <= hi; ++cb) {
-        const uint64_t lim = (uint64_t)(cb + 1) * (uint32_t)cbn;
-        const uint64_t cb0 = (uint64_t)cb * (uint32_t)cbn;
+        const uint32_t cb0 = cb * (uint32_t)cbn; // at most N + cbn < 2^32
+        const uint32_t lim = cb0 + (uint32_t)cbn;
         const uint32_t first = ptr;
-        while (ptr < e && (skeys[ptr] & mask) < lim)
-            ++ptr;
+        for (;;) {
+            uint32_t below = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i)
+                below += win[i] < lim;
+            ptr = max(ptr, min(wq * 4 + below, e));
+            if (below < 8 || ptr >= e)
+                break;
+            wq += 2;
+            load_window();
+        }
         const uint32_t cnt = ptr - first;
         if (!FILL) {
             const uint32_t m = wave_max_u32(cnt);
             if (lane == 0)
                 tile_group[t0 + cb - lo] = (m + kGroupSteps - 1) / kGroupSteps;
         } else {
+            static_assert(kGroupSteps == 8, "a lane's ids of a group are one 16-byte store");
             const uint32_t g0 = tile_group[t0 + cb - lo];
-            const uint32_t steps = (tile_group[t0 + cb - lo + 1] - g0) * kGroupSteps;
+            const uint32_t groups = tile_group[t0 + cb - lo + 1] - g0;
+            const uint32_t steps = groups * kGroupSteps;
             auto slot = [&](uint32_t k) -> uint16_t & {
                 return idx16[((uint64_t)(g0 + k / kGroupSteps) * 64 + lane) * kGroupSteps +
                              (k % kGroupSteps)];
             };
+            auto each_id = [&](auto &&visit) {
+                for (uint32_t q = first >> 2; q * 4 < ptr; q += 2) {
+                    uint32_t w[8];
+                    load_columns(cols, q, qmax, w);
+#pragma unroll
+                    for (uint32_t i = 0; i < 8; ++i)
+                        if (q * 4 + i >= first && q * 4 + i < ptr)
+                            visit(w[i] - cb0);
+                }
+            };
             // steps of class c' = (id - lane) mod 16 are c', c' + 16, ...: how many ids of
             // every class find one
             cls16 used, run;
-            for (uint32_t j = 0; j < cnt; ++j) {
-                const uint32_t id = (uint32_t)((skeys[first + j] & mask) - cb0);
-                const uint32_t c = (id - lane) & 15u;
-                const uint32_t cap = c < steps ? (steps - c + 15u) >> 4 : 0u;
-                const uint32_t u = used.get(c);
-                if (u < cap)
-                    used.set(c, u + 1);
-            }
-            for (uint32_t k = 0; k < steps; ++k)
-                slot(k) = (uint16_t)((uint32_t)cbn + ((lane + k) & 15u));
-            uint32_t kfree = 0;
-            for (uint32_t j = 0; j < cnt; ++j) {
-                const uint32_t id = (uint32_t)((skeys[first + j] & mask) - cb0);
-                const uint32_t c = (id - lane) & 15u;
-                const uint32_t m = run.get(c);
-                uint32_t k;
-                if (m < used.get(c)) {
-                    run.set(c, m + 1);
-                    k = c + 16u * m;
-                } else { // no step of its class left: the next step no class claims
-                    while ((kfree >> 4) < used.get(kfree & 15u))
-                        ++kfree;
-                    k = kfree++;
+            if (cnt)
+                each_id([&](uint32_t id) {
+                    const uint32_t c = (id - lane) & 15u;
+                    const uint32_t cap = c < steps ? (steps - c + 15u) >> 4 : 0u;
+                    const uint32_t u = used.get(c);
+                    if (u < cap)
+                        used.set(c, u + 1);
+                });
+            for (uint32_t g = 0; g < groups; ++g) {
+                uint32_t p[4];
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) {
+                    const uint32_t k = g * kGroupSteps + 2 * i;
+                    p[i] = ((uint32_t)cbn + ((lane + k) & 15u)) |
+                           (((uint32_t)cbn + ((lane + k + 1) & 15u)) << 16);
                 }
-                slot(k) = (uint16_t)id;
+                // memcpy: the ids stored over it below are of another type
+                __builtin_memcpy(__builtin_assume_aligned(&slot(g * kGroupSteps), 16), p, 16);
             }
+            uint32_t kfree = 0;
+            if (cnt)
+                each_id([&](uint32_t id) {
+                    const uint32_t c = (id - lane) & 15u;
+                    const uint32_t m = run.get(c);
+                    uint32_t k;
+                    if (m < used.get(c)) {
+                        run.set(c, m + 1);
+                        k = c + 16u * m;
+                    } else { // no step of its class left: the next step no class claims
+                        while ((kfree >> 4) < used.get(kfree & 15u))
+                            ++kfree;
+                        k = kfree++;
+                    }
+                    slot(k) = (uint16_t)id;
+                });
         }
     }
 }
@@ -399,8 +465,8 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_HIP(ctx, rank.alloc((size_t)n * 4));
     BG_HIP(ctx, deg_sorted.alloc(((size_t)n + 1) * 4));
     BG_HIP(ctx, nparts.alloc(((size_t)n + 1) * 4));
-    BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8));
-    BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8));
+    BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8 + 16));
+    BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8 + 16));
     BG_HIP(ctx, hist.alloc(hist_words * 4));
     // one workspace for the scans of the sort histograms, of the n + 1 row counters and of
     // the slice counters (S + 1 <= sort_n / 32 + 2); the tile scan gets its own below
@@ -423,6 +489,10 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_LAUNCH_CHECK(ctx, "blocked_keys");
     uint64_t *skeys = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nnz,
                                  sym ? cbits : 0, 2 * cbits, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
+    // the columns alone, in whole 16-byte chunks, into the buffer that the sort has left
+    uint32_t *cols = skeys == keys_a.as<uint64_t>() ? keys_b.as<uint32_t>()
+                                                    : keys_a.as<uint32_t>();
+    column_kernel<<<blocks_for(nnz, 256), 256, 0, s>>>(skeys, nnz, cbits, cols);
     BG_LAUNCH_CHECK(ctx, "blocked radix_sort");
     uint32_t V = 0, n_multi = 0;
     BG_HIP(ctx, hipMemcpyAsync(&V, vptr + n, 4, hipMemcpyDeviceToHost, s));
@@ -483,7 +553,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_HIP(ctx, tile_group.alloc(((size_t)T + 1) * 4));
     BG_HIP(ctx, hipMemsetAsync(tile_group.as<uint32_t>() + T, 0, 4, s));
     tile_kernel<false><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(),
-                                        skeys, cbits, cbn, sl_cb.as<uint32_t>(),
+                                        (const uint4 *)cols, nnz, cbn, sl_cb.as<uint32_t>(),
                                         sl_tile_base.as<uint32_t>(), tile_group.as<uint32_t>(),
                                         nullptr);
     BG_LAUNCH_CHECK(ctx, "tile count");
@@ -508,8 +578,8 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_HIP(ctx, idx16.alloc(((size_t)G + 1) * kGroupIds * 2));
     tail_group_kernel<<<blocks_for((int64_t)kGroupIds, 256), 256, 0, s>>>(idx16.as<uint16_t>(), G,
                                                                          cbn);
-    tile_kernel<true><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(), skeys,
-                                       cbits, cbn, sl_cb.as<uint32_t>(),
+    tile_kernel<true><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(),
+                                       (const uint4 *)cols, nnz, cbn, sl_cb.as<uint32_t>(),
                                        sl_tile_base.as<uint32_t>(), tile_group.as<uint32_t>(),
                                        idx16.as<uint16_t>());
     BG_LAUNCH_CHECK(ctx, "tile fill");

@@ -74,9 +74,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(const uint32_
     const uint32_t base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
     uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n)
-            s += in[base + k];
+    for (int k = 0; k < kScanItems; ++k) {
+        const uint32_t v = in[min(base + k, n - 1)];
+        s += base + k < n ? v : 0;
+    }
     uint32_t total;
     (void)block_exclusive_scan(s, &total);
     if (threadIdx.x == 0)
@@ -92,8 +93,11 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(uint32_t *__re
     uint32_t v[kScanItems];
     uint32_t s = 0;
 #pragma unroll
+    for (int k = 0; k < kScanItems; ++k)
+        v[k] = data[min(base + k, n - 1)]; // unconditional: eight loads in flight
+#pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (base + k < n) ? data[base + k] : 0;
+        v[k] = (base + k < n) ? v[k] : 0;
         s += v[k];
     }
     uint32_t total;
@@ -121,8 +125,11 @@ __global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(uint32_t 
         uint32_t v[kScanItems];
         uint32_t s = 0;
 #pragma unroll
+        for (int k = 0; k < kScanItems; ++k)
+            v[k] = data[min(base + k, n - 1)]; // unconditional: eight loads in flight
+#pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
-            v[k] = (base + k < n) ? data[base + k] : 0;
+            v[k] = (base + k < n) ? v[k] : 0;
             s += v[k];
         }
         uint32_t total;
