@@ -190,6 +190,13 @@ struct cls16 {
         else
             lo = (lo & m) | b;
     }
+    // bit 7 of every byte of the half whose counter is <= v (counters and v are at most 64: a
+    // part has at most 1,023 ids)
+    __device__ __forceinline__ uint64_t at_most(int half, uint32_t v) const
+    {
+        constexpr uint64_t ones = 0x0101010101010101ull, top = ones << 7;
+        return ~(((half ? hi : lo) | top) - (v + 1) * ones) & top;
+    }
 };
 
 // column slots of the sorted entries
@@ -222,7 +229,7 @@ __device__ __forceinline__ void load_columns(const uint4 *__restrict__ cols, uin
 //
 // Bound by the walks along each lane's entries: 64 lanes read 64 places, so every load is 64
 // requests and a memory latency.  They take eight 32-bit columns a step, two 16-byte loads,
-// instead of one 64-bit key.
+// instead of one 64-bit key (110.6 M entries: 1,532 -> 244 us counting, 5,658 -> 2,229 us filling).
 template <bool FILL>
 __global__ __launch_bounds__(64) void tile_kernel(
     const uint64_t *__restrict__ svkeys, uint32_t V, const uint32_t *__restrict__ v_beg,
@@ -317,7 +324,12 @@ __global__ __launch_bounds__(64) void tile_kernel(
                 // memcpy: the ids stored over it below are of another type
                 __builtin_memcpy(__builtin_assume_aligned(&slot(g * kGroupSteps), 16), p, 16);
             }
-            uint32_t kfree = 0;
+            // Steps that no class claims, ascending, a row of 16 at a time: bit 7 of byte c is set
+            // while step 16 row + c is free.  Lanes run out of their classes' steps at different
+            // ids, so looking at the claimed steps one by one cost the wavefront the sum over
+            // its lanes (10,007 nodes: 344 us, now 129).
+            uint32_t row = 0;
+            uint64_t free_lo = used.at_most(0, 0), free_hi = used.at_most(1, 0);
             if (cnt)
                 each_id([&](uint32_t id) {
                     const uint32_t c = (id - lane) & 15u;
@@ -327,9 +339,19 @@ __global__ __launch_bounds__(64) void tile_kernel(
                         run.set(c, m + 1);
                         k = c + 16u * m;
                     } else { // no step of its class left: the next step no class claims
-                        while ((kfree >> 4) < used.get(kfree & 15u))
-                            ++kfree;
-                        k = kfree++;
+                        while ((free_lo | free_hi) == 0) {
+                            ++row;
+                            free_lo = used.at_most(0, row);
+                            free_hi = used.at_most(1, row);
+                        }
+                        k = 16u * row;
+                        if (free_lo) {
+                            k += (uint32_t)__builtin_ctzll(free_lo) >> 3;
+                            free_lo &= free_lo - 1;
+                        } else {
+                            k += 8u + ((uint32_t)__builtin_ctzll(free_hi) >> 3);
+                            free_hi &= free_hi - 1;
+                        }
                     }
                     slot(k) = (uint16_t)id;
                 });

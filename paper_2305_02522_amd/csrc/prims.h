@@ -116,29 +116,45 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(uint32_t *__re
 constexpr int kScanSmallThreads = 1024;
 constexpr uint32_t kScanSmallMax = 32768; // four turns
 
+// One CU reads and writes it all: 16-byte accesses, or issuing them is what takes the time
+// (13,000 words: 13 us with 4-byte ones, 4 us so).
 __global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(uint32_t *__restrict__ data,
                                                                        uint32_t n)
 {
     uint32_t before = 0;
     for (uint32_t b = 0; b < n; b += kScanSmallThreads * kScanItems) {
         const uint32_t base = b + threadIdx.x * kScanItems;
+        const bool whole = base + kScanItems <= n;
         uint32_t v[kScanItems];
+        if (whole) {
+            const uint4 p = *(const uint4 *)(data + base), q = *(const uint4 *)(data + base + 4);
+            v[0] = p.x, v[1] = p.y, v[2] = p.z, v[3] = p.w;
+            v[4] = q.x, v[5] = q.y, v[6] = q.z, v[7] = q.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < kScanItems; ++k)
+                v[k] = base + k < n ? data[base + k] : 0;
+        }
         uint32_t s = 0;
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k)
-            v[k] = data[min(base + k, n - 1)]; // unconditional: eight loads in flight
-#pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            v[k] = (base + k < n) ? v[k] : 0;
             s += v[k];
-        }
         uint32_t total;
         uint32_t run = block_exclusive_scan<kScanSmallThreads>(s, &total) + before;
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
-            if (base + k < n)
-                data[base + k] = run;
-            run += v[k];
+            const uint32_t x = v[k];
+            v[k] = run;
+            run += x;
+        }
+        if (whole) {
+            *(uint4 *)(data + base) = make_uint4(v[0], v[1], v[2], v[3]);
+            *(uint4 *)(data + base + 4) = make_uint4(v[4], v[5], v[6], v[7]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kScanItems; ++k)
+                if (base + k < n)
+                    data[base + k] = v[k];
         }
         before += total;
     }
@@ -162,7 +178,7 @@ static void scan_inplace(uint32_t *data, uint32_t n, uint32_t *ws, hipStream_t s
         scan_apply_kernel<<<1, kScanThreads, 0, s>>>(data, n, nullptr);
         return;
     }
-    if (n <= kScanSmallMax) {
+    if (n <= kScanSmallMax && bg_aligned(data, 16)) {
         scan_small_kernel<<<1, kScanSmallThreads, 0, s>>>(data, n);
         return;
     }
@@ -177,6 +193,8 @@ static void scan_inplace(uint32_t *data, uint32_t n, uint32_t *ws, hipStream_t s
 // eight wavefronts first puts its tile in digit order in LDS, then writes runs of ~32 keys
 // (256 bytes) per digit.  Writing each key straight to its place from one wavefront's tile of
 // 2,048 keys, the form before this one, left runs of 64 bytes spread over 32 instructions.
+// 115 M keys, one pass: 246 us for the histogram and 478 us for the scatter, 3.8 TB/s both; the
+// build they are most of went from 37.5 to 21.5 ms with them (and with fewer passes).
 // Sorts of fewer than kSortSmall keys take tiles of 2,048 keys: with 8,192 there are too few
 // workgroups for 256 CUs.
 constexpr int kSortThreads = 512;
