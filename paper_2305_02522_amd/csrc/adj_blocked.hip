@@ -77,13 +77,11 @@ __global__ void slot_kernel(const int32_t *__restrict__ order, const int32_t *__
         atomicAdd(n_multi, 1u);
 }
 
-// keys (row slot << cbits | column slot), one wavefront per row.  A symmetric adjacency gives
-// the same set with the two exchanged, and then the keys are written in column order: only
-// the row bits are left to sort (18 of 36 bits on 232,965 nodes: three passes, not five).
+// keys (row slot << cbits | column slot), one wavefront per row
 __global__ __launch_bounds__(256) void blocked_keys_kernel(
     const uint32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ order, const int32_t *__restrict__ rank,
-    const uint32_t *__restrict__ rp2, uint32_t n, int cbits, bool sym, uint64_t *__restrict__ keys)
+    const uint32_t *__restrict__ rp2, uint32_t n, int cbits, uint64_t *__restrict__ keys)
 {
     const uint32_t s = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -91,10 +89,8 @@ __global__ __launch_bounds__(256) void blocked_keys_kernel(
         return;
     const int32_t i = order[s];
     const uint32_t beg = rowptr[i], d = rowptr[i + 1] - beg, o = rp2[s];
-    for (uint32_t k = lane; k < d; k += 64) {
-        const uint32_t c = (uint32_t)rank[col[beg + k]];
-        keys[o + k] = sym ? ((uint64_t)c << cbits) | s : ((uint64_t)s << cbits) | c;
-    }
+    for (uint32_t k = lane; k < d; k += 64)
+        keys[o + k] = ((uint64_t)s << cbits) | (uint32_t)rank[col[beg + k]];
 }
 
 // part descriptors and their sort keys
@@ -190,32 +186,7 @@ struct cls16 {
         else
             lo = (lo & m) | b;
     }
-    // bit 7 of every byte of the half whose counter is <= v (counters and v are at most 64: a
-    // part has at most 1,023 ids)
-    __device__ __forceinline__ uint64_t at_most(int half, uint32_t v) const
-    {
-        constexpr uint64_t ones = 0x0101010101010101ull, top = ones << 7;
-        return ~(((half ? hi : lo) | top) - (v + 1) * ones) & top;
-    }
 };
-
-// column slots of the sorted entries
-__global__ void column_kernel(const uint64_t *__restrict__ skeys, uint32_t nnz, int cbits,
-                              uint32_t *__restrict__ cols)
-{
-    const uint32_t u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < nnz)
-        cols[u] = (uint32_t)skeys[u] & ((1u << cbits) - 1);
-}
-
-// Entries 4q .. 4q + 7; chunks behind the last (qmax) repeat it.
-__device__ __forceinline__ void load_columns(const uint4 *__restrict__ cols, uint32_t q,
-                                             uint32_t qmax, uint32_t (&w)[8])
-{
-    const uint4 a = cols[min(q, qmax)], b = cols[min(q + 1, qmax)];
-    w[0] = a.x, w[1] = a.y, w[2] = a.z, w[3] = a.w;
-    w[4] = b.x, w[5] = b.y, w[6] = b.z, w[7] = b.w;
-}
 
 // per (slice, block) tile: steps = longest lane; FILL = false counts groups,
 // FILL = true writes the lane-interleaved ids.
@@ -226,21 +197,17 @@ __device__ __forceinline__ void load_columns(const uint4 *__restrict__ cols, uin
 // a row of class (L + k) mod 16: an id goes to the first free step of its class, ids whose
 // class has no step left take any free step, and padding steps address the all-zero row
 // of the wanted class (rows cbn .. cbn + 15 of the staged block are zero).
-//
-// Bound by the walks along each lane's entries: 64 lanes read 64 places, so every load is 64
-// requests and a memory latency.  They take eight 32-bit columns a step, two 16-byte loads,
-// instead of one 64-bit key (110.6 M entries: 1,532 -> 244 us counting, 5,658 -> 2,229 us filling).
 template <bool FILL>
 __global__ __launch_bounds__(64) void tile_kernel(
     const uint64_t *__restrict__ svkeys, uint32_t V, const uint32_t *__restrict__ v_beg,
-    const uint32_t *__restrict__ v_end, const uint4 *__restrict__ cols, uint32_t nnz, int cbn,
+    const uint32_t *__restrict__ v_end, const uint64_t *__restrict__ skeys, int cbits, int cbn,
     const uint32_t *__restrict__ sl_cb, const uint32_t *__restrict__ sl_tile_base,
     uint32_t *__restrict__ tile_group, uint16_t *__restrict__ idx16)
 {
     const uint32_t slice = blockIdx.x;
     const uint32_t lane = threadIdx.x;
     const uint32_t pos = slice * 64 + lane;
-    const uint32_t qmax = (nnz - 1) >> 2;
+    const uint64_t mask = (1ull << cbits) - 1;
     uint32_t ptr = 0, e = 0;
     if (pos < V) {
         const uint32_t v = (uint32_t)svkeys[pos] & kVidMask;
@@ -249,112 +216,53 @@ __global__ __launch_bounds__(64) void tile_kernel(
     }
     const uint32_t lo = sl_cb[slice] & 0xFFFFu, hi = sl_cb[slice] >> 16;
     const uint32_t t0 = sl_tile_base[slice];
-    // the eight entries from 4 wq on, 0 in front of the part and the largest value behind it, so
-    // that the number of them below a limit says where the part's entries below it end
-    const uint32_t beg = ptr;
-    uint32_t wq = beg >> 2;
-    uint32_t win[8];
-    auto load_window = [&]() {
-        load_columns(cols, wq, qmax, win);
-#pragma unroll
-        for (uint32_t i = 0; i < 8; ++i) {
-            const uint32_t at = wq * 4 + i;
-            win[i] = at >= e ? 0xFFFFFFFFu : (at < beg ? 0u : win[i]);
-        }
-    };
-    load_window();
     for (uint32_t cb = lo; cb <= hi; ++cb) {
-        const uint32_t cb0 = cb * (uint32_t)cbn; // at most N + cbn < 2^32
-        const uint32_t lim = cb0 + (uint32_t)cbn;
+        const uint64_t lim = (uint64_t)(cb + 1) * (uint32_t)cbn;
+        const uint64_t cb0 = (uint64_t)cb * (uint32_t)cbn;
         const uint32_t first = ptr;
-        for (;;) {
-            uint32_t below = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < 8; ++i)
-                below += win[i] < lim;
-            ptr = max(ptr, min(wq * 4 + below, e));
-            if (below < 8 || ptr >= e)
-                break;
-            wq += 2;
-            load_window();
-        }
+        while (ptr < e && (skeys[ptr] & mask) < lim)
+            ++ptr;
         const uint32_t cnt = ptr - first;
         if (!FILL) {
             const uint32_t m = wave_max_u32(cnt);
             if (lane == 0)
                 tile_group[t0 + cb - lo] = (m + kGroupSteps - 1) / kGroupSteps;
         } else {
-            static_assert(kGroupSteps == 8, "a lane's ids of a group are one 16-byte store");
             const uint32_t g0 = tile_group[t0 + cb - lo];
-            const uint32_t groups = tile_group[t0 + cb - lo + 1] - g0;
-            const uint32_t steps = groups * kGroupSteps;
+            const uint32_t steps = (tile_group[t0 + cb - lo + 1] - g0) * kGroupSteps;
             auto slot = [&](uint32_t k) -> uint16_t & {
                 return idx16[((uint64_t)(g0 + k / kGroupSteps) * 64 + lane) * kGroupSteps +
                              (k % kGroupSteps)];
             };
-            auto each_id = [&](auto &&visit) {
-                for (uint32_t q = first >> 2; q * 4 < ptr; q += 2) {
-                    uint32_t w[8];
-                    load_columns(cols, q, qmax, w);
-#pragma unroll
-                    for (uint32_t i = 0; i < 8; ++i)
-                        if (q * 4 + i >= first && q * 4 + i < ptr)
-                            visit(w[i] - cb0);
-                }
-            };
             // steps of class c' = (id - lane) mod 16 are c', c' + 16, ...: how many ids of
             // every class find one
             cls16 used, run;
-            if (cnt)
-                each_id([&](uint32_t id) {
-                    const uint32_t c = (id - lane) & 15u;
-                    const uint32_t cap = c < steps ? (steps - c + 15u) >> 4 : 0u;
-                    const uint32_t u = used.get(c);
-                    if (u < cap)
-                        used.set(c, u + 1);
-                });
-            for (uint32_t g = 0; g < groups; ++g) {
-                uint32_t p[4];
-#pragma unroll
-                for (uint32_t i = 0; i < 4; ++i) {
-                    const uint32_t k = g * kGroupSteps + 2 * i;
-                    p[i] = ((uint32_t)cbn + ((lane + k) & 15u)) |
-                           (((uint32_t)cbn + ((lane + k + 1) & 15u)) << 16);
-                }
-                // memcpy: the ids stored over it below are of another type
-                __builtin_memcpy(__builtin_assume_aligned(&slot(g * kGroupSteps), 16), p, 16);
+            for (uint32_t j = 0; j < cnt; ++j) {
+                const uint32_t id = (uint32_t)((skeys[first + j] & mask) - cb0);
+                const uint32_t c = (id - lane) & 15u;
+                const uint32_t cap = c < steps ? (steps - c + 15u) >> 4 : 0u;
+                const uint32_t u = used.get(c);
+                if (u < cap)
+                    used.set(c, u + 1);
             }
-            // Steps that no class claims, ascending, a row of 16 at a time: bit 7 of byte c is set
-            // while step 16 row + c is free.  Lanes run out of their classes' steps at different
-            // ids, so looking at the claimed steps one by one cost the wavefront the sum over
-            // its lanes (10,007 nodes: 344 us, now 129).
-            uint32_t row = 0;
-            uint64_t free_lo = used.at_most(0, 0), free_hi = used.at_most(1, 0);
-            if (cnt)
-                each_id([&](uint32_t id) {
-                    const uint32_t c = (id - lane) & 15u;
-                    const uint32_t m = run.get(c);
-                    uint32_t k;
-                    if (m < used.get(c)) {
-                        run.set(c, m + 1);
-                        k = c + 16u * m;
-                    } else { // no step of its class left: the next step no class claims
-                        while ((free_lo | free_hi) == 0) {
-                            ++row;
-                            free_lo = used.at_most(0, row);
-                            free_hi = used.at_most(1, row);
-                        }
-                        k = 16u * row;
-                        if (free_lo) {
-                            k += (uint32_t)__builtin_ctzll(free_lo) >> 3;
-                            free_lo &= free_lo - 1;
-                        } else {
-                            k += 8u + ((uint32_t)__builtin_ctzll(free_hi) >> 3);
-                            free_hi &= free_hi - 1;
-                        }
-                    }
-                    slot(k) = (uint16_t)id;
-                });
+            for (uint32_t k = 0; k < steps; ++k)
+                slot(k) = (uint16_t)((uint32_t)cbn + ((lane + k) & 15u));
+            uint32_t kfree = 0;
+            for (uint32_t j = 0; j < cnt; ++j) {
+                const uint32_t id = (uint32_t)((skeys[first + j] & mask) - cb0);
+                const uint32_t c = (id - lane) & 15u;
+                const uint32_t m = run.get(c);
+                uint32_t k;
+                if (m < used.get(c)) {
+                    run.set(c, m + 1);
+                    k = c + 16u * m;
+                } else { // no step of its class left: the next step no class claims
+                    while ((kfree >> 4) < used.get(kfree & 15u))
+                        ++kfree;
+                    k = kfree++;
+                }
+                slot(k) = (uint16_t)id;
+            }
         }
     }
 }
@@ -466,9 +374,8 @@ void bg_free_blocked(bitgnn_blocked *b)
     free(b);
 }
 
-// Builds adj->blk from the CSR arrays of `adj` (already on the device); `sym`: the adjacency is
-// known to be symmetric.
-int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
+// Builds adj->blk from the CSR arrays of `adj` (already on the device).
+int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
 {
     const uint32_t n = (uint32_t)adj->n, nnz = (uint32_t)adj->nnz;
     const int cbn = ctx->cb_nodes, part_len = ctx->part_len;
@@ -481,18 +388,18 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
 
     DevBuf rank, deg_sorted, nparts, keys_a, keys_b, hist, scan_ws, multi;
     const uint32_t sort_n = nnz > n ? nnz : n;
-    // room for sorts of up to sort_max keys (sort_n in whole small tiles)
-    const uint32_t sort_max = (sort_n + kSortTileSmall - 1) / kSortTileSmall * kSortTileSmall;
-    const size_t hist_words = sort_hist_words(sort_max);
+    const uint32_t sort_tiles = (sort_n + kSortTile - 1) / kSortTile;
     BG_HIP(ctx, rank.alloc((size_t)n * 4));
     BG_HIP(ctx, deg_sorted.alloc(((size_t)n + 1) * 4));
     BG_HIP(ctx, nparts.alloc(((size_t)n + 1) * 4));
-    BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8 + 16));
-    BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8 + 16));
-    BG_HIP(ctx, hist.alloc(hist_words * 4));
+    BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8));
+    BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8));
+    BG_HIP(ctx, hist.alloc((size_t)256 * sort_tiles * 4));
     // one workspace for the scans of the sort histograms, of the n + 1 row counters and of
     // the slice counters (S + 1 <= sort_n / 32 + 2); the tile scan gets its own below
-    const uint64_t scan_max = hist_words > (uint64_t)n + 1 ? hist_words : (uint64_t)n + 1;
+    const uint64_t scan_max = (uint64_t)256 * sort_tiles > (uint64_t)n + 1
+                                  ? (uint64_t)256 * sort_tiles
+                                  : (uint64_t)n + 1;
     BG_HIP(ctx, scan_ws.alloc(scan_ws_words(scan_max) * 4));
 
     BG_HIP(ctx, multi.alloc(4));
@@ -506,15 +413,11 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     const uint32_t *rp2 = deg_sorted.as<uint32_t>();
     uint32_t *vptr = nparts.as<uint32_t>();
     blocked_keys_kernel<<<blocks_for(n, 4), 256, 0, s>>>(adj->rowptr, adj->col, adj->order,
-                                                        rank.as<int32_t>(), rp2, n, cbits, sym,
+                                                        rank.as<int32_t>(), rp2, n, cbits,
                                                         keys_a.as<uint64_t>());
     BG_LAUNCH_CHECK(ctx, "blocked_keys");
-    uint64_t *skeys = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nnz,
-                                 sym ? cbits : 0, 2 * cbits, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
-    // the columns alone, in whole 16-byte chunks, into the buffer that the sort has left
-    uint32_t *cols = skeys == keys_a.as<uint64_t>() ? keys_b.as<uint32_t>()
-                                                    : keys_a.as<uint32_t>();
-    column_kernel<<<blocks_for(nnz, 256), 256, 0, s>>>(skeys, nnz, cbits, cols);
+    uint64_t *skeys = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nnz, 2 * cbits,
+                                 hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     BG_LAUNCH_CHECK(ctx, "blocked radix_sort");
     uint32_t V = 0, n_multi = 0;
     BG_HIP(ctx, hipMemcpyAsync(&V, vptr + n, 4, hipMemcpyDeviceToHost, s));
@@ -536,19 +439,10 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_LAUNCH_CHECK(ctx, "vrow");
     // V <= nnz + n, so the histogram buffers sized for sort_n suffice when V <= sort_n;
     // V can exceed sort_n only if n > nnz, i.e. never on the graphs that get here
-    if (V > sort_max)
+    if ((V + kSortTile - 1) / kSortTile > sort_tiles)
         return BITGNN_OK;
-    // The parts are written in the order of their ids (bits 0-29) and a block number has as
-    // many bits as ncb - 1: two sorts skip the bits that are in order or zero (three passes
-    // instead of eight for 23 blocks).
-    int bb = 0;
-    while (((ncb - 1) >> bb) > 0)
-        ++bb;
-    uint64_t *svkeys = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), V, 30, 40 + bb,
+    uint64_t *svkeys = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), V, 64,
                                   hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
-    svkeys = radix_sort(svkeys, svkeys == vk_a.as<uint64_t>() ? vk_b.as<uint64_t>()
-                                                              : vk_a.as<uint64_t>(),
-                        V, 52, 52 + bb, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
 
     // work items of 16 slices, or of 8 or 4 on graphs with too few slices to give every
     // compute unit an item of 16 (measured on the 131 K-node R-MAT graph: 126 us per
@@ -575,7 +469,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_HIP(ctx, tile_group.alloc(((size_t)T + 1) * 4));
     BG_HIP(ctx, hipMemsetAsync(tile_group.as<uint32_t>() + T, 0, 4, s));
     tile_kernel<false><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(),
-                                        (const uint4 *)cols, nnz, cbn, sl_cb.as<uint32_t>(),
+                                        skeys, cbits, cbn, sl_cb.as<uint32_t>(),
                                         sl_tile_base.as<uint32_t>(), tile_group.as<uint32_t>(),
                                         nullptr);
     BG_LAUNCH_CHECK(ctx, "tile count");
@@ -600,8 +494,8 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
     BG_HIP(ctx, idx16.alloc(((size_t)G + 1) * kGroupIds * 2));
     tail_group_kernel<<<blocks_for((int64_t)kGroupIds, 256), 256, 0, s>>>(idx16.as<uint16_t>(), G,
                                                                          cbn);
-    tile_kernel<true><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(),
-                                       (const uint4 *)cols, nnz, cbn, sl_cb.as<uint32_t>(),
+    tile_kernel<true><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(), skeys,
+                                       cbits, cbn, sl_cb.as<uint32_t>(),
                                        sl_tile_base.as<uint32_t>(), tile_group.as<uint32_t>(),
                                        idx16.as<uint16_t>());
     BG_LAUNCH_CHECK(ctx, "tile fill");
@@ -618,7 +512,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym)
                                                    sl_tile_base.as<uint32_t>(),
                                                    tile_group.as<uint32_t>(), S, W, spw, cbn,
                                                    vk_a.as<uint64_t>());
-    uint64_t *wsorted = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), W, 32, 64,
+    uint64_t *wsorted = radix_sort(vk_a.as<uint64_t>(), vk_b.as<uint64_t>(), W, 64,
                                    hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     wg_item_kernel<<<blocks_for(W, 256), 256, 0, s>>>(wsorted, W, wg_cb.as<uint32_t>(),
                                                      wg_item.as<uint2>());

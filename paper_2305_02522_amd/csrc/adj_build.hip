@@ -5,8 +5,8 @@
 // Everything runs on the GPU with hand-written kernels:
 //   1. one 64-bit key (row << cb | col) per directed pair (+ reversed pairs,
 //      + diagonal), endpoints range-checked;
-//   2. LSD radix sort of the keys, 8 bits per pass, one workgroup per tile of
-//      8,192 keys; the stable rank inside a wave comes from 8 wave votes
+//   2. LSD radix sort of the keys, 8 bits per pass, one wavefront per tile of
+//      2048 keys; the stable rank inside a wave comes from 8 wave votes
 //      (lanes with the same digit find each other through the vote masks);
 //   3. duplicates dropped with a flag-scan-compact;
 //   4. row pointers by binary search of each row's first key, degrees, and a
@@ -121,10 +121,8 @@ __global__ void degree_kernel(const uint32_t *__restrict__ rowptr, uint32_t N,
         return;
     const uint32_t d = rowptr[i + 1] - rowptr[i];
     deg[i] = (int32_t)d;
-    // Stable ascending sort of the upper half = decreasing degree, ties by row id.  d <= N, so
-    // only as many bits as N has are sorted (14 instead of 64 for 10,007 rows: two passes, not
-    // eight).
-    order_keys[i] = ((uint64_t)(N - d) << 32) | i;
+    // ascending sort of this key = decreasing degree, ties by row id
+    order_keys[i] = ((uint64_t)(0xFFFFFFFFu - d) << 32) | i;
     atomicMax(max_deg, (int)d);
 }
 
@@ -288,13 +286,13 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
         ++cb;
 
     const uint32_t sort_n = nkeys > (uint32_t)N ? nkeys : (uint32_t)N;
-    const size_t hist_words = sort_hist_words(sort_n);
+    const uint32_t sort_tiles = (sort_n + kSortTile - 1) / kSortTile;
     const uint32_t uniq_tiles = (nkeys + kScanTile - 1) / kScanTile;
     DevBuf keys_a, keys_b, hist, scan_ws, counts, flag;
     BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8));
     BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8));
-    BG_HIP(ctx, hist.alloc(hist_words * 4));
-    BG_HIP(ctx, scan_ws.alloc(scan_ws_words(hist_words) * 4));
+    BG_HIP(ctx, hist.alloc((size_t)256 * sort_tiles * 4));
+    BG_HIP(ctx, scan_ws.alloc(scan_ws_words((uint64_t)256 * sort_tiles) * 4));
     BG_HIP(ctx, counts.alloc(((size_t)uniq_tiles + 1) * 4));
     BG_HIP(ctx, flag.alloc(2 * sizeof(int)));
     BG_HIP(ctx, hipMemsetAsync(flag.p, 0, 2 * sizeof(int), s));
@@ -308,7 +306,7 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
         make_keys_kernel<<<blocks_for(span, 256), 256, 0, s>>>(
             src, dst, (uint32_t)E, (uint32_t)N, sym, loops, cb, keys_a.as<uint64_t>(), d_err);
         BG_LAUNCH_CHECK(ctx, "make_keys");
-        sorted = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nkeys, 0, 2 * cb,
+        sorted = radix_sort(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nkeys, 2 * cb,
                             hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
         BG_LAUNCH_CHECK(ctx, "radix_sort");
         uint64_t *other = sorted == keys_a.as<uint64_t>() ? keys_b.as<uint64_t>()
@@ -349,11 +347,8 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     degree_kernel<<<blocks_for(N, 256), 256, 0, s>>>(rowptr.as<uint32_t>(), (uint32_t)N,
                                                     deg.as<int32_t>(), oa, d_maxdeg);
     BG_LAUNCH_CHECK(ctx, "degree");
-    int nbits = 1; // of a value in [0, N]
-    while ((N >> nbits) > 0)
-        ++nbits;
     uint64_t *osorted =
-        radix_sort(oa, ob, (uint32_t)N, 32, 32 + nbits, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
+        radix_sort(oa, ob, (uint32_t)N, 64, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     order_from_keys_kernel<<<blocks_for(N, 256), 256, 0, s>>>(osorted, (uint32_t)N,
                                                              order.as<int32_t>());
     degree_counts_kernel<<<1, 32, 0, s>>>(order.as<int32_t>(), deg.as<int32_t>(), (uint32_t)N,
@@ -380,7 +375,7 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     if ((int64_t)nnz >= (int64_t)ctx->min_avg_degree * N) {
         keys_a.reset();
         keys_b.reset();
-        int rc = bg_build_blocked(ctx, s, adj, sym);
+        int rc = bg_build_blocked(ctx, s, adj);
         if (rc != BITGNN_OK) {
             bitgnn_adj_destroy(adj);
             return rc;

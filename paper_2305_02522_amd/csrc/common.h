@@ -208,7 +208,7 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
                          int64_t x_stride, int32_t K, int32_t kwords, const uint64_t *wbits,
                          int32_t M, int64_t w_stride, int epilogue, const int32_t *T,
                          const float *alpha, void *out, int64_t out_stride);
-int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, bool sym);
+int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj);
 void bg_free_blocked(bitgnn_blocked *b);
 int bg_ws_need(bitgnn_ctx *ctx, size_t bytes, const char *who);
 int bg_static_scratch_init(bitgnn_ctx *ctx);

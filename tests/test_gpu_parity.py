@@ -158,24 +158,6 @@ def test_adj_build_matches_set_definition(B, ctx, n, e, flags, seed):
     adj.close()
 
 
-# Edges of the sort: whole and broken tiles of 2,048 and 8,192 keys, one key around the size at
-# which the tile changes, histograms around the one-workgroup scan's largest; degrees from few
-# bits and from more than two passes' worth.
-@pytest.mark.parametrize("n,e", [(1 << 8, 2047), (255, 2048), (257, 2049), (3, 8193),
-                                 (70000, 128 * 2048), (70000, 128 * 2048 + 1),
-                                 (1 << 16, (1 << 20) - 1), (65537, 1 << 20), (999, (1 << 20) + 1)])
-def test_adj_build_sort_edges(B, ctx, n, e):
-    r = np.random.default_rng(e)
-    src, dst = W.random_graph(r, n, e)
-    src[: min(e, 2 * n) // 2] = n - 1  # one long row, repeated keys in the small graphs
-    adj = B.adj_build(ctx, dev(src), dev(dst), e, n, 0)
-    rp_ref, col_ref = orc.adjacency(src, dst, n, 0)
-    rp, col, deg = _csr_from_gpu(B, adj)
-    assert np.array_equal(rp, rp_ref) and np.array_equal(col, col_ref)
-    assert np.array_equal(deg, orc.degrees(rp_ref))
-    adj.close()
-
-
 def test_tuning_validation(B, ctx):
     for bad in ((63, 512, 32), (10209, 512, 32), (8192, 3, 32), (8192, 1024, 32), (8192, 512, -1)):
         with pytest.raises(B.BitgnnError) as e:
