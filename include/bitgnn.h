@@ -120,7 +120,9 @@ int bitgnn_ctx_bgemm_kernel(const bitgnn_ctx *ctx, int64_t n, int32_t kwords, in
 
 /* Grows the context's aggregation workspace to at least `bytes` (never shrinks it).  A
  * set-up call: it allocates, and synchronizes the device when it replaces a smaller
- * workspace, so no work of this context may be in flight or being captured.
+ * workspace, so no work of this context may be in flight or being captured.  A workspace that
+ * calls recorded into a HIP graph work in is not freed when it is replaced but with the
+ * context: such graphs may be replayed after any later reserve or build.
  * bitgnn_ctx_workspace reports the current size. */
 int bitgnn_ctx_reserve(bitgnn_ctx *ctx, size_t bytes);
 int bitgnn_ctx_workspace(const bitgnn_ctx *ctx, size_t *bytes);

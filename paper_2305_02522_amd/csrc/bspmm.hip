@@ -1505,7 +1505,7 @@ static int launch_bspmm_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj
     }
     const size_t hperm_bytes = (((size_t)adj->n * 16) + 255) & ~(size_t)255;
     const size_t part_bytes = (size_t)b->n_vrows * part_planes_for(b) * 16;
-    int rc = bg_ws_need(ctx, hperm_bytes + part_bytes, "bitgnn_bspmm");
+    int rc = bg_ws_need(ctx, s, hperm_bytes + part_bytes, "bitgnn_bspmm");
     if (rc != BITGNN_OK)
         return rc;
     uint4 *hperm = (uint4 *)ctx->sc->ws;
@@ -1564,7 +1564,7 @@ int bg_launch_agg_project_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_a
         ((size_t)b->n_vrows * part_planes_for(b) * 16 + 255) & ~(size_t)255;
     const int32_t Mpad = (M + 15) / 16 * 16;
     const size_t w8_bytes = (size_t)nwin * Mpad * 128;
-    int rc = bg_ws_need(ctx, hperm_bytes + part_bytes + w8_bytes + (size_t)nwin * Mpad * 4,
+    int rc = bg_ws_need(ctx, s, hperm_bytes + part_bytes + w8_bytes + (size_t)nwin * Mpad * 4,
                         "bitgnn_gcn_out_layer");
     if (rc != BITGNN_OK)
         return rc;
@@ -1719,7 +1719,7 @@ static int launch_bspmm_path(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *a
         ++seg_planes;
     const size_t seg_bytes = (size_t)adj->n_long_segs * seg_planes * W32 * 4;
     if (perm_bytes + seg_bytes) {
-        const int rc = bg_ws_need(ctx, perm_bytes + seg_bytes, "bitgnn_bspmm");
+        const int rc = bg_ws_need(ctx, s, perm_bytes + seg_bytes, "bitgnn_bspmm");
         if (rc != BITGNN_OK)
             return rc;
     }
@@ -1916,7 +1916,7 @@ extern "C" int bitgnn_bspmm_static(bitgnn_ctx *ctx, void *stream, const bitgnn_a
                "holds %zu (use bitgnn_bspmm)",
                need, avail);
     unsigned char *base = (unsigned char *)g_static_scratch[ctx->device];
-    bg_scratch st;
+    bg_scratch st{};
     st.queue = (uint32_t *)base;
     st.seed_table = (uint32_t *)(base + kStaticQueueBytes);
     st.seed_table_words = kSeedTableWords;
@@ -1960,7 +1960,7 @@ int bg_launch_spmm_i32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     const int64_t grid = ((vrows << lpr_log2) + kBlock - 1) / kBlock;
     BG_REQUIRE(ctx, grid < (1ll << 31), BITGNN_ERR_UNSUPPORTED, "bitgnn_spmm_i32: N too large");
     if (adj->n_long_segs) {
-        const int rc = bg_ws_need(ctx, (size_t)adj->n_long_segs * M * 4, "bitgnn_spmm_i32");
+        const int rc = bg_ws_need(ctx, s, (size_t)adj->n_long_segs * M * 4, "bitgnn_spmm_i32");
         if (rc != BITGNN_OK)
             return rc;
     }

@@ -22,6 +22,13 @@ struct bg_scratch {
     // bitgnn_adj_workspace_bytes, allocated by bitgnn_ctx_reserve / bitgnn_adj_build only
     void *ws;
     size_t ws_bytes;
+    bool ws_recorded; // a call recorded into a HIP graph works in ws
+};
+
+// A workspace that was replaced by a larger one while a recorded graph may still use it.
+struct bg_retired {
+    void *p;
+    bg_retired *next;
 };
 
 struct bitgnn_ctx {
@@ -31,6 +38,7 @@ struct bitgnn_ctx {
     void *bgemm_ws;       // device scratch of the matrix-core BMM: widened weights and their
                           // popcounts (fixed size, allocated with the context)
     bg_scratch own;       // the context's scratch
+    bg_retired *retired;  // superseded workspaces that recorded graphs hold, freed with the context
     bg_scratch *sc;       // the scratch the current call uses (&own outside such a call)
     uint32_t fused_spin_limit; // polls of one barrier wait before it is abandoned
     char err[256];
@@ -210,7 +218,7 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
                          const float *alpha, void *out, int64_t out_stride);
 int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj);
 void bg_free_blocked(bitgnn_blocked *b);
-int bg_ws_need(bitgnn_ctx *ctx, size_t bytes, const char *who);
+int bg_ws_need(bitgnn_ctx *ctx, hipStream_t s, size_t bytes, const char *who);
 int bg_static_scratch_init(bitgnn_ctx *ctx);
 // Bytes of context workspace the aggregations on `adj` need for up to C aggregated
 // channels and M output classes.

@@ -64,6 +64,12 @@ extern "C" void bitgnn_ctx_destroy(bitgnn_ctx *ctx)
         (void)hipFree(ctx->bgemm_ws);
     if (ctx->own.ws)
         (void)hipFree(ctx->own.ws);
+    while (ctx->retired) {
+        bg_retired *r = ctx->retired;
+        ctx->retired = r->next;
+        (void)hipFree(r->p);
+        free(r);
+    }
     for (int i = 0; i < 2 * kMaxTimed; ++i)
         if (ctx->tev[i])
             (void)hipEventDestroy(ctx->tev[i]);
@@ -109,23 +115,39 @@ extern "C" int bitgnn_ctx_bgemm_kernel(const bitgnn_ctx *ctx, int64_t n, int32_t
 }
 
 // The aggregation workspace.  Only this set-up call (and bitgnn_adj_build, through it)
-// allocates: it may synchronize the device to replace a smaller workspace.
+// allocates: it may synchronize the device to replace a smaller workspace.  One that a recorded
+// call works in is kept until the context is destroyed, because the graph may be replayed.
 extern "C" int bitgnn_ctx_reserve(bitgnn_ctx *ctx, size_t bytes)
 {
     if (!ctx)
         return BITGNN_ERR_INVALID_ARG;
     BG_NEED_DEVICE(ctx);
-    if (bytes <= ctx->own.ws_bytes)
+    bg_scratch &own = ctx->own;
+    if (bytes <= own.ws_bytes)
         return BITGNN_OK;
-    if (ctx->own.ws) {
-        BG_HIP(ctx, hipDeviceSynchronize());
-        BG_HIP(ctx, hipFree(ctx->own.ws));
-        ctx->own.ws = nullptr;
-        ctx->own.ws_bytes = 0;
-    }
     bytes = (bytes + (1u << 20)) & ~(size_t)((1u << 20) - 1);
-    BG_HIP(ctx, hipMalloc(&ctx->own.ws, bytes));
-    ctx->own.ws_bytes = bytes;
+    if (own.ws && own.ws_recorded) {
+        bg_retired *r = (bg_retired *)malloc(sizeof(bg_retired));
+        BG_REQUIRE(ctx, r, BITGNN_ERR_INVALID_ARG, "bitgnn_ctx_reserve: out of host memory");
+        void *ws = nullptr;
+        const hipError_t e = hipMalloc(&ws, bytes);
+        if (e != hipSuccess)
+            free(r);
+        BG_HIP(ctx, e);
+        *r = bg_retired{own.ws, ctx->retired};
+        ctx->retired = r;
+        own.ws = ws;
+    } else {
+        if (own.ws) {
+            BG_HIP(ctx, hipDeviceSynchronize());
+            BG_HIP(ctx, hipFree(own.ws));
+            own.ws = nullptr;
+            own.ws_bytes = 0;
+        }
+        BG_HIP(ctx, hipMalloc(&own.ws, bytes));
+    }
+    own.ws_bytes = bytes;
+    own.ws_recorded = false;
     return BITGNN_OK;
 }
 
@@ -137,15 +159,23 @@ extern "C" int bitgnn_ctx_workspace(const bitgnn_ctx *ctx, size_t *bytes)
     return BITGNN_OK;
 }
 
-// Compute calls never allocate: a workspace that is too small is an error.
-int bg_ws_need(bitgnn_ctx *ctx, size_t bytes, const char *who)
+// Compute calls never allocate: a workspace that is too small is an error.  Notes whether the
+// call is being recorded (the null stream cannot be; where the runtime gives no answer, it may).
+int bg_ws_need(bitgnn_ctx *ctx, hipStream_t s, size_t bytes, const char *who)
 {
-    if (bytes <= ctx->sc->ws_bytes)
-        return BITGNN_OK;
-    return bitgnn_fail(ctx, BITGNN_ERR_WORKSPACE,
-                       "%s: needs %zu bytes of workspace, %zu available "
-                       "(bitgnn_adj_workspace_bytes + bitgnn_ctx_reserve)",
-                       who, bytes, ctx->sc->ws_bytes);
+    if (bytes > ctx->sc->ws_bytes)
+        return bitgnn_fail(ctx, BITGNN_ERR_WORKSPACE,
+                           "%s: needs %zu bytes of workspace, %zu available "
+                           "(bitgnn_adj_workspace_bytes + bitgnn_ctx_reserve)",
+                           who, bytes, ctx->sc->ws_bytes);
+    if (s && !ctx->sc->ws_recorded) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        const bool known = hipStreamIsCapturing(s, &st) == hipSuccess;
+        if (!known)
+            (void)hipGetLastError();
+        ctx->sc->ws_recorded = !known || st != hipStreamCaptureStatusNone;
+    }
+    return BITGNN_OK;
 }
 
 extern "C" int bitgnn_ctx_kernel_timing(bitgnn_ctx *ctx, int enable)

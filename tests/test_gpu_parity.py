@@ -933,6 +933,61 @@ def test_layer_calls_capture_into_a_hip_graph_on_a_fresh_context(B, tuning):
     c.close()
 
 
+@pytest.mark.parametrize("grow", ["reserve", "build"])
+@pytest.mark.parametrize("tuning", ["blocked-small", "csr-only"])
+def test_recorded_calls_survive_a_larger_workspace(B, tuning, grow):
+    """Graphs recorded before the context's workspace grows are replayed afterwards, with new
+    allocations in between that would take the place of a workspace that was freed."""
+    c = B.Context(0)
+    B.ctx_set_tuning(c, *TUNINGS[tuning])
+    n, C, M = 3000, 128, 40
+    adj, rp, col, r = _graph(B, c, n, 150000, W.ADJ_SYMMETRIZE, 99, hubs=1)
+    v = W.pm1(r, (n, C))
+    z = r.integers(-90, 91, size=(n, M)).astype(np.int32)
+    t = r.integers(-3, 4, size=C).astype(np.int32)
+    hb, zd, td, alpha = _pack_host(v), dev(z), dev(t), dev(np.ones(M, np.float32))
+    bits = torch.empty((n, 2), dtype=torch.int64, device="cuda")
+    y, f = torch.empty((n, M), device="cuda"), torch.empty((n, C), device="cuda")
+
+    def calls():
+        B.bspmm(c, adj, hb, C, 2, B.EPI_THRESH_BITS, td, bits, 2)
+        B.spmm_i32(c, adj, zd, M, M, 90, alpha, y, M)
+        B.spmm_f32(c, adj, hb, True, C, 2, None, None, B.EPI_SCALE_F32, None, f, C)
+
+    calls()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    had = B.ctx_workspace(c)
+    other = None
+    if grow == "reserve":
+        B.ctx_reserve(c, 3 * had)
+    else:
+        other = _graph(B, c, 60000, 1500000, W.ADJ_SYMMETRIZE, 100, hubs=1)[0]
+        B.ctx_reserve(c, max(B.adj_workspace_bytes(c, other, 512, 64), 2 * had))
+    assert B.ctx_workspace(c) > had
+    hog = [torch.full((had // 4,), -1, dtype=torch.int32, device="cuda") for _ in range(4)]
+    s = orc.spmm_pm1(rp, col, v)
+    for rep in range(3):
+        for o in (bits, y, f):
+            o.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(words_np(bits), orc.to_words(orc.rebin(s, t))), rep
+        assert np.array_equal(y.cpu().numpy(), orc.spmm_i64(rp, col, z).astype(np.float32)), rep
+        assert np.array_equal(f.cpu().numpy(), s.astype(np.float32)), rep
+        assert all(bool((h == -1).all()) for h in hog)
+        calls()                                              # eager work between the replays
+    torch.cuda.synchronize()
+    del graph
+    for a in (adj, other):
+        if a is not None:
+            a.close()
+    c.close()
+
+
 def test_compute_calls_report_a_workspace_that_is_too_small(B):
     """A call that needs more workspace than was reserved fails with ERR_WORKSPACE instead of
     allocating; after bitgnn_ctx_reserve it runs and is right."""
