@@ -113,8 +113,7 @@ __global__ void rowptr_kernel(const uint64_t *__restrict__ ukeys, uint32_t nnz, 
 }
 
 __global__ void degree_kernel(const uint32_t *__restrict__ rowptr, uint32_t N,
-                              int32_t *__restrict__ deg, uint64_t *__restrict__ order_keys,
-                              int *__restrict__ max_deg)
+                              int32_t *__restrict__ deg, uint64_t *__restrict__ order_keys)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N)
@@ -123,24 +122,6 @@ __global__ void degree_kernel(const uint32_t *__restrict__ rowptr, uint32_t N,
     deg[i] = (int32_t)d;
     // ascending sort of this key = decreasing degree, ties by row id
     order_keys[i] = ((uint64_t)(0xFFFFFFFFu - d) << 32) | i;
-    atomicMax(max_deg, (int)d);
-}
-
-// thread k < 32: rows with at least 2^k neighbours, by binary search in the degree order
-__global__ void degree_counts_kernel(const int32_t *__restrict__ order,
-                                     const int32_t *__restrict__ deg, uint32_t N,
-                                     uint32_t *__restrict__ n_ge)
-{
-    const uint32_t k = threadIdx.x;
-    uint32_t lo = 0, hi = N;
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if ((uint32_t)deg[order[mid]] >= (1u << k))
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    n_ge[k] = lo;
 }
 
 __global__ void rank_kernel(const int32_t *__restrict__ order, uint32_t N,
@@ -189,12 +170,28 @@ __global__ void col_slot_kernel(const int32_t *__restrict__ col, uint32_t nnz,
         col_slot[e] = rank[col[e]];
 }
 
+// What the host reads of the degree order in one copy.
+struct DegreeInfo {
+    int32_t max_degree;
+    uint32_t n_ge[32]; // rows with at least 2^k neighbours (zero on entry)
+};
+
 __global__ void order_from_keys_kernel(const uint64_t *__restrict__ keys, uint32_t N,
-                                       int32_t *__restrict__ order)
+                                       int32_t *__restrict__ order, DegreeInfo *__restrict__ info)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N)
-        order[i] = (int32_t)(uint32_t)keys[i];
+    if (i >= N)
+        return;
+    const uint64_t key = keys[i];
+    order[i] = (int32_t)(uint32_t)key;
+    // this row is the last with at least 2^k neighbours for every k between the next row's
+    // degree and its own
+    const uint32_t d = 0xFFFFFFFFu - (uint32_t)(key >> 32);
+    const uint32_t next = i + 1 < N ? 0xFFFFFFFFu - (uint32_t)(keys[i + 1] >> 32) : 0u;
+    for (int k = 32 - __clz((int)next); k < 32 - __clz((int)d); ++k)
+        info->n_ge[k] = i + 1;
+    if (i == 0)
+        info->max_degree = (int32_t)d;
 }
 
 } // namespace
@@ -294,10 +291,10 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     BG_HIP(ctx, hist.alloc((size_t)256 * sort_tiles * 4));
     BG_HIP(ctx, scan_ws.alloc(scan_ws_words((uint64_t)256 * sort_tiles) * 4));
     BG_HIP(ctx, counts.alloc(((size_t)uniq_tiles + 1) * 4));
-    BG_HIP(ctx, flag.alloc(2 * sizeof(int)));
-    BG_HIP(ctx, hipMemsetAsync(flag.p, 0, 2 * sizeof(int), s));
+    BG_HIP(ctx, flag.alloc(sizeof(int) + sizeof(DegreeInfo)));
+    BG_HIP(ctx, hipMemsetAsync(flag.p, 0, sizeof(int) + sizeof(DegreeInfo), s));
     int *d_err = flag.as<int>();
-    int *d_maxdeg = d_err + 1;
+    DegreeInfo *d_info = (DegreeInfo *)(d_err + 1);
 
     uint64_t *sorted = keys_a.as<uint64_t>();
     uint32_t nnz = 0;
@@ -328,9 +325,7 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     BG_REQUIRE(ctx, h_err == 0, BITGNN_ERR_INDEX_RANGE,
                "bitgnn_adj_build: an edge endpoint is outside [0, %lld)", (long long)N);
 
-    DevBuf rowptr, col, deg, order, n_ge;
-    uint32_t h_n_ge[32];
-    BG_HIP(ctx, n_ge.alloc(sizeof(h_n_ge)));
+    DevBuf rowptr, col, deg, order;
     BG_HIP(ctx, rowptr.alloc(((size_t)N + 1) * 4));
     BG_HIP(ctx, col.alloc((size_t)nnz * 4));
     BG_HIP(ctx, deg.alloc((size_t)N * 4));
@@ -345,18 +340,15 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     BG_HIP(ctx, hipStreamSynchronize(s));
     uint64_t *oa = keys_a.as<uint64_t>(), *ob = keys_b.as<uint64_t>();
     degree_kernel<<<blocks_for(N, 256), 256, 0, s>>>(rowptr.as<uint32_t>(), (uint32_t)N,
-                                                    deg.as<int32_t>(), oa, d_maxdeg);
+                                                    deg.as<int32_t>(), oa);
     BG_LAUNCH_CHECK(ctx, "degree");
     uint64_t *osorted =
         radix_sort(oa, ob, (uint32_t)N, 64, hist.as<uint32_t>(), scan_ws.as<uint32_t>(), s);
     order_from_keys_kernel<<<blocks_for(N, 256), 256, 0, s>>>(osorted, (uint32_t)N,
-                                                             order.as<int32_t>());
-    degree_counts_kernel<<<1, 32, 0, s>>>(order.as<int32_t>(), deg.as<int32_t>(), (uint32_t)N,
-                                          n_ge.as<uint32_t>());
+                                                             order.as<int32_t>(), d_info);
     BG_LAUNCH_CHECK(ctx, "order");
-    BG_HIP(ctx, hipMemcpyAsync(h_n_ge, n_ge.p, sizeof(h_n_ge), hipMemcpyDeviceToHost, s));
-    int h_maxdeg = 0;
-    BG_HIP(ctx, hipMemcpyAsync(&h_maxdeg, d_maxdeg, sizeof(int), hipMemcpyDeviceToHost, s));
+    DegreeInfo info;
+    BG_HIP(ctx, hipMemcpyAsync(&info, d_info, sizeof(info), hipMemcpyDeviceToHost, s));
     BG_HIP(ctx, hipStreamSynchronize(s));
 
     bitgnn_adj *adj = (bitgnn_adj *)calloc(1, sizeof(bitgnn_adj));
@@ -364,8 +356,8 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     adj->device = ctx->device;
     adj->n = N;
     adj->nnz = nnz;
-    adj->max_degree = h_maxdeg;
-    memcpy(adj->n_ge, h_n_ge, sizeof(h_n_ge));
+    adj->max_degree = info.max_degree;
+    memcpy(adj->n_ge, info.n_ge, sizeof(info.n_ge));
     adj->device_bytes = ((size_t)N + 1) * 4 + (size_t)nnz * 4 + (size_t)N * 8;
     adj->rowptr = (uint32_t *)rowptr.release();
     adj->col = (int32_t *)col.release();
