@@ -184,32 +184,36 @@ extern "C" int bitgnn_add(bitgnn_ctx *ctx, void *stream, const void *a, int a_is
                BITGNN_ERR_ALIGNMENT, "bitgnn_add: misaligned pointer");
     BG_NEED_DEVICE(ctx);
     hipStream_t s = (hipStream_t)stream;
-    const int64_t waves = (n * words + 63) / 64;
-    const int64_t blocks = C >= 4 ? (waves + kAddBlock / 64 - 1) / (kAddBlock / 64)
-                                  : (n + kAddBlock - 1) / kAddBlock;
-    BG_REQUIRE(ctx, blocks < (1ll << 31), BITGNN_ERR_UNSUPPORTED,
-               "bitgnn_add: n*C too large for one launch");
+    // A launch takes fewer than 2^32 threads: rows in chunks of at most 2^30 tiles.
+    const int64_t chunk = C >= 4 ? (1ll << 30) / words : 1ll << 30;
+    for (int64_t r0 = 0; r0 < n; r0 += chunk) {
+        const int64_t rows = n - r0 < chunk ? n - r0 : chunk;
+        const int64_t threads = C >= 4 ? (rows * words + 63) / 64 * 64 : rows;
+        const unsigned blocks = (unsigned)((threads + kAddBlock - 1) / kAddBlock);
+        const void *pa = (const char *)a + r0 * lda * (a_is_bits ? 8 : 4);
+        const void *pb = (const char *)b + r0 * ldb * (b_is_bits ? 8 : 4);
+        void *po = (char *)out + r0 * ldo * (bits_out ? 8 : 4);
 #define BG_ADD(AB, BB, OB)                                                                        \
     do {                                                                                          \
         if (C >= 4)                                                                               \
-            add4_kernel<AB, BB, OB><<<(unsigned)blocks, kAddBlock, 0, s>>>(                       \
-                a, lda, b, ldb, n, C, (int32_t)words, tau, out, ldo);                             \
+            add4_kernel<AB, BB, OB><<<blocks, kAddBlock, 0, s>>>(pa, lda, pb, ldb, rows, C,       \
+                                                                 (int32_t)words, tau, po, ldo);   \
         else                                                                                      \
-            add_narrow_kernel<AB, BB, OB><<<(unsigned)blocks, kAddBlock, 0, s>>>(                 \
-                a, lda, b, ldb, n, C, tau, out, ldo);                                             \
+            add_narrow_kernel<AB, BB, OB><<<blocks, kAddBlock, 0, s>>>(pa, lda, pb, ldb, rows, C, \
+                                                                       tau, po, ldo);             \
     } while (0)
-    const int sel = (a_is_bits ? 4 : 0) | (b_is_bits ? 2 : 0) | (bits_out ? 1 : 0);
-    switch (sel) {
-    case 0: BG_ADD(false, false, false); break;
-    case 1: BG_ADD(false, false, true); break;
-    case 2: BG_ADD(false, true, false); break;
-    case 3: BG_ADD(false, true, true); break;
-    case 4: BG_ADD(true, false, false); break;
-    case 5: BG_ADD(true, false, true); break;
-    case 6: BG_ADD(true, true, false); break;
-    default: BG_ADD(true, true, true); break;
-    }
+        switch ((a_is_bits ? 4 : 0) | (b_is_bits ? 2 : 0) | (bits_out ? 1 : 0)) {
+        case 0: BG_ADD(false, false, false); break;
+        case 1: BG_ADD(false, false, true); break;
+        case 2: BG_ADD(false, true, false); break;
+        case 3: BG_ADD(false, true, true); break;
+        case 4: BG_ADD(true, false, false); break;
+        case 5: BG_ADD(true, false, true); break;
+        case 6: BG_ADD(true, true, false); break;
+        default: BG_ADD(true, true, true); break;
+        }
 #undef BG_ADD
+    }
     BG_LAUNCH_CHECK(ctx, "add_kernel");
     return BITGNN_OK;
 }

@@ -627,6 +627,23 @@ def test_add_edges_of_the_four_channel_lanes(B, ctx, n, C):
         test_add_variants(B, ctx, n, C, *bits)
 
 
+def test_add_beyond_the_threads_of_one_launch(B, ctx):
+    """2^32 tiles and some: more than a launch takes.  a + a >= 0 gives a's own bits."""
+    n = (1 << 32) + 130
+    if torch.cuda.mem_get_info()[0] < 5 * 8 * n // 2:
+        pytest.skip("needs 80 GiB of free device memory")
+    a = torch.arange(n, dtype=torch.int64, device="cuda")
+    a *= 0x1E3779B97F4A7C15
+    out = torch.zeros_like(a)
+    B.add(ctx, a, True, 1, a, True, 1, n, 64, B.EPI_THRESH_BITS,
+          torch.zeros(64, device="cuda"), out, 1)
+    torch.cuda.synchronize()
+    for i in range(0, n, 1 << 30):
+        assert torch.equal(out[i:i + (1 << 30)], a[i:i + (1 << 30)]), i
+    del a, out
+    torch.cuda.empty_cache()
+
+
 def test_add_merges_a_sage_layer_like_the_concatenated_form(B, ctx):
     """ADD.FFF on the two scaled products of a GraphSAGE layer, binarized: the bits of the
     library's concatenated layer."""
