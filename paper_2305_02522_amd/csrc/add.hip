@@ -4,12 +4,14 @@
 // as the other low-level functions do).
 //
 // gfx950 mapping: 16 lanes take a 64-channel tile of a row, 4 channels each: 16 bytes of a
-// float operand, one broadcast 8-byte word of a bit operand, and four tiles are in flight per
-// 16 lanes.  The thresholded bits of a lane are a nibble; four DPP OR steps leave the tile's
-// word in all 16 lanes, each lane keeps the word of one of 16 consecutive tiles and the
-// wavefront stores 64 words at once.  Bound by the HBM stream of the operands / result:
-// 300,001 x 100 floats, two operands to bits, 69 -> 37 us (one channel per lane and one tile
-// per wavefront and turn before).
+// float operand, one broadcast 8-byte word of a bit operand.  A wavefront's 64 lanes take four
+// adjacent tiles (1 KB of a float operand per load) and go on by four tiles a turn, four turns
+// in flight.  The thresholded bits of a lane are a nibble; four DPP OR steps leave the tile's
+// word in all 16 lanes, each lane keeps the word of one turn and the wavefront stores all its
+// words at once.  Bound by the HBM stream of the operands / result: 300,001 x 100 floats, two
+// operands to bits, 62 -> 36 us against one channel per lane and one tile per wavefront and
+// turn; 131,072 x 128 floats to floats 31 -> 32, 19,717 x 256 11.3 -> 10.1 (16 consecutive
+// tiles per 16 lanes had taken 38 and 13.2 there).
 #include "common.h"
 
 namespace {
@@ -55,6 +57,7 @@ template <bool A_BITS, bool B_BITS, bool BITS_OUT>
 __global__ __launch_bounds__(kAddBlock) void add4_kernel(const void *__restrict__ a, int64_t lda,
                                                          const void *__restrict__ b, int64_t ldb,
                                                          int64_t n, int32_t C, int32_t tiles,
+                                                         int32_t turns,
                                                          const float *__restrict__ tau,
                                                          void *__restrict__ out, int64_t ldo)
 {
@@ -62,18 +65,21 @@ __global__ __launch_bounds__(kAddBlock) void add4_kernel(const void *__restrict_
     const int64_t wave = (int64_t)blockIdx.x * (kAddBlock / 64) +
                          __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t total = n * (int64_t)tiles;
-    const int64_t q0 = wave * 64; // first tile of this wavefront
+    const int64_t q0 = wave * (4 * turns); // first tile of this wavefront
     if (q0 >= total)
         return;
-    const int64_t rowb = q0 / tiles; // wave-uniform; the tiles' rows follow in 32 bits
-    const uint32_t offb = (uint32_t)(q0 - rowb * tiles) + 16u * (uint32_t)grp;
+    // four tiles a turn, one per 16 lanes; wave-uniform first row, the tiles' rows follow in 32 bits
+    const int64_t rowb = q0 / tiles;
+    const uint32_t offb = (uint32_t)(q0 - rowb * tiles) + (uint32_t)grp;
     uint32_t drow = offb / (uint32_t)tiles;
     int32_t t = (int32_t)(offb - drow * (uint32_t)tiles);
+    const uint32_t turn_rows = 4u / (uint32_t)tiles;
+    const int32_t turn_tiles = 4 - (int32_t)turn_rows * tiles;
     const int64_t last = n - 1 - rowb;
     const uint32_t dlast = last > 64 ? 64u : (uint32_t)last; // rows past the last are clamped
     uint32_t mine_lo = 0, mine_hi = 0, mine_drow = 0;
     int32_t mine_t = 0;
-    for (int i0 = 0; i0 < 16; i0 += kAddUnroll) {
+    for (int i0 = 0; i0 < turns; i0 += kAddUnroll) {
         add_piece<A_BITS> va[kAddUnroll];
         add_piece<B_BITS> vb[kAddUnroll];
         float tv[kAddUnroll][4];
@@ -94,8 +100,10 @@ __global__ __launch_bounds__(kAddBlock) void add4_kernel(const void *__restrict_
                 mine_drow = drow;
                 mine_t = t;
             }
-            if (++t == tiles) {
-                t = 0;
+            drow += turn_rows;
+            t += turn_tiles;
+            if (t >= tiles) {
+                t -= tiles;
                 ++drow;
             }
         }
@@ -124,7 +132,7 @@ __global__ __launch_bounds__(kAddBlock) void add4_kernel(const void *__restrict_
             }
         }
     }
-    if (BITS_OUT && q0 + lane < total)
+    if (BITS_OUT && sub < turns && q0 + 4 * sub + grp < total)
         ((uint64_t *)out)[(rowb + mine_drow) * ldo + mine_t] = ((uint64_t)mine_hi << 32) | mine_lo;
 }
 
@@ -184,11 +192,16 @@ extern "C" int bitgnn_add(bitgnn_ctx *ctx, void *stream, const void *a, int a_is
                BITGNN_ERR_ALIGNMENT, "bitgnn_add: misaligned pointer");
     BG_NEED_DEVICE(ctx);
     hipStream_t s = (hipStream_t)stream;
-    // A launch takes fewer than 2^32 threads: rows in chunks of at most 2^30 tiles.
-    const int64_t chunk = C >= 4 ? (1ll << 30) / words : 1ll << 30;
+    // A launch takes fewer than 2^32 threads: rows in chunks of at most 2^28 tiles.
+    const int64_t chunk = C >= 4 ? (1ll << 28) / words : 1ll << 30;
     for (int64_t r0 = 0; r0 < n; r0 += chunk) {
         const int64_t rows = n - r0 < chunk ? n - r0 : chunk;
-        const int64_t threads = C >= 4 ? (rows * words + 63) / 64 * 64 : rows;
+        // 16 turns store 64 words at once; below 2^18 tiles (8 wavefronts of 4 turns per SIMD and
+        // two rounds) 4 turns, so that more wavefronts share the work: 19,717 x 500, bits and
+        // floats to bits 15.4 us with 16 turns, 9.5 with 4.
+        const int turns = rows * words < 1 << 18 ? 4 : 16;
+        const int64_t threads =
+            C >= 4 ? (rows * words + 4 * turns - 1) / (4 * turns) * 64 : rows;
         const unsigned blocks = (unsigned)((threads + kAddBlock - 1) / kAddBlock);
         const void *pa = (const char *)a + r0 * lda * (a_is_bits ? 8 : 4);
         const void *pb = (const char *)b + r0 * ldb * (b_is_bits ? 8 : 4);
@@ -196,8 +209,8 @@ extern "C" int bitgnn_add(bitgnn_ctx *ctx, void *stream, const void *a, int a_is
 #define BG_ADD(AB, BB, OB)                                                                        \
     do {                                                                                          \
         if (C >= 4)                                                                               \
-            add4_kernel<AB, BB, OB><<<blocks, kAddBlock, 0, s>>>(pa, lda, pb, ldb, rows, C,       \
-                                                                 (int32_t)words, tau, po, ldo);   \
+            add4_kernel<AB, BB, OB><<<blocks, kAddBlock, 0, s>>>(                                 \
+                pa, lda, pb, ldb, rows, C, (int32_t)words, turns, tau, po, ldo);                  \
         else                                                                                      \
             add_narrow_kernel<AB, BB, OB><<<blocks, kAddBlock, 0, s>>>(pa, lda, pb, ldb, rows, C, \
                                                                        tau, po, ldo);             \

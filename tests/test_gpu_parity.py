@@ -620,9 +620,11 @@ def test_add_variants(B, ctx, n, C, a_bits, b_bits):
     assert np.all(gb[:, wds] == np.uint64(0xFFFFFFFFFFFFFFFF))
 
 
-@pytest.mark.parametrize("n,C", [(3, 2), (130, 3), (65, 4), (33, 5), (64, 63), (17, 67), (9, 1100)])
+@pytest.mark.parametrize("n,C", [(3, 2), (130, 3), (65, 4), (33, 5), (64, 63), (17, 67), (9, 1100),
+                                 (21, 129), (7, 257), (90001, 130)])
 def test_add_edges_of_the_four_channel_lanes(B, ctx, n, C):
-    """Rows shorter than a lane's 4 channels, rows that end inside them, more tiles than rows."""
+    """Rows shorter than a lane's 4 channels, rows that end inside them, more tiles than rows,
+    rows of 3 and 5 tiles (a wavefront goes on by 4), more than 2^18 tiles (16 turns)."""
     for bits in ((False, False), (True, True), (False, True)):
         test_add_variants(B, ctx, n, C, *bits)
 
