@@ -86,7 +86,6 @@ struct SpmmArgs {
     const uint32_t *rowptr;
     const int32_t *col;
     const int32_t *order;
-    uint32_t n;
     const void *x;
     int64_t row_bytes; // bytes from one row of x to the next
     const float *xscale;
@@ -96,6 +95,7 @@ struct SpmmArgs {
     int64_t ldo;
     uint32_t n_hub;       // rows (the first of the degree order) that take the hub form
     uint32_t hub_tiles;   // 64-channel tiles of a hub row
+    uint32_t slot0, slot_end; // rows of the teams, in degree order
     uint32_t windows;      // channel windows of a row
     uint32_t window_major; // order of the teams
     uint32_t team_blocks;  // window_major: workgroups per window
@@ -319,8 +319,8 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
         window = team - team_row * a.windows;
     }
     const uint32_t sub = threadIdx.x & 15;
-    const uint32_t slot = a.n_hub + team_row;
-    const bool has = slot < a.n;
+    const uint32_t slot = a.slot0 + team_row;
+    const bool has = slot < a.slot_end;
     const uint32_t i = has ? (uint32_t)a.order[slot] : 0u;
     const uint32_t beg = has ? a.rowptr[i] : 0u, deg = has ? a.rowptr[i + 1] - beg : 0u;
     // row lengths of the wavefront's four teams (scalar)
@@ -525,7 +525,6 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     a.rowptr = adj->rowptr;
     a.col = adj->col;
     a.order = adj->order;
-    a.n = (uint32_t)adj->n;
     a.x = x;
     a.row_bytes = ldx * (xscale ? 2 : x_is_bits ? 8 : 4);
     a.xscale = xscale;
@@ -547,29 +546,26 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     // (about 70 G cache lines a second).  232,965 nodes, 110.6 M non-zeros, longest row 9,735,
     // int16 rows of 41 channels: 1,675 us without hubs, 2,063 with; 300,001 nodes, 14.7 M
     // non-zeros, longest row 3,676, float rows of 64 channels: 397 without, 353 with.
-    const int lines = (C * (xscale ? 16 : x_is_bits ? 1 : 32) + 1023) / 1024;
-    a.n_hub = 2.0 * 65.0 * (double)adj->max_degree > (double)adj->nnz * lines / 70.0 ? adj->n_ge[k]
-                                                                                    : 0;
+    const int64_t lines = ((int64_t)C * (xscale ? 16 : x_is_bits ? 1 : 32) + 1023) / 1024;
     a.hub_tiles = ((uint32_t)C + 63) / 64;
+    uint32_t n_hub = 2.0 * 65.0 * (double)adj->max_degree > (double)adj->nnz * (double)lines / 70.0
+                         ? adj->n_ge[k]
+                         : 0;
+    // (a launch takes fewer than 2^32 threads)
+    if ((uint64_t)n_hub * a.hub_tiles * kHubBlock > 1u << 30)
+        n_hub = 0;
     // channels per lane: 16 bytes of a float row, 8 of an integer row, 4 or 8 bits; narrow
     // rows spread over all lanes of a team
     const int V = x_is_bits && !xscale ? (C <= 64 ? 4 : 8) : C <= 16 ? 1 : 4;
     a.windows = ((uint32_t)C + kTeam * V - 1) / (kTeam * V);
-    const uint64_t rows = a.n - a.n_hub;
-    const uint32_t threads = a.n_hub ? kHubBlock : kSpBlock, kTeams = threads / kTeam;
-    a.team_blocks = (uint32_t)((rows + kTeams - 1) / kTeams);
     // One window of all rows after the other keeps a smaller table hot in L2; it pays when the
     // windows are whole cache lines and nothing but the rows is gathered (300,001 nodes, 128
     // floats: 683 us against 769; with factors, which are gathered once per window, it loses).
     a.window_major = a.windows > 1 && !f && !x_is_bits && a.row_bytes % 128 == 0 &&
                      bg_aligned(x, 128) &&
                      (uint64_t)adj->n * (uint64_t)a.row_bytes > (8u << 20);
-    const uint64_t grid = (uint64_t)a.n_hub * a.hub_tiles +
-                          (a.window_major ? (uint64_t)a.windows * a.team_blocks
-                                          : (rows * a.windows + kTeams - 1) / kTeams);
-    BG_REQUIRE(ctx, grid < (1ull << 31), BITGNN_ERR_UNSUPPORTED, "bitgnn_spmm_f32: N*C too large");
     const bool big = (uint64_t)adj->n * (uint64_t)a.row_bytes >= (1ull << 32);
-    bg_time_begin(ctx, s);
+    uint32_t threads, grid;
     auto launch = [&](auto xk, auto v) {
         constexpr int XK = decltype(xk)::value, VV = decltype(v)::value;
         auto go = [&](auto bo, auto hf, auto bg) {
@@ -577,9 +573,9 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
                            BG = decltype(bg)::value;
             if (a.n_hub)
                 spmm_f32_kernel<XK, BO, HF, VV, BG, true>
-                    <<<(unsigned)grid, threads, kHubLds, s>>>(a);
+                    <<<grid, threads, kHubLds, s>>>(a);
             else
-                spmm_f32_kernel<XK, BO, HF, VV, BG, false><<<(unsigned)grid, threads, 0, s>>>(a);
+                spmm_f32_kernel<XK, BO, HF, VV, BG, false><<<grid, threads, 0, s>>>(a);
         };
         auto go2 = [&](auto bo, auto hf) {
             big ? go(bo, hf, std::true_type{}) : go(bo, hf, std::false_type{});
@@ -587,21 +583,36 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
         auto go3 = [&](auto bo) { f ? go2(bo, std::true_type{}) : go2(bo, std::false_type{}); };
         bits_out ? go3(std::true_type{}) : go3(std::false_type{});
     };
-    if (xscale) {
-        if (V == 1)
-            launch(const_int<2>{}, const_int<1>{});
-        else
-            launch(const_int<2>{}, const_int<4>{});
-    } else if (x_is_bits) {
-        if (V == 4)
-            launch(const_int<1>{}, const_int<4>{});
-        else
-            launch(const_int<1>{}, const_int<8>{});
-    } else {
-        if (V == 1)
-            launch(const_int<0>{}, const_int<1>{});
-        else
-            launch(const_int<0>{}, const_int<4>{});
+    // One launch, unless there are more than 2^26 teams.
+    const int64_t rows_max = (1ll << 26) / a.windows;
+    bg_time_begin(ctx, s);
+    for (int64_t slot = n_hub; slot == n_hub || slot < adj->n; slot += rows_max) {
+        const int64_t rows = adj->n - slot < rows_max ? adj->n - slot : rows_max;
+        a.slot0 = (uint32_t)slot;
+        a.slot_end = (uint32_t)(slot + rows);
+        a.n_hub = slot == n_hub ? n_hub : 0; // the hub rows start first
+        threads = a.n_hub ? kHubBlock : kSpBlock;
+        const uint32_t teams = threads / kTeam; // of a workgroup
+        a.team_blocks = ((uint32_t)rows + teams - 1) / teams;
+        grid = a.n_hub * a.hub_tiles +
+               (a.window_major ? a.windows * a.team_blocks
+                               : ((uint32_t)rows * a.windows + teams - 1) / teams);
+        if (xscale) {
+            if (V == 1)
+                launch(const_int<2>{}, const_int<1>{});
+            else
+                launch(const_int<2>{}, const_int<4>{});
+        } else if (x_is_bits) {
+            if (V == 4)
+                launch(const_int<1>{}, const_int<4>{});
+            else
+                launch(const_int<1>{}, const_int<8>{});
+        } else {
+            if (V == 1)
+                launch(const_int<0>{}, const_int<1>{});
+            else
+                launch(const_int<0>{}, const_int<4>{});
+        }
     }
     bg_time_end(ctx, s);
     BG_LAUNCH_CHECK(ctx, "bitgnn_spmm_f32");

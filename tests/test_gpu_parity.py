@@ -537,6 +537,34 @@ def test_spmm_f32_long_rows(B, ctx, C):
     adj.close()
 
 
+def test_spmm_f32_beyond_the_teams_of_one_launch(B, ctx):
+    """More than 2^28 teams of 16 lanes (33,000 rows x 8,192 windows of 128 channels), five
+    launches.  Every row has one neighbour, so its bits are that neighbour's; one row in eight
+    has none, and its zeros are below the threshold."""
+    n, cw = 33000, 16384
+    if torch.cuda.mem_get_info()[0] < 4 * 8 * n * cw:
+        pytest.skip("needs 18 GB of free device memory")
+    r = np.random.default_rng(17)
+    src = r.permutation(n).astype(np.int32)[: n - n // 8]
+    dst = r.integers(0, n, size=len(src), dtype=np.int32)
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, 0)
+    x = torch.arange(n * cw, dtype=torch.int64, device="cuda").view(n, cw)
+    x *= 0x1E3779B97F4A7C15
+    out = torch.full((n, cw), -1, dtype=torch.int64, device="cuda")
+    B.spmm_f32(ctx, adj, x, True, 64 * cw, cw, None, None, B.EPI_THRESH_BITS,
+               torch.full((64 * cw,), 0.5, device="cuda"), out, cw)
+    torch.cuda.synchronize()
+    ids = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+    ids[dev(src).long()] = dev(dst).long()
+    for i in range(0, n, 4096):
+        j = ids[i:i + 4096]
+        want = x[j.clamp(min=0)] * (j >= 0).unsqueeze(1)
+        assert torch.equal(out[i:i + 4096], want), i
+    adj.close()
+    del x, out
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("C", [31, 64, 300])
 def test_spmm_f32_bits_without_factors(B, ctx, tuned, C):
     """+-1 rows without factors go through the bit aggregation (both formats), or, on a context
