@@ -134,15 +134,23 @@ __device__ __forceinline__ void scaled_epilogue(const uint32_t (&acc)[P], uint32
                     cnt[b] |= ((a >> b) & 1u) << p;
             }
         uint32_t byte = 0;
+        float y[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
-            const float y = ri * __builtin_fmaf(2.0f, (float)cnt[b], -fdeg);
+            y[b] = ri * __builtin_fmaf(2.0f, (float)cnt[b], -fdeg);
             if (EPI == kEpiScaledBits) // (bits past the row's end are cleared below)
-                byte |= y >= s_tau[(b0 + b) * W32 + w] ? 1u << b : 0u;
-            else if (b0 + b < tail)
-                o[b0 + b] = y;
+                byte |= y[b] >= s_tau[(b0 + b) * W32 + w] ? 1u << b : 0u;
         }
         ge |= byte << b0;
+        if (EPI == kEpiScaledF32) {
+            if (b0 + 8 <= tail)
+                __builtin_memcpy(o + b0, y, sizeof(y));
+            else
+#pragma unroll
+                for (int b = 0; b < 8; ++b)
+                    if (b0 + b < tail)
+                        o[b0 + b] = y[b];
+        }
     }
     if (EPI == kEpiScaledBits) {
         if (tail < 32u)
