@@ -349,17 +349,18 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
         const uint32_t k = t + sub;
         return (uint32_t)a.col[k < deg ? beg + k : deg ? beg + deg - 1 : 0u];
     };
-    // kAhead neighbours (from the first'th on) of the block whose ids the team holds
-    auto load = [&](uint32_t id, auto first, piece (&x)[kAhead]) {
+    // the neighbours from the first'th on of the block whose ids the team holds, as many as the
+    // array takes
+    auto load = [&](uint32_t id, auto first, auto &x) {
         constexpr int K0 = decltype(first)::value;
-        static_for<0, kAhead>([&](auto kk) {
+        static_for<0, (int)(sizeof(x) / sizeof(x[0]))>([&](auto kk) {
             constexpr int K = decltype(kk)::value;
             x[K] = xl.template load<K0 + K, BIG>(a, id);
         });
     };
-    auto consume = [&](float fl, auto first, const piece (&x)[kAhead], uint32_t t, auto full) {
+    auto consume = [&](float fl, auto first, const auto &x, uint32_t t, auto full) {
         constexpr int K0 = decltype(first)::value;
-        static_for<0, kAhead>([&](auto kk) {
+        static_for<0, (int)(sizeof(x) / sizeof(x[0]))>([&](auto kk) {
             constexpr int K = decltype(kk)::value;
             const float fk = HASF ? row_bcast_f<K0 + K>(fl) : 1.0f;
             if (decltype(full)::value || t + K0 + K < deg) {
@@ -371,37 +372,52 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
             }
         });
     };
-    // The ids of a block of 16 neighbours are requested two blocks ahead, the factors one
-    // block ahead, the rows kAhead neighbours ahead.
-    uint32_t id0 = ids_of(0), id1 = ids_of(16);
-    float f0 = HASF ? a.f[id0] : 1.0f;
-    piece x[2][kAhead];
-    __builtin_amdgcn_sched_barrier(0); // ids and factors stay older than the rows
-    load(id0, const_int<0>{}, x[0]);
-    auto step = [&](uint32_t t, auto full) {
-        const float f1 = HASF ? a.f[id1] : 1.0f;
-        const uint32_t id2 = ids_of(t + 32);
-        static_for<0, 16 / kAhead>([&](auto qq) {
-            constexpr int Q = decltype(qq)::value;
-            if constexpr (Q + 1 < 16 / kAhead)
-                load(id0, const_int<(Q + 1) * kAhead>{}, x[(Q + 1) & 1]);
-            else
-                load(id1, const_int<0>{}, x[0]);
-            __builtin_amdgcn_sched_barrier(0); // the requests go out before the sums wait
-            consume(f0, const_int<Q * kAhead>{}, x[Q & 1], t, full);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        id0 = id1;
-        id1 = id2;
-        f0 = f1;
+    // Four rows of at most 4 or 8 neighbours request just those; the loop below asks for 24 (20)
+    // (54,198 nodes, 265 K non-zeros, int16 rows of 192 channels 36 us with the loop alone, 23 so).
+    auto short_rows = [&](auto count) {
+        const uint32_t id = ids_of(0);
+        const float fl = HASF ? a.f[id] : 1.0f;
+        piece x[decltype(count)::value];
+        load(id, const_int<0>{}, x);
+        consume(fl, const_int<0>{}, x, 0, std::false_type{});
     };
-    // First the blocks that are whole for all four teams.  No load stands behind a branch: the
-    // waits after it would have to be for every load in flight.
-    uint32_t t = 0;
-    for (; t + 16 <= dmin; t += 16)
-        step(t, std::true_type{});
-    for (; t < dmax; t += 16)
-        step(t, std::false_type{});
+    if (dmax <= 4) {
+        short_rows(const_int<4>{});
+    } else if (dmax <= 8) {
+        short_rows(const_int<8>{});
+    } else {
+        // The ids of a block of 16 neighbours are requested two blocks ahead, the factors one
+        // block ahead, the rows kAhead neighbours ahead.
+        uint32_t id0 = ids_of(0), id1 = ids_of(16);
+        float f0 = HASF ? a.f[id0] : 1.0f;
+        piece x[2][kAhead];
+        __builtin_amdgcn_sched_barrier(0); // ids and factors stay older than the rows
+        load(id0, const_int<0>{}, x[0]);
+        auto step = [&](uint32_t t, auto full) {
+            const float f1 = HASF ? a.f[id1] : 1.0f;
+            const uint32_t id2 = ids_of(t + 32);
+            static_for<0, 16 / kAhead>([&](auto qq) {
+                constexpr int Q = decltype(qq)::value;
+                if constexpr (Q + 1 < 16 / kAhead)
+                    load(id0, const_int<(Q + 1) * kAhead>{}, x[(Q + 1) & 1]);
+                else
+                    load(id1, const_int<0>{}, x[0]);
+                __builtin_amdgcn_sched_barrier(0); // the requests go out before the sums wait
+                consume(f0, const_int<Q * kAhead>{}, x[Q & 1], t, full);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            id0 = id1;
+            id1 = id2;
+            f0 = f1;
+        };
+        // First the blocks that are whole for all four teams.  No load stands behind a branch: the
+        // waits after it would have to be for every load in flight.
+        uint32_t t = 0;
+        for (; t + 16 <= dmin; t += 16)
+            step(t, std::true_type{});
+        for (; t < dmax; t += 16)
+            step(t, std::false_type{});
+    }
     const float ri = (a.r && has) ? a.r[i] : 1.0f;
     if (BITS_OUT) {
         // the lane's V bits at their nominal positions (channels past C fall off), OR-ed over

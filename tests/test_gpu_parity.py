@@ -537,6 +537,53 @@ def test_spmm_f32_long_rows(B, ctx, C):
     adj.close()
 
 
+def _check_row_lengths(B, ctx, lens, n, C, seed, kinds=("f32", "bits", "i16"), factors=(True, False),
+                       pad=0):
+    """bitgnn_spmm_f32 / _i16 on a graph whose first rows have the given lengths (the others
+    none), for every operand type, bit for bit against the step-rounded reference."""
+    r = np.random.default_rng(seed)
+    src = np.repeat(np.arange(len(lens)), lens).astype(np.int32)
+    dst = np.concatenate([np.sort(r.permutation(n)[:k]) for k in lens]).astype(np.int32)
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, 0)
+    rp, col = orc.adjacency(src, dst, n, 0)
+    f, rv = (r.uniform(-1.5, 1.5, n).astype(np.float32) for _ in range(2))
+    alpha = r.uniform(0.5, 1.5, C).astype(np.float32)
+    tau = r.uniform(-0.5, 0.5, C).astype(np.float32)
+    cw, ldz = (C + 63) // 64, C + pad
+    v, z = W.pm1(r, (n, C)), r.integers(-900, 901, size=(n, C)).astype(np.int16)
+    xf = r.standard_normal((n, C)).astype(np.float32)
+    out = torch.empty((n, C + 1), dtype=torch.float32, device="cuda")
+    ob = torch.empty((n, cw), dtype=torch.int64, device="cuda")
+    ops = {"f32": (xf, dev(np.pad(xf, ((0, 0), (0, pad)))), ldz),
+           "bits": (v.astype(np.float32), _pack_host(v), cw),
+           "i16": (orc.scale(z.astype(np.int64), alpha), dev(np.pad(z, ((0, 0), (0, pad)))), ldz)}
+    for has_f in factors:
+        fd = dev(f) if has_f else None
+        for kind in kinds:
+            x, xd, ldx = ops[kind]
+            want = orc.spmm_weighted_f32(rp, col, x, rv, f if has_f else None)
+            out.fill_(7.0)
+            for epi, t, o, ldo in ((B.EPI_SCALE_F32, None, out, C + 1),
+                                   (B.EPI_THRESH_BITS, dev(tau), ob, cw)):
+                if kind == "i16":
+                    B.spmm_i16(ctx, adj, xd, C, ldx, dev(alpha), dev(rv), fd, epi, t, o, ldo)
+                else:
+                    B.spmm_f32(ctx, adj, xd, kind == "bits", C, ldx, dev(rv), fd, epi, t, o, ldo)
+            torch.cuda.synchronize()
+            got = out.cpu().numpy()
+            # +0 and -0 compare equal here: an empty row times a negative factor
+            assert np.array_equal(got[:, :C], want) and np.all(got[:, C] == 7.0), (kind, has_f)
+            assert np.array_equal(words_np(ob), orc.to_words(orc.rebin_f32(want, tau))), (kind, has_f)
+    adj.close()
+
+
+@pytest.mark.parametrize("C", [7, 41, 64, 130, 300])
+def test_spmm_f32_short_rows(B, ctx, C):
+    """Rows around 4, 8 and 16 neighbours, where a wavefront's four teams request no more rows
+    than they need."""
+    _check_row_lengths(B, ctx, [k for k in range(20) for _ in range(9)], 211, C, 600 + C)
+
+
 def test_spmm_f32_beyond_the_teams_of_one_launch(B, ctx):
     """More than 2^28 teams of 16 lanes (33,000 rows x 8,192 windows of 128 channels), five
     launches.  Every row has one neighbour, so its bits are that neighbour's; one row in eight
