@@ -97,8 +97,8 @@ struct SpmmArgs {
     uint32_t hub_tiles;   // 64-channel tiles of a hub row
     uint32_t slot0, slot_end; // rows of the teams, in degree order
     uint32_t windows;      // channel windows of a row
-    uint32_t window_major; // order of the teams
-    uint32_t team_blocks;  // window_major: workgroups per window
+    uint32_t group;        // windows of a row that are taken side by side
+    uint32_t group_blocks; // workgroups per group of windows
 };
 
 // The sign a packed bit gives f: bit set -> +f, clear -> -f.  `inv` holds the inverted bit at
@@ -307,20 +307,15 @@ __device__ __forceinline__ void spmm_hub_row(const SpmmArgs &a, uint32_t slot, u
 template <int XKIND, bool BITS_OUT, bool HASF, int V, bool BIG, int kThreads>
 __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
 {
-    // window and row of this team: the windows of a row side by side (one instruction then
-    // covers adjacent pieces of a row), or one window of all rows after the other
-    const uint32_t team = tb * (kThreads / kTeam) + threadIdx.x / kTeam;
-    uint32_t window, team_row;
-    if (a.window_major) {
-        window = tb / a.team_blocks;
-        team_row = team - window * a.team_blocks * (kThreads / kTeam);
-    } else {
-        team_row = team / a.windows;
-        window = team - team_row * a.windows;
-    }
+    // window and row of this team: a group of windows of a row side by side (one instruction then
+    // covers adjacent pieces of a row), one group of all rows after the other
+    const uint32_t grp = tb / a.group_blocks;
+    const uint32_t team = (tb - grp * a.group_blocks) * (kThreads / kTeam) + threadIdx.x / kTeam;
+    const uint32_t team_row = team / a.group;
+    const uint32_t window = grp * a.group + (team - team_row * a.group);
     const uint32_t sub = threadIdx.x & 15;
     const uint32_t slot = a.slot0 + team_row;
-    const bool has = slot < a.slot_end;
+    const bool has = slot < a.slot_end && window < a.windows;
     const uint32_t i = has ? (uint32_t)a.order[slot] : 0u;
     const uint32_t beg = has ? a.rowptr[i] : 0u, deg = has ? a.rowptr[i + 1] - beg : 0u;
     // row lengths of the wavefront's four teams (scalar)
@@ -577,13 +572,25 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     // rows spread over all lanes of a team
     const int V = x_is_bits && !xscale ? (C <= 64 ? 4 : 8) : C <= 16 ? 1 : 4;
     a.windows = ((uint32_t)C + kTeam * V - 1) / (kTeam * V);
-    // One window of all rows after the other keeps a smaller table hot in L2; it pays when the
-    // windows are whole cache lines and nothing but the rows is gathered (300,001 nodes, 128
-    // floats: 683 us against 769; with factors, which are gathered once per window, it loses).
-    a.window_major = a.windows > 1 && !f && !x_is_bits && a.row_bytes % 128 == 0 &&
-                     bg_aligned(x, 128) &&
-                     (uint64_t)adj->n * (uint64_t)a.row_bytes > (8u << 20);
-    const bool big = (uint64_t)adj->n * (uint64_t)a.row_bytes >= (1ull << 32);
+    // All windows of a row side by side, with two exceptions.  Four windows (1 KB of a float row)
+    // of all rows after the other keep a smaller part of a table hot that is larger than an L2: it
+    // pays where rows are gathered often (32 times on average) and the gathers take several times
+    // as long as the longest row's walk, which is then paid once per group.  500 floats with
+    // factors: 4,643 nodes, 296 K non-zeros, longest row 90: 49 us side by side, 38 in fours; but
+    // 3,111 nodes, 305 K, longest row 536: 40 and 53.  500 int16 channels: 48,545 nodes, 9.1 M,
+    // 2,856: 907 and 823; but 8,911 nodes, 2.5 M, 1,442: 170 and 202.
+    // One window after the other pays when the windows are whole cache lines and nothing but the
+    // rows is gathered (300,001 nodes, 128 floats: 683 us against 769; with factors, which are
+    // gathered once per window, it loses).  Packed rows are short.
+    const uint64_t table = (uint64_t)adj->n * (uint64_t)a.row_bytes;
+    a.group = a.windows;
+    if (!x_is_bits && !f && a.row_bytes % 128 == 0 && bg_aligned(x, 128) && table > (8u << 20))
+        a.group = 1;
+    else if (!x_is_bits && a.windows > 4 && table > (4u << 20) && adj->nnz >= 32 * adj->n &&
+             adj->nnz * (int64_t)a.windows >= 16000 * adj->max_degree)
+        a.group = 4;
+    const uint32_t groups = (a.windows + a.group - 1) / a.group;
+    const bool big = table >= (1ull << 32);
     uint32_t threads, grid;
     auto launch = [&](auto xk, auto v) {
         constexpr int XK = decltype(xk)::value, VV = decltype(v)::value;
@@ -603,7 +610,7 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
         bits_out ? go3(std::true_type{}) : go3(std::false_type{});
     };
     // One launch, unless there are more than 2^26 teams.
-    const int64_t rows_max = (1ll << 26) / a.windows;
+    const int64_t rows_max = (1ll << 26) / (groups * a.group);
     bg_time_begin(ctx, s);
     for (int64_t slot = n_hub; slot == n_hub || slot < adj->n; slot += rows_max) {
         const int64_t rows = adj->n - slot < rows_max ? adj->n - slot : rows_max;
@@ -612,10 +619,8 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
         a.n_hub = slot == n_hub ? n_hub : 0; // the hub rows start first
         threads = a.n_hub ? kHubBlock : kSpBlock;
         const uint32_t teams = threads / kTeam; // of a workgroup
-        a.team_blocks = ((uint32_t)rows + teams - 1) / teams;
-        grid = a.n_hub * a.hub_tiles +
-               (a.window_major ? a.windows * a.team_blocks
-                               : ((uint32_t)rows * a.windows + teams - 1) / teams);
+        a.group_blocks = ((uint32_t)rows * a.group + teams - 1) / teams;
+        grid = a.n_hub * a.hub_tiles + groups * a.group_blocks;
         if (xscale) {
             if (V == 1)
                 launch(const_int<2>{}, const_int<1>{});

@@ -584,6 +584,19 @@ def test_spmm_f32_short_rows(B, ctx, C):
     _check_row_lengths(B, ctx, [k for k in range(20) for _ in range(9)], 211, C, 600 + C)
 
 
+@pytest.mark.parametrize("n,C,pad,lens,rest", [
+    # tables over 4 MiB, short longest rows: groups of four windows, a last group of 4, 3 and 1
+    (4301, 500, 0, [], 75), (4301, 700, 1, [], 75), (3001, 830, 0, [75], 70),
+    # over 8 MiB, rows of whole cache lines: without factors one window after the other
+    (17001, 128, 0, [700, 40], 9), (17011, 192, 64, [40], 9), (8497, 300, 84, [1500], 9)])
+def test_spmm_f32_window_groups(B, ctx, n, C, pad, lens, rest):
+    r = np.random.default_rng(n)
+    lens = lens + list(r.integers(0, rest, size=n - len(lens)))
+    if C >= 500:  # the rule's other two conditions
+        assert sum(lens) >= 32 * n and sum(lens) * ((C + 63) // 64) >= 16000 * max(lens)
+    _check_row_lengths(B, ctx, lens, n, C, n + 1, kinds=("f32", "i16"), pad=pad)
+
+
 def test_spmm_f32_beyond_the_teams_of_one_launch(B, ctx):
     """More than 2^28 teams of 16 lanes (33,000 rows x 8,192 windows of 128 channels), five
     launches.  Every row has one neighbour, so its bits are that neighbour's; one row in eight
