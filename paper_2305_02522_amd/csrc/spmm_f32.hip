@@ -16,12 +16,13 @@
 //    factors of 16 neighbours and hand them out with DPP row broadcasts, which the address
 //    add and the multiply take as an operand: no scalar work per neighbour.
 //  * hubs: the sum of a row has a fixed order, so its adds are a serial chain, and on a
-//    power-law graph the longest row's chain is longer than everything else together.  Rows
-//    of at least hub_deg neighbours get a workgroup per 64 channels in which seven wavefronts
-//    gather and multiply (that has no order) and leave the products in LDS, and one wavefront
-//    does nothing but read and add them.
+//    power-law graph the longest row's chain is longer than everything else together.  Hub
+//    rows get a workgroup per 64 channels in which seven wavefronts gather and multiply (that
+//    has no order) and leave the products in LDS, and one wavefront does nothing but read and
+//    add them.  choose_plan() prices which rows are hubs.
 #include "common.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace {
@@ -513,6 +514,84 @@ int bg_check_spmm_f32(bitgnn_ctx *ctx, const bitgnn_adj *adj, const void *x, int
     return BITGNN_OK;
 }
 
+namespace {
+
+uint32_t windows_of(int32_t C, int V) { return ((uint32_t)C + kTeam * V - 1) / (kTeam * V); }
+
+// What a launch without the fixed part of a call (about 5 us) is expected to take in
+// microseconds, with the rows of at least 2^k neighbours as hub rows (k < 0: none).  Two things
+// take time side by side: the longest row that a team walks, and everybody's gathers.  Fitted on
+// 181 graphs (R-MAT, Chung-Lu, block model; 2,000 to 370,000 nodes, mean degree 3 to 400), 3,200
+// operands of 7 to 500 channels, with each k forced in turn; the k chosen here is on average 2 %
+// slower than the best of them.
+double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large, int V, int k)
+{
+    // ns per neighbour of a row; per gather of a team; per row and window (order, row pointers,
+    // store; the thresholds of 8 channels per lane cost most).  `large`: x is larger than an L2.
+    double chain, gather, row;
+    if (V == 1)
+        chain = 18, gather = 0.0055, row = 0.08;
+    else if (xkind == 1)
+        chain = V == 8 ? 54 : 34, gather = V == 8 ? 0.006 : 0.005,
+        row = V == 8 && bits_out ? 0.2 : 0.09;
+    else if (xkind == 2)
+        chain = 42, gather = 0.0085, row = 0.14;
+    else
+        chain = large ? 65 : 35, gather = large ? 0.0085 : 0.014, row = 0.12;
+    const double windows = windows_of(C, V), nnz = (double)adj->nnz, n = (double)adj->n;
+    if (k < 0)
+        return std::hypot(chain * (double)adj->max_degree, windows * (nnz * gather + n * row)) * 1e-3;
+    // Non-zeros of the hub rows, from the counts (a row between two powers of two counts as their
+    // mean).  A hub workgroup takes 4 ns of the chip and 0.017 per neighbour, and its LDS and
+    // registers leave fewer wavefronts to the other rows.
+    double hub = 0;
+    for (int j = k; j < 31 && adj->n_ge[j]; ++j) {
+        const double lo = (double)(1u << j), hi = std::fmin(2 * lo, (double)adj->max_degree + 1);
+        hub += (double)(adj->n_ge[j] - adj->n_ge[j + 1]) * 0.5 * (lo + hi);
+    }
+    hub = std::fmin(hub, nnz);
+    const double rows = adj->n_ge[k], tiles = (double)((C + 63) / 64);
+    const double walk =
+        (xkind == 1 ? 1.0 : 1.2) * std::fmin((double)adj->max_degree, (double)(1u << k));
+    const double teams = windows * ((nnz - hub) * gather * 1.2 + (n - rows) * row * 1.5);
+    return std::hypot(chain * walk, teams + tiles * (rows * 4 + hub * 0.017)) * 1e-3 + 1.2;
+}
+
+struct Plan {
+    int V;          // channels per lane of a team
+    uint32_t n_hub; // hub rows
+    double us;      // team_us of the two
+};
+
+// Channels per lane: 16 bytes of a float row, 8 of an integer row; narrow rows spread over all
+// lanes of a team.  Packed rows take 4 or 8 bits per lane: 8 halve the gathers, 4 walk a row
+// faster (34 against 54 ns a neighbour) and store it faster, so both are priced.  Hub rows are
+// those of at least 2^k neighbours, k >= 7, for the k that is priced lowest; R-MAT graph of 8,192
+// nodes, 111 K non-zeros, longest row 1,526, packed rows of 100 channels with factors: 104 us
+// without hubs, 13 at 2^7; Chung-Lu graph of 22,106 nodes, 7.7 M, 2,538, 256 floats: 498 without,
+// 845 at 2^7, 563 at 2^10.
+Plan choose_plan(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large)
+{
+    Plan best{0, 0, 0};
+    const int Vs[2] = {xkind != 1 && C <= 16 ? 1 : 4, 8};
+    for (int q = 0; q < (xkind == 1 && C > 64 ? 2 : 1); ++q)
+        for (int k = 6; k < 31; ++k) {
+            const int kk = k == 6 ? -1 : k; // 6: no hubs
+            const uint32_t n_hub = kk < 0 ? 0 : adj->n_ge[kk];
+            // (no hubs left; or more workgroups than a launch takes: fewer than 2^32 threads)
+            if (kk >= 0 && n_hub == 0)
+                break;
+            if ((uint64_t)n_hub * (((uint32_t)C + 63) / 64) * kHubBlock > 1u << 30)
+                continue;
+            const double us = team_us(adj, xkind, C, bits_out, large, Vs[q], kk);
+            if (best.V == 0 || us < best.us)
+                best = Plan{Vs[q], n_hub, us};
+        }
+    return best;
+}
+
+} // namespace
+
 // `xscale` non-null: x holds int16 rows (ldx in int16 units) and a value is
 // xscale[c] * (float)x; otherwise x_is_bits selects packed +-1 or float rows.
 int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const void *x,
@@ -548,30 +627,13 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     a.tau = tau;
     a.out = out;
     a.ldo = ldo;
-    // Hub rows: those whose serial walk by a team (45-65 ns a neighbour) would last a good part
-    // of the launch, at least 2^9 neighbours, 2^11 with bit rows, whose team form takes fewer
-    // instructions per neighbour than the hub form.  Measured on an R-MAT graph (131,072 nodes,
-    // 3.86 M non-zeros, longest row 15,635) for thresholds 2^8 .. 2^12: int16 rows of 40
-    // channels 101 92 126 122 267 us (1,027 without hubs), float rows of 64 106 102 136 134 295
-    // (1,059), bit rows of 256 273 208 208 176 285 (1,188).
-    int k = x_is_bits && !xscale ? 11 : 9;
-    // They take wavefronts from the other rows and gather more slowly than teams do, so they are
-    // used only where the longest row's walk by a team would last more than half of the gathers
-    // (about 70 G cache lines a second).  232,965 nodes, 110.6 M non-zeros, longest row 9,735,
-    // int16 rows of 41 channels: 1,675 us without hubs, 2,063 with; 300,001 nodes, 14.7 M
-    // non-zeros, longest row 3,676, float rows of 64 channels: 397 without, 353 with.
-    const int64_t lines = ((int64_t)C * (xscale ? 16 : x_is_bits ? 1 : 32) + 1023) / 1024;
     a.hub_tiles = ((uint32_t)C + 63) / 64;
-    uint32_t n_hub = 2.0 * 65.0 * (double)adj->max_degree > (double)adj->nnz * (double)lines / 70.0
-                         ? adj->n_ge[k]
-                         : 0;
-    // (a launch takes fewer than 2^32 threads)
-    if ((uint64_t)n_hub * a.hub_tiles * kHubBlock > 1u << 30)
-        n_hub = 0;
-    // channels per lane: 16 bytes of a float row, 8 of an integer row, 4 or 8 bits; narrow
-    // rows spread over all lanes of a team
-    const int V = x_is_bits && !xscale ? (C <= 64 ? 4 : 8) : C <= 16 ? 1 : 4;
-    a.windows = ((uint32_t)C + kTeam * V - 1) / (kTeam * V);
+    const uint64_t table = (uint64_t)adj->n * (uint64_t)a.row_bytes;
+    const bool large = table > (4u << 20); // than an L2
+    const Plan plan = choose_plan(adj, xscale ? 2 : x_is_bits ? 1 : 0, C, bits_out, large);
+    const uint32_t n_hub = plan.n_hub;
+    const int V = plan.V;
+    a.windows = windows_of(C, V);
     // All windows of a row side by side, with two exceptions.  Four windows (1 KB of a float row)
     // of all rows after the other keep a smaller part of a table hot that is larger than an L2: it
     // pays where rows are gathered often (32 times on average) and the gathers take several times
@@ -582,11 +644,10 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     // One window after the other pays when the windows are whole cache lines and nothing but the
     // rows is gathered (300,001 nodes, 128 floats: 683 us against 769; with factors, which are
     // gathered once per window, it loses).  Packed rows are short.
-    const uint64_t table = (uint64_t)adj->n * (uint64_t)a.row_bytes;
     a.group = a.windows;
     if (!x_is_bits && !f && a.row_bytes % 128 == 0 && bg_aligned(x, 128) && table > (8u << 20))
         a.group = 1;
-    else if (!x_is_bits && a.windows > 4 && table > (4u << 20) && adj->nnz >= 32 * adj->n &&
+    else if (!x_is_bits && a.windows > 4 && large && adj->nnz >= 32 * adj->n &&
              adj->nnz * (int64_t)a.windows >= 16000 * adj->max_degree)
         a.group = 4;
     const uint32_t groups = (a.windows + a.group - 1) / a.group;

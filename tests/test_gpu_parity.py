@@ -597,6 +597,21 @@ def test_spmm_f32_window_groups(B, ctx, n, C, pad, lens, rest):
     _check_row_lengths(B, ctx, lens, n, C, n + 1, kinds=("f32", "i16"), pad=pad)
 
 
+@pytest.mark.parametrize("C", [9, 41, 64, 100, 130, 300])
+def test_spmm_f32_hub_rows_from_128(B, ctx, C):
+    """One long row on a small graph: every row of 128 neighbours and more is a hub (112
+    neighbours a stage, stages in fours)."""
+    lens = [2600, 111, 112, 113, 127, 128, 129, 255, 256, 257, 447, 448, 449, 895, 896, 897, 1, 0]
+    _check_row_lengths(B, ctx, lens, 2600, C, 700 + C)
+
+
+@pytest.mark.parametrize("C", [65, 128, 200, 260])
+def test_spmm_f32_bits_eight_channels_a_lane(B, ctx, C):
+    """Packed rows with factors where the gathers outlast the longest row's walk."""
+    lens = list(np.random.default_rng(5).integers(90, 150, size=6000))
+    _check_row_lengths(B, ctx, lens, 6000, C, 800 + C, kinds=("bits",), factors=(True,))
+
+
 def test_spmm_f32_beyond_the_teams_of_one_launch(B, ctx):
     """More than 2^28 teams of 16 lanes (33,000 rows x 8,192 windows of 128 channels), five
     launches.  Every row has one neighbour, so its bits are that neighbour's; one row in eight
