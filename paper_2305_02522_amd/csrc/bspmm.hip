@@ -27,6 +27,8 @@
 // lanes of a wavefront have similar trip counts.
 #include "common.h"
 
+#include <cmath>
+
 namespace {
 
 constexpr int kBlock = 256;
@@ -1660,6 +1662,15 @@ size_t bg_adj_workspace_bytes(const bitgnn_adj *adj, int32_t C, int32_t M)
     return need;
 }
 
+// What bounds the blocked kernel in a pass of 128 channels, in microseconds.
+static double blocked_pass_us(const bitgnn_blocked *b)
+{
+    const double stream = (double)b->n_groups * 64 * kGroupSteps / 1.3e6;
+    const double rounds = (double)((b->n_wgs + 255) / 256);
+    const double walk = rounds * (double)b->ncb * 3.0;
+    return stream > walk ? stream : walk;
+}
+
 // Rough time models (microseconds, fitted on MI355X) of the two aggregation paths.  The
 // CSR kernel is bound by its gather traffic or by the serial walk of the longest row;
 // the blocked kernel by its id stream or, on small graphs, by the chain of LDS refills a
@@ -1677,31 +1688,52 @@ bool bg_prefer_blocked(const bitgnn_adj *adj, int passes, int64_t bytes_per_nnz,
     const double csr_traffic = (double)adj->nnz * (8.0 + 0.12 * (double)bytes_per_nnz) / 1e6;
     const double csr_chain = (double)longest_chain * chain_us_per_nnz;
     const double csr = (csr_traffic > csr_chain ? csr_traffic : csr_chain) + 10.0;
-    const double stream = (double)b->n_groups * 64 * kGroupSteps / 1.3e6;
-    const double rounds = (double)((b->n_wgs + 255) / 256);
-    const double walk = rounds * (double)b->ncb * 3.0;
-    const double blk = passes * ((stream > walk ? stream : walk) + 30.0);
+    const double blk = passes * (blocked_pass_us(b) + 30.0);
     return blk < csr;
 }
 
-// force: 0 = choose (a measured preference of bitgnn_adj_tune first, else the time model),
-// 1 = CSR kernel, 2 = column-blocked kernel (the caller has checked that the form exists)
+// Which form a bit aggregation of C channels takes: a measured preference of bitgnn_adj_tune
+// first, else the time model.
+static bool takes_blocked(const bitgnn_adj *adj, int32_t C)
+{
+    const int passes = (C + 127) / 128;
+    if (adj->blk && !adj->blk->forced && adj->pref[passes < 4 ? passes - 1 : 3])
+        return adj->pref[passes < 4 ? passes - 1 : 3] == 2;
+    return bg_prefer_blocked(adj, passes, 4 * (int64_t)((C + 31) / 32), 0.06,
+                             adj->max_degree < (int64_t)adj->seg_len ? adj->max_degree
+                                                                     : (int64_t)adj->seg_len);
+}
+
+// What bg_launch_bspmm_scaled is expected to take in microseconds, without the fixed part of a
+// call (about 5 us).  Fitted on 202 graphs (R-MAT, Chung-Lu, block model; 2,000 to 700,000 nodes,
+// mean degree 3 to 400) with 7 to 700 channels: CSR within 19 % (rms), blocked within 13 %.
+double bg_bspmm_scaled_us(const bitgnn_adj *adj, int32_t C, bool bits_out)
+{
+    const double W32 = (C + 31) / 32, n = (double)adj->n, nnz = (double)adj->nnz;
+    if (takes_blocked(adj, C))
+        return (C + 127) / 128 * (28.0 + 0.57 * blocked_pass_us(adj->blk) + n * 0.13e-3) +
+               n * W32 * (bits_out ? 0.032e-3 : 0.056e-3) - 5.0;
+    const bool large = adj->seg_len > kSegLenSmall;
+    const double longest = (double)(adj->max_degree < (int64_t)adj->seg_len
+                                        ? adj->max_degree
+                                        : (int64_t)adj->seg_len);
+    double us = 2.0 + std::hypot(nnz * (6.5e-3 + 0.33e-3 * W32), (large ? 127 : 49) * longest) * 1e-3 +
+                n * W32 * (bits_out ? 0.007e-3 : 0.032e-3);
+    if (adj->n_long)
+        us += 9.5 + (double)adj->n_long_segs * adj->seg_len * W32 * 0.7e-6;
+    if (adj->col_slot)
+        us += n * W32 * 0.011e-3 + (adj->n_long ? 6.5 : 0.0);
+    return us;
+}
+
+// force: 0 = choose, 1 = CSR kernel, 2 = column-blocked kernel (the caller has checked that the
+// form exists)
 static int launch_bspmm_path(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
                              const uint64_t *hbits, int32_t C, int64_t h_stride, int epilogue,
                              const int32_t *T, void *out, int64_t out_stride, int force,
                              const ScaledEpi &se = ScaledEpi{})
 {
-    const int passes = (C + 127) / 128;
-    bool blocked;
-    if (force)
-        blocked = force == 2;
-    else if (adj->blk && !adj->blk->forced && adj->pref[passes < 4 ? passes - 1 : 3])
-        blocked = adj->pref[passes < 4 ? passes - 1 : 3] == 2;
-    else
-        blocked = bg_prefer_blocked(adj, passes, 4 * (int64_t)((C + 31) / 32), 0.06,
-                                    adj->max_degree < (int64_t)adj->seg_len
-                                        ? adj->max_degree
-                                        : (int64_t)adj->seg_len);
+    const bool blocked = force ? force == 2 : takes_blocked(adj, C);
     if (blocked)
         return launch_bspmm_blocked(ctx, s, adj, hbits, C, h_stride, epilogue, T, out, out_stride,
                                     se);

@@ -207,6 +207,7 @@ int bg_launch_bspmm(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const
 int bg_launch_bspmm_scaled(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
                            const uint64_t *hbits, int32_t C, int64_t h_stride, const float *r,
                            const float *tau, void *out, int64_t out_stride);
+double bg_bspmm_scaled_us(const bitgnn_adj *adj, int32_t C, bool bits_out);
 int bg_launch_spmm_i32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const int32_t *Z,
                        int32_t M, int64_t z_stride, const float *alpha, void *out,
                        int64_t out_stride);

@@ -602,18 +602,6 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     if (adj->n == 0)
         return BITGNN_OK;
     const bool bits_out = epilogue == BITGNN_EPI_THRESH_BITS;
-    // +-1 rows without factors: the float sum of a row is its integer sum, exact while partial
-    // sums stay below 2^24, so the bit aggregation's counters give it (89,250 nodes, 877 K
-    // non-zeros, 500 channels: 108 -> 41 us).  It needs the workspace; without it the floats
-    // are added here, and so they are on small graphs, where the bit aggregation's fixed cost
-    // (17-30 us with its long-row and merge launches) is what counts: 2,839 nodes, 260 K
-    // non-zeros, 64 channels 26 against 9 us, 512 channels 20 against 20; 20,000 nodes, 598 K
-    // non-zeros, 64 channels 13 against 9, 128 channels 10 against 14.
-    if (x_is_bits && !xscale && !f && C <= 2048 && adj->max_degree < (1ll << 24) &&
-        adj->nnz * (int64_t)C >= 48000000 &&
-        bg_adj_workspace_bytes(adj, C, 1) <= ctx->sc->ws_bytes)
-        return bg_launch_bspmm_scaled(ctx, s, adj, (const uint64_t *)x, C, ldx, r,
-                                      bits_out ? tau : nullptr, out, ldo);
     SpmmArgs a;
     a.rowptr = adj->rowptr;
     a.col = adj->col;
@@ -631,6 +619,18 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     const uint64_t table = (uint64_t)adj->n * (uint64_t)a.row_bytes;
     const bool large = table > (4u << 20); // than an L2
     const Plan plan = choose_plan(adj, xscale ? 2 : x_is_bits ? 1 : 0, C, bits_out, large);
+    // +-1 rows without factors: the float sum of a row is its integer sum, exact while partial
+    // sums stay below 2^24, so the bit aggregation's counters give it.  It needs the workspace
+    // (without it the floats are added here) and is taken where it is priced lower; which is
+    // better has no simple line: 23,507 nodes, 2.2 M non-zeros, 256 channels to bits 19 us against
+    // 45 added as floats, 8,920 nodes, 788 K, 64 channels 23 against 10.  On 958 operands the
+    // choice costs 1.5 % more than always knowing the faster one.
+    if (x_is_bits && !xscale && !f && C <= 2048 && adj->max_degree < (1ll << 24) &&
+        adj->n * (int64_t)((C + 31) / 32) < (1ll << 31) &&
+        bg_adj_workspace_bytes(adj, C, 1) <= ctx->sc->ws_bytes &&
+        bg_bspmm_scaled_us(adj, C, bits_out) < plan.us)
+        return bg_launch_bspmm_scaled(ctx, s, adj, (const uint64_t *)x, C, ldx, r,
+                                      bits_out ? tau : nullptr, out, ldo);
     const uint32_t n_hub = plan.n_hub;
     const int V = plan.V;
     a.windows = windows_of(C, V);

@@ -642,8 +642,8 @@ def test_spmm_f32_beyond_the_teams_of_one_launch(B, ctx):
 
 @pytest.mark.parametrize("C", [31, 64, 300])
 def test_spmm_f32_bits_without_factors(B, ctx, tuned, C):
-    """+-1 rows without factors go through the bit aggregation (both formats), or, on a context
-    whose workspace is too small for that, through the float sums: the same values."""
+    """+-1 rows without factors on graphs where adding the floats is priced lower, whatever the
+    formats and the workspace (test_spmm_f32_bits_through_the_counters has the others)."""
     n = 900
     adj, rp, col, r = _graph(B, ctx, n, 30000, W.ADJ_SYMMETRIZE, 70 + C, 2)
     B.ctx_reserve(ctx, B.adj_workspace_bytes(ctx, adj, C, 1))
@@ -670,6 +670,82 @@ def test_spmm_f32_bits_without_factors(B, ctx, tuned, C):
             assert np.all(gb[:, cw] == np.uint64(0xFFFFFFFFFFFFFFFF))
     small.close()
     adj.close()
+
+
+def _kernels_of(call):
+    """Names of the kernels that a call launches."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages()]
+
+
+@pytest.mark.parametrize("tuning,form,n,mean,power,C", [
+    ("csr-only", "bspmm_long_rows_kernel", 9001, 280, True, 97),  # a last word of one channel
+    ("csr-only", "bspmm_long_rows_kernel", 9001, 280, True, 256),
+    ("csr-only", "bspmm_long_rows_kernel", 20011, 200, True, 289),  # 14 bits of counter
+    ("csr-only", "bspmm_kernel", 23001, 80, False, 289),            # no row of several segments
+    ("csr-only", "csr_permute_kernel", 70001, 40, False, 130),      # a degree-ordered copy
+    ("default", "bspmm", 9001, 280, True, 130),                     # an odd number of words
+    ("blocked-largest-block", "bspmm_merge_kernel", 9001, 280, True, 97),
+    ("blocked-largest-block", "bspmm_merge_kernel", 9001, 280, True, 256),  # two passes
+    ("blocked-largest-block", "bspmm_merge_kernel", 20011, 200, True, 289),
+    ("blocked-largest-block", "bspmm_merge_kernel", 12001, 500, False, 64)])
+def test_spmm_f32_bits_through_the_counters(B, n, mean, power, C, tuning, form):
+    """+-1 rows without factors where the bit aggregation's counters are priced lower than adding
+    floats: the values of the float sums, in both formats, stored as floats and as bits, with and
+    without the row factor.  A context whose workspace is too small adds the floats."""
+    r = np.random.default_rng(n + C)
+    if power:
+        w = (np.arange(n) + 10.0) ** -0.75
+        lens = np.minimum(w / w.sum() * mean * n, n * 0.55).astype(np.int64)
+    else:
+        lens = r.integers(mean // 2, mean + mean // 2, size=n)
+    lens[-9:] = 0
+    lens = r.permutation(lens)
+    src = np.repeat(np.arange(n), lens).astype(np.int32)
+    dst = r.integers(0, n, size=len(src), dtype=np.int32)
+    big, small = B.Context(0), B.Context(0)
+    for c in (big, small):
+        B.ctx_set_tuning(c, *TUNINGS[tuning])
+    adj = B.adj_build(big, dev(src), dev(dst), len(src), n, 0)
+    rp, col = orc.adjacency(src, dst, n, 0)
+    need = B.adj_workspace_bytes(big, adj, C, 1)
+    B.ctx_reserve(big, need)
+    v = W.pm1(r, (n, C))
+    hb, rv = _pack_host(v), r.uniform(-1.0, 1.0, n).astype(np.float32)
+    tau = r.uniform(-0.5, 0.5, C).astype(np.float32)
+    cw = (C + 63) // 64
+    sums = orc.spmm_pm1(rp, col, v).astype(np.float32)     # exact: below 2^24
+    for rr in (rv, None):
+        want = sums if rr is None else rr[:, None] * sums
+        rd = None if rr is None else dev(rr)
+        for c in (big, small):
+            out = torch.full((n, C + 1), 7.0, dtype=torch.float32, device="cuda")
+            ob = torch.full((n, cw + 1), -1, dtype=torch.int64, device="cuda")
+
+            def floats():
+                B.spmm_f32(c, adj, hb, True, C, cw, rd, None, B.EPI_SCALE_F32, None, out, C + 1)
+
+            def bits():
+                B.spmm_f32(c, adj, hb, True, C, cw, rd, None, B.EPI_THRESH_BITS, dev(tau), ob,
+                           cw + 1)
+
+            for call in (floats, bits):
+                names = _kernels_of(call) if rr is None else call()
+                if rr is None:
+                    through = any("bspmm" in k for k in names)
+                    # (plain CSR without long rows works without scratch)
+                    assert through == (c is big or need == 0) and any("spmm" in k for k in names), names
+                    assert not through or any(form in k for k in names), names
+            torch.cuda.synchronize()
+            got, gb = out.cpu().numpy(), words_np(ob)
+            assert np.array_equal(got[:, :C], want) and np.all(got[:, C] == 7.0)
+            assert np.array_equal(gb[:, :cw], orc.to_words(orc.rebin_f32(want, tau)))
+            assert np.all(gb[:, cw] == np.uint64(0xFFFFFFFFFFFFFFFF))
+    small.close()
+    adj.close()
+    big.close()
 
 
 def test_spmm_f32_rejects_bad_arguments(B, ctx):
