@@ -634,22 +634,27 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     const uint32_t n_hub = plan.n_hub;
     const int V = plan.V;
     a.windows = windows_of(C, V);
-    // All windows of a row side by side, with two exceptions.  Four windows (1 KB of a float row)
-    // of all rows after the other keep a smaller part of a table hot that is larger than an L2: it
-    // pays where rows are gathered often (32 times on average) and the gathers take several times
-    // as long as the longest row's walk, which is then paid once per group.  500 floats with
-    // factors: 4,643 nodes, 296 K non-zeros, longest row 90: 49 us side by side, 38 in fours; but
-    // 3,111 nodes, 305 K, longest row 536: 40 and 53.  500 int16 channels: 48,545 nodes, 9.1 M,
-    // 2,856: 907 and 823; but 8,911 nodes, 2.5 M, 1,442: 170 and 202.
-    // One window after the other pays when the windows are whole cache lines and nothing but the
-    // rows is gathered (300,001 nodes, 128 floats: 683 us against 769; with factors, which are
-    // gathered once per window, it loses).  Packed rows are short.
+    // All windows of a row side by side; two other orders keep a smaller part of the table hot
+    // where it is larger than an L2 and its rows are gathered often (24 times on average).
+    //  * Four windows (1 KB of a float row) of all rows after the other, where the gathers take
+    //    several times as long as the longest row's walk, which is then paid once per group.
+    //    500 floats with factors: 4,643 nodes, 296 K non-zeros, longest row 90: 49 us side by
+    //    side, 38 in fours; but 3,111 nodes, 305 K, longest row 536: 40 and 53.  500 int16
+    //    channels: 48,545 nodes, 9.1 M, 2,856: 907 and 823; but 8,911 nodes, 2.5 M, 1,442: 170
+    //    and 202.
+    //  * One window after the other, where the windows are whole cache lines and nothing but the
+    //    rows is gathered (300,001 nodes, 14.7 M non-zeros, 128 floats: 769 and 683 us; with
+    //    factors, which are gathered once per window, it loses; of 256 floats at a mean degree
+    //    below 10 it takes 1.1, of 192 1.2 times the time).
+    // Packed rows are short.
     a.group = a.windows;
-    if (!x_is_bits && !f && a.row_bytes % 128 == 0 && bg_aligned(x, 128) && table > (8u << 20))
-        a.group = 1;
-    else if (!x_is_bits && a.windows > 4 && large && adj->nnz >= 32 * adj->n &&
-             adj->nnz * (int64_t)a.windows >= 16000 * adj->max_degree)
-        a.group = 4;
+    if (!x_is_bits && adj->nnz >= 24 * adj->n) {
+        if (!f && a.row_bytes % 128 == 0 && bg_aligned(x, 128) && table > (8u << 20))
+            a.group = 1;
+        else if (large && a.windows > 4 &&
+                 adj->nnz * (int64_t)a.windows >= 16000 * adj->max_degree)
+            a.group = 4;
+    }
     const uint32_t groups = (a.windows + a.group - 1) / a.group;
     const bool big = table >= (1ull << 32);
     uint32_t threads, grid;

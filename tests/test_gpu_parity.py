@@ -588,12 +588,12 @@ def test_spmm_f32_short_rows(B, ctx, C):
     # tables over 4 MiB, short longest rows: groups of four windows, a last group of 4, 3 and 1
     (4301, 500, 0, [], 75), (4301, 700, 1, [], 75), (3001, 830, 0, [75], 70),
     # over 8 MiB, rows of whole cache lines: without factors one window after the other
-    (17001, 128, 0, [700, 40], 9), (17011, 192, 64, [40], 9), (8497, 300, 84, [1500], 9)])
+    (17001, 128, 0, [700, 40], 75), (17011, 192, 64, [40], 75), (8497, 300, 84, [1500], 75)])
 def test_spmm_f32_window_groups(B, ctx, n, C, pad, lens, rest):
     r = np.random.default_rng(n)
     lens = lens + list(r.integers(0, rest, size=n - len(lens)))
-    if C >= 500:  # the rule's other two conditions
-        assert sum(lens) >= 32 * n and sum(lens) * ((C + 63) // 64) >= 16000 * max(lens)
+    assert sum(lens) >= 24 * n  # the rule's other conditions
+    assert C < 500 or sum(lens) * ((C + 63) // 64) >= 16000 * max(lens)
     _check_row_lengths(B, ctx, lens, n, C, n + 1, kinds=("f32", "i16"), pad=pad)
 
 
