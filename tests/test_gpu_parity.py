@@ -158,6 +158,24 @@ def test_adj_build_matches_set_definition(B, ctx, n, e, flags, seed):
     adj.close()
 
 
+# Edges of the sort: whole and broken tiles of keys, histograms around the sizes at which the scan
+# takes another level; degrees from few bits and from more than two passes' worth.
+@pytest.mark.parametrize("n,e", [(1 << 8, 2047), (255, 2048), (257, 2049), (3, 8193),
+                                 (70000, 128 * 2048), (70000, 128 * 2048 + 1),
+                                 (1 << 16, (1 << 20) - 1), (65537, 1 << 20), (999, (1 << 20) + 1)])
+def test_adj_build_sort_edges(B, ctx, n, e):
+    r = np.random.default_rng(e)
+    src, dst = W.random_graph(r, n, e)
+    src[: min(e, 2 * n) // 2] = n - 1  # one long row, repeated keys in the small graphs
+    adj = B.adj_build(ctx, dev(src), dev(dst), e, n, 0)
+    rp_ref, col_ref = orc.adjacency(src, dst, n, 0)
+    rp, col, deg = _csr_from_gpu(B, adj)
+    assert np.array_equal(rp, rp_ref) and np.array_equal(col, col_ref)
+    assert np.array_equal(deg, orc.degrees(rp_ref))
+    assert adj.max_degree == orc.degrees(rp_ref).max()
+    adj.close()
+
+
 def test_tuning_validation(B, ctx):
     for bad in ((63, 512, 32), (10209, 512, 32), (8192, 3, 32), (8192, 1024, 32), (8192, 512, -1)):
         with pytest.raises(B.BitgnnError) as e:
@@ -610,6 +628,52 @@ def test_spmm_f32_bits_eight_channels_a_lane(B, ctx, C):
     """Packed rows with factors where the gathers outlast the longest row's walk."""
     lens = list(np.random.default_rng(5).integers(90, 150, size=6000))
     _check_row_lengths(B, ctx, lens, 6000, C, 800 + C, kinds=("bits",), factors=(True,))
+
+
+@pytest.mark.parametrize("lens", [[2000, 600, 130, 17, 1], [8, 5, 30]])
+@pytest.mark.parametrize("C", [9, 70])
+def test_spmm_f32_rows_over_4_gib(B, ctx, C, lens):
+    """Rows 1 MiB apart, 4.1 GiB in all: row offsets of 64 bits, with hub rows and without."""
+    n, stride = 4200, 1 << 20
+    if torch.cuda.mem_get_info()[0] < 3 * n * stride:
+        pytest.skip("needs 13 GB of free device memory")
+    r = np.random.default_rng(C + len(lens))
+    lens = lens + list(r.integers(0, 7, size=n - len(lens)))
+    src = np.repeat(np.arange(n), lens).astype(np.int32)
+    dst = r.integers(0, n, size=len(src), dtype=np.int32)
+    dst[: n // 2] |= 2048                                   # many rows past the first 2 GiB
+    dst %= n
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, 0)
+    rp, col = orc.adjacency(src, dst, n, 0)
+    f, rv = (r.uniform(-1.5, 1.5, n).astype(np.float32) for _ in range(2))
+    alpha, tau = r.uniform(0.5, 1.5, C).astype(np.float32), r.uniform(-0.5, 0.5, C).astype(np.float32)
+    v, z = W.pm1(r, (n, C)), r.integers(-900, 901, size=(n, C)).astype(np.int16)
+    xf, cw = r.standard_normal((n, C)).astype(np.float32), (C + 63) // 64
+    out = torch.empty((n, C), dtype=torch.float32, device="cuda")
+    ob = torch.empty((n, cw), dtype=torch.int64, device="cuda")
+    buf = torch.zeros(n * stride, dtype=torch.uint8, device="cuda")
+    for kind, x, raw, dtype in (("f32", xf, xf, torch.float32),
+                                ("bits", v.astype(np.float32), _pack_host(v), torch.int64),
+                                ("i16", orc.scale(z.astype(np.int64), alpha), z, torch.int16)):
+        xd = buf.view(dtype).view(n, -1)
+        raw = raw if torch.is_tensor(raw) else dev(raw)
+        xd[:, :raw.shape[1]] = raw
+        ld = xd.shape[1]
+        for fv in (f, None):
+            fd = None if fv is None else dev(fv)
+            want = orc.spmm_weighted_f32(rp, col, x, rv, fv)
+            for epi, t, o, ldo in ((B.EPI_SCALE_F32, None, out, C),
+                                   (B.EPI_THRESH_BITS, dev(tau), ob, cw)):
+                if kind == "i16":
+                    B.spmm_i16(ctx, adj, xd, C, ld, dev(alpha), dev(rv), fd, epi, t, o, ldo)
+                else:
+                    B.spmm_f32(ctx, adj, xd, kind == "bits", C, ld, dev(rv), fd, epi, t, o, ldo)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want), (kind, fv is None)
+            assert np.array_equal(words_np(ob), orc.to_words(orc.rebin_f32(want, tau))), kind
+    adj.close()
+    del buf, xd
+    torch.cuda.empty_cache()
 
 
 def test_spmm_f32_beyond_the_teams_of_one_launch(B, ctx):
