@@ -68,7 +68,8 @@ __global__ __launch_bounds__(kAddBlock) void add4_kernel(const void *__restrict_
     const int64_t q0 = wave * (4 * turns); // first tile of this wavefront
     if (q0 >= total)
         return;
-    // four tiles a turn, one per 16 lanes; wave-uniform first row, the tiles' rows follow in 32 bits
+    // four tiles a turn, one per 16 lanes; the first row is wave-uniform, the tiles' rows follow in
+    // 32 bits
     const int64_t rowb = q0 / tiles;
     const uint32_t offb = (uint32_t)(q0 - rowb * tiles) + (uint32_t)grp;
     uint32_t drow = offb / (uint32_t)tiles;

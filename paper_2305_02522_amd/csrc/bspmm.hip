@@ -1717,7 +1717,8 @@ double bg_bspmm_scaled_us(const bitgnn_adj *adj, int32_t C, bool bits_out)
     const double longest = (double)(adj->max_degree < (int64_t)adj->seg_len
                                         ? adj->max_degree
                                         : (int64_t)adj->seg_len);
-    double us = 2.0 + std::hypot(nnz * (6.5e-3 + 0.33e-3 * W32), (large ? 127 : 49) * longest) * 1e-3 +
+    const double walk = (large ? 127 : 49) * longest;
+    double us = 2.0 + std::hypot(nnz * (6.5e-3 + 0.33e-3 * W32), walk) * 1e-3 +
                 n * W32 * (bits_out ? 0.007e-3 : 0.032e-3);
     if (adj->n_long)
         us += 9.5 + (double)adj->n_long_segs * adj->seg_len * W32 * 0.7e-6;

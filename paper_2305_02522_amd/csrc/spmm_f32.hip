@@ -522,9 +522,10 @@ uint32_t windows_of(int32_t C, int V) { return ((uint32_t)C + kTeam * V - 1) / (
 // microseconds, with the rows of at least 2^k neighbours as hub rows (k < 0: none).  Two things
 // take time side by side: the longest row that a team walks, and everybody's gathers.  Fitted on
 // 181 graphs (R-MAT, Chung-Lu, block model; 2,000 to 370,000 nodes, mean degree 3 to 400), 3,200
-// operands of 7 to 500 channels, with each k forced in turn; the k chosen here is on average 2 %
+// operands of 7 to 500 channels, each k timed in turn; the k chosen here is on average 1 to 2 %
 // slower than the best of them.
-double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large, int V, int k)
+double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large, int V,
+               int k)
 {
     // ns per neighbour of a row; per gather of a team; per row and window (order, row pointers,
     // store; the thresholds of 8 channels per lane cost most).  `large`: x is larger than an L2.
@@ -540,7 +541,8 @@ double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool 
         chain = large ? 65 : 35, gather = large ? 0.0085 : 0.014, row = 0.12;
     const double windows = windows_of(C, V), nnz = (double)adj->nnz, n = (double)adj->n;
     if (k < 0)
-        return std::hypot(chain * (double)adj->max_degree, windows * (nnz * gather + n * row)) * 1e-3;
+        return std::hypot(chain * (double)adj->max_degree,
+                          windows * (nnz * gather + n * row)) * 1e-3;
     // Non-zeros of the hub rows, from the counts (a row between two powers of two counts as their
     // mean).  A hub workgroup takes 4 ns of the chip and 0.017 per neighbour, and its LDS and
     // registers leave fewer wavefronts to the other rows.

@@ -555,8 +555,8 @@ def test_spmm_f32_long_rows(B, ctx, C):
     adj.close()
 
 
-def _check_row_lengths(B, ctx, lens, n, C, seed, kinds=("f32", "bits", "i16"), factors=(True, False),
-                       pad=0):
+def _check_row_lengths(B, ctx, lens, n, C, seed, kinds=("f32", "bits", "i16"),
+                       factors=(True, False), pad=0):
     """bitgnn_spmm_f32 / _i16 on a graph whose first rows have the given lengths (the others
     none), for every operand type, bit for bit against the step-rounded reference."""
     r = np.random.default_rng(seed)
@@ -591,7 +591,7 @@ def _check_row_lengths(B, ctx, lens, n, C, seed, kinds=("f32", "bits", "i16"), f
             got = out.cpu().numpy()
             # +0 and -0 compare equal here: an empty row times a negative factor
             assert np.array_equal(got[:, :C], want) and np.all(got[:, C] == 7.0), (kind, has_f)
-            assert np.array_equal(words_np(ob), orc.to_words(orc.rebin_f32(want, tau))), (kind, has_f)
+            assert np.array_equal(words_np(ob), orc.to_words(orc.rebin_f32(want, tau))), kind
     adj.close()
 
 
@@ -646,7 +646,7 @@ def test_spmm_f32_rows_over_4_gib(B, ctx, C, lens):
     adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, 0)
     rp, col = orc.adjacency(src, dst, n, 0)
     f, rv = (r.uniform(-1.5, 1.5, n).astype(np.float32) for _ in range(2))
-    alpha, tau = r.uniform(0.5, 1.5, C).astype(np.float32), r.uniform(-0.5, 0.5, C).astype(np.float32)
+    alpha, tau = (r.uniform(a, b, C).astype(np.float32) for a, b in ((0.5, 1.5), (-0.5, 0.5)))
     v, z = W.pm1(r, (n, C)), r.integers(-900, 901, size=(n, C)).astype(np.int16)
     xf, cw = r.standard_normal((n, C)).astype(np.float32), (C + 63) // 64
     out = torch.empty((n, C), dtype=torch.float32, device="cuda")
@@ -800,7 +800,8 @@ def test_spmm_f32_bits_through_the_counters(B, n, mean, power, C, tuning, form):
                 if rr is None:
                     through = any("bspmm" in k for k in names)
                     # (plain CSR without long rows works without scratch)
-                    assert through == (c is big or need == 0) and any("spmm" in k for k in names), names
+                    assert through == (c is big or need == 0), names
+                    assert any("spmm" in k for k in names), names
                     assert not through or any(form in k for k in names), names
             torch.cuda.synchronize()
             got, gb = out.cpu().numpy(), words_np(ob)
