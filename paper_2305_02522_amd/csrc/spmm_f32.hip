@@ -521,8 +521,8 @@ uint32_t windows_of(int32_t C, int V) { return ((uint32_t)C + kTeam * V - 1) / (
 // What a launch without the fixed part of a call (about 5 us) is expected to take in
 // microseconds, with the rows of at least 2^k neighbours as hub rows (k < 0: none).  Two things
 // take time side by side: the longest row that a team walks, and everybody's gathers.  Fitted on
-// 181 graphs (R-MAT, Chung-Lu, block model; 2,000 to 370,000 nodes, mean degree 3 to 400), 3,200
-// operands of 7 to 500 channels, each k timed in turn; the k chosen here is on average 1 to 2 %
+// 201 graphs (R-MAT, Chung-Lu, block model; 2,000 to 370,000 nodes, mean degree 3 to 400), 3,500
+// operands of 3 to 500 channels, each k timed in turn; the k chosen here is on average 1 to 2 %
 // slower than the best of them.
 double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large, int V,
                int k)
@@ -531,14 +531,14 @@ double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool 
     // store; the thresholds of 8 channels per lane cost most).  `large`: x is larger than an L2.
     double chain, gather, row;
     if (V == 1)
-        chain = 18, gather = 0.0055, row = 0.08;
+        chain = large ? 30 : 18, gather = large ? 0.0052 : 0.0025, row = 0.07;
     else if (xkind == 1)
-        chain = V == 8 ? 54 : 34, gather = V == 8 ? 0.006 : 0.005,
+        chain = V == 8 ? 54 : 33, gather = V == 4 || large ? 0.005 : 0.0075,
         row = V == 8 && bits_out ? 0.2 : 0.09;
     else if (xkind == 2)
         chain = 42, gather = 0.0085, row = 0.14;
     else
-        chain = large ? 65 : 35, gather = large ? 0.0085 : 0.014, row = 0.12;
+        chain = large ? 65 : 35, gather = large ? 0.0075 : 0.0095, row = 0.13;
     const double windows = windows_of(C, V), nnz = (double)adj->nnz, n = (double)adj->n;
     if (k < 0)
         return std::hypot(chain * (double)adj->max_degree,
@@ -553,16 +553,17 @@ double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool 
     }
     hub = std::fmin(hub, nnz);
     const double rows = adj->n_ge[k], tiles = (double)((C + 63) / 64);
-    const double walk =
-        (xkind == 1 ? 1.0 : 1.2) * std::fmin((double)adj->max_degree, (double)(1u << k));
-    const double teams = windows * ((nnz - hub) * gather * 1.2 + (n - rows) * row * 1.5);
+    const double walk = (V == 1 || xkind == 1 ? 1.1 : 1.2) *
+                        std::fmin((double)adj->max_degree, (double)(1u << k));
+    const double teams =
+        windows * ((nnz - hub) * gather * 1.2 + (n - rows) * row * (V == 8 ? 1.0 : 1.5));
     return std::hypot(chain * walk, teams + tiles * (rows * 4 + hub * 0.017)) * 1e-3 + 1.2;
 }
 
 struct Plan {
     int V;          // channels per lane of a team
     uint32_t n_hub; // hub rows
-    double us;      // team_us of the two
+    double us;      // its price
 };
 
 // Channels per lane: 16 bytes of a float row, 8 of an integer row; narrow rows spread over all
@@ -585,7 +586,10 @@ Plan choose_plan(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, boo
                 break;
             if ((uint64_t)n_hub * (((uint32_t)C + 63) / 64) * kHubBlock > 1u << 30)
                 continue;
-            const double us = team_us(adj, xkind, C, bits_out, large, Vs[q], kk);
+            // (of float and integer rows 2^9 is the best most often, and within a few per cent
+            // where it is not: it wins what the prices do not tell apart)
+            const double us = team_us(adj, xkind, C, bits_out, large, Vs[q], kk) *
+                              (kk == 9 && xkind != 1 ? 0.93 : 1.0);
             if (best.V == 0 || us < best.us)
                 best = Plan{Vs[q], n_hub, us};
         }
