@@ -310,9 +310,10 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
 {
     // window and row of this team: a group of windows of a row side by side (one instruction then
     // covers adjacent pieces of a row), one group of all rows after the other
-    const uint32_t grp = tb / a.group_blocks;
+    // (the divisions are latency that every row waits for, so what needs none goes without)
+    const uint32_t grp = a.group < a.windows ? tb / a.group_blocks : 0u;
     const uint32_t team = (tb - grp * a.group_blocks) * (kThreads / kTeam) + threadIdx.x / kTeam;
-    const uint32_t team_row = team / a.group;
+    const uint32_t team_row = a.group == 1 ? team : team / a.group;
     const uint32_t window = grp * a.group + (team - team_row * a.group);
     const uint32_t sub = threadIdx.x & 15;
     const uint32_t slot = a.slot0 + team_row;
