@@ -20,8 +20,9 @@
  *  - every data pointer is a DEVICE pointer owned by the caller and must stay
  *    valid until the enqueued work has run.  The library allocates device
  *    memory only inside a bitgnn_adj and inside a context: a few hundred KB of
- *    fixed scratch, plus the aggregation workspace (degree-ordered activation
- *    rows, partial counters of row parts and segments).  bitgnn_adj_build
+ *    fixed scratch, memory kept for the next bitgnn_adj_build (at most 4 GiB), plus
+ *    the aggregation workspace (degree-ordered activation rows, partial counters of
+ *    row parts and segments).  bitgnn_adj_build
  *    reserves that workspace for aggregations of up to
  *    BITGNN_DEFAULT_WS_CHANNELS channels and BITGNN_DEFAULT_WS_CLASSES classes
  *    on the graph it builds; wider calls need bitgnn_adj_workspace_bytes +
@@ -161,9 +162,10 @@ int bitgnn_pack_weights_i8(bitgnn_ctx *ctx, void *stream, const int8_t *w, int32
  * ADD_SELF_LOOPS).  Duplicates collapse (set semantics).  Row i of the result
  * lists N(i) = { j : A_hat[i][j] = 1 } in increasing j.
  * src, dst: int32 [E] device arrays, left unchanged.  Requires
- * E*(1 + symmetrize) + N < 2^31.  Synchronizes `stream`.  Temporary sort
- * buffers are freed before returning; the handle keeps the CSR arrays, the
- * degrees and a degree-sorted row order.  Also grows the context's aggregation
+ * E*(1 + symmetrize) + N < 2^31.  Synchronizes `stream`.  The handle keeps the CSR
+ * arrays, the degrees and a degree-sorted row order.  Temporary sort buffers, and the
+ * arrays of handles that are destroyed, are kept by the context for its next builds,
+ * at most 4 GiB of them, and freed with it (or when an allocation would fail).  Also grows the context's aggregation
  * workspace (bitgnn_ctx_reserve) to what this graph needs at the default widths.
  * Errors: BITGNN_ERR_INDEX_RANGE if an endpoint is outside [0, N). */
 int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *src, const int32_t *dst,
@@ -187,6 +189,8 @@ int bitgnn_adj_csr(const bitgnn_adj *adj, const uint32_t **rowptr, const int32_t
 int bitgnn_adj_blocked_info(const bitgnn_adj *adj, int64_t *parts, int64_t *slices,
                             int64_t *workgroups, int64_t *tiles, int64_t *stored_ids,
                             int64_t *cb_nodes);
+/* Waits for the device, then frees the handle or leaves its arrays to later builds of the
+ * context that made it.  The handle may outlive that context. */
 void bitgnn_adj_destroy(bitgnn_adj *adj);
 
 /* Tuning utility (the paper's Section 3.4, per graph): runs bitgnn_bspmm's two kernels

@@ -361,19 +361,6 @@ __global__ void slice_desc_kernel(const uint32_t *__restrict__ sl_cb,
 
 } // namespace
 
-void bg_free_blocked(bitgnn_blocked *b)
-{
-    if (!b)
-        return;
-    (void)hipFree(b->wg_item);
-    (void)hipFree(b->sl_desc);
-    (void)hipFree(b->tile_group);
-    (void)hipFree(b->idx16);
-    (void)hipFree(b->row_vptr);
-    (void)hipFree(b->part_info);
-    free(b);
-}
-
 // Builds adj->blk from the CSR arrays of `adj` (already on the device).
 int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
 {
@@ -386,7 +373,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     while ((1ll << cbits) < adj->n)
         ++cbits;
 
-    DevBuf rank, deg_sorted, nparts, keys_a, keys_b, hist, scan_ws, multi;
+    DevBuf rank(ctx), deg_sorted(ctx), nparts(ctx), keys_a(ctx), keys_b(ctx), hist(ctx), scan_ws(ctx), multi(ctx);
     const uint32_t sort_n = nnz > n ? nnz : n;
     const uint32_t sort_tiles = (sort_n + kSortTile - 1) / kSortTile;
     BG_HIP(ctx, rank.alloc((size_t)n * 4));
@@ -403,7 +390,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     BG_HIP(ctx, scan_ws.alloc(scan_ws_words(scan_max) * 4));
 
     BG_HIP(ctx, multi.alloc(4));
-    BG_HIP(ctx, hipMemsetAsync(multi.p, 0, 4, s));
+    BG_HIP(ctx, hipMemsetAsync(multi.as<void>(), 0, 4, s));
     slot_kernel<<<blocks_for((int64_t)n + 1, 256), 256, 0, s>>>(
         adj->order, adj->deg, n, part_len, rank.as<int32_t>(), deg_sorted.as<uint32_t>(),
         nparts.as<uint32_t>(), multi.as<uint32_t>());
@@ -421,13 +408,13 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     BG_LAUNCH_CHECK(ctx, "blocked radix_sort");
     uint32_t V = 0, n_multi = 0;
     BG_HIP(ctx, hipMemcpyAsync(&V, vptr + n, 4, hipMemcpyDeviceToHost, s));
-    BG_HIP(ctx, hipMemcpyAsync(&n_multi, multi.p, 4, hipMemcpyDeviceToHost, s));
+    BG_HIP(ctx, hipMemcpyAsync(&n_multi, multi.as<void>(), 4, hipMemcpyDeviceToHost, s));
     BG_HIP(ctx, hipStreamSynchronize(s));
     if (V >= kVidMask)
         return BITGNN_OK;
 
     // parts, sorted by (first block, last block, decreasing length)
-    DevBuf v_beg, v_end, v_slot, vk_a, vk_b;
+    DevBuf v_beg(ctx), v_end(ctx), v_slot(ctx), vk_a(ctx), vk_b(ctx);
     BG_HIP(ctx, v_beg.alloc((size_t)V * 4));
     BG_HIP(ctx, v_end.alloc((size_t)V * 4));
     BG_HIP(ctx, v_slot.alloc((size_t)V * 4));
@@ -453,7 +440,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     while (spw > 4 && (S + spw - 1) / spw < want)
         spw /= 2;
     const uint32_t W = (S + spw - 1) / spw;
-    DevBuf sl_cb, sl_tile_base, wg_cb, part_info;
+    DevBuf sl_cb(ctx), sl_tile_base(ctx), wg_cb(ctx), part_info(ctx);
     BG_HIP(ctx, sl_cb.alloc((size_t)S * 4));
     BG_HIP(ctx, sl_tile_base.alloc(((size_t)S + 1) * 4));
     BG_HIP(ctx, wg_cb.alloc((size_t)W * 4));
@@ -465,7 +452,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     BG_HIP(ctx, hipMemcpyAsync(&T, sl_tile_base.as<uint32_t>() + S, 4, hipMemcpyDeviceToHost, s));
     BG_HIP(ctx, hipStreamSynchronize(s));
 
-    DevBuf tile_group;
+    DevBuf tile_group(ctx);
     BG_HIP(ctx, tile_group.alloc(((size_t)T + 1) * 4));
     BG_HIP(ctx, hipMemsetAsync(tile_group.as<uint32_t>() + T, 0, 4, s));
     tile_kernel<false><<<S, 64, 0, s>>>(svkeys, V, v_beg.as<uint32_t>(), v_end.as<uint32_t>(),
@@ -475,7 +462,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     BG_LAUNCH_CHECK(ctx, "tile count");
     // the number of tiles is not bounded by the sizes above (sparse rows that span many
     // column blocks): size the workspace of this scan by itself
-    DevBuf tile_scan_ws;
+    DevBuf tile_scan_ws(ctx);
     BG_HIP(ctx, tile_scan_ws.alloc(scan_ws_words((uint64_t)T + 1) * 4));
     scan_inplace(tile_group.as<uint32_t>(), T + 1, tile_scan_ws.as<uint32_t>(), s);
     uint32_t G = 0;
@@ -490,7 +477,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     if (ctx->min_avg_degree > 0 && (uint64_t)G * kGroupIds > 6ull * nnz)
         return BITGNN_OK;
 
-    DevBuf idx16;
+    DevBuf idx16(ctx);
     BG_HIP(ctx, idx16.alloc(((size_t)G + 1) * kGroupIds * 2));
     tail_group_kernel<<<blocks_for((int64_t)kGroupIds, 256), 256, 0, s>>>(idx16.as<uint16_t>(), G,
                                                                          cbn);
@@ -505,7 +492,7 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
                                                       wg_cb.as<uint32_t>());
     BG_LAUNCH_CHECK(ctx, "wg_range");
     // dispatch order: heaviest workgroups first (the key buffers of the parts are free again)
-    DevBuf wg_item, sl_desc;
+    DevBuf wg_item(ctx), sl_desc(ctx);
     BG_HIP(ctx, wg_item.alloc((size_t)W * 8));
     BG_HIP(ctx, sl_desc.alloc((size_t)S * 16));
     wg_cost_kernel<<<blocks_for(W, 64), 64, 0, s>>>(wg_cb.as<uint32_t>(), sl_cb.as<uint32_t>(),
@@ -538,12 +525,12 @@ int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     b->n_groups = G;
     b->device_bytes = ((size_t)G + 1) * kGroupIds * 2 + ((size_t)T + 1) * 4 + (size_t)S * 16 +
                       (size_t)W * 8 + ((size_t)n + 1) * 4 + (size_t)V * 8;
-    b->wg_item = (uint2 *)wg_item.release();
-    b->sl_desc = (uint4 *)sl_desc.release();
-    b->tile_group = (uint32_t *)tile_group.release();
-    b->idx16 = (uint16_t *)idx16.release();
-    b->row_vptr = (uint32_t *)nparts.release();
-    b->part_info = (uint2 *)part_info.release();
+    b->wg_item = wg_item.give<uint2>(adj);
+    b->sl_desc = sl_desc.give<uint4>(adj);
+    b->tile_group = tile_group.give<uint32_t>(adj);
+    b->idx16 = idx16.give<uint16_t>(adj);
+    b->row_vptr = nparts.give<uint32_t>(adj);
+    b->part_info = part_info.give<uint2>(adj);
     adj->blk = b;
     adj->device_bytes += b->device_bytes;
     return BITGNN_OK;

@@ -206,7 +206,7 @@ static int adj_finish(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     // graph a few percent of the nodes take half of all gathers; in a degree-ordered copy of
     // the activations their rows are adjacent and stay in L2.
     if (!adj->blk && nnz > 0 && N >= 65536) {
-        DevBuf rank, col_slot;
+        DevBuf rank(ctx), col_slot(ctx);
         BG_HIP(ctx, rank.alloc((size_t)N * 4));
         BG_HIP(ctx, col_slot.alloc((size_t)nnz * 4));
         rank_kernel<<<blocks_for(N, 256), 256, 0, s>>>(adj->order, (uint32_t)N, rank.as<int32_t>());
@@ -214,25 +214,25 @@ static int adj_finish(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
                                                             col_slot.as<int32_t>());
         BG_LAUNCH_CHECK(ctx, "col_slot");
         BG_HIP(ctx, hipStreamSynchronize(s));
-        adj->col_slot = (int32_t *)col_slot.release();
+        adj->col_slot = col_slot.give<int32_t>(adj);
         adj->device_bytes += (size_t)nnz * 4;
     }
     // segments of the long rows for the CSR bit-SpMM
     if (N > 0) {
-        DevBuf nseg, seg_slot, cnt;
+        DevBuf nseg(ctx), seg_slot(ctx), cnt(ctx);
         BG_HIP(ctx, nseg.alloc(((size_t)N + 1) * 4));
         BG_HIP(ctx, cnt.alloc(4));
-        BG_HIP(ctx, hipMemsetAsync(cnt.p, 0, 4, s));
+        BG_HIP(ctx, hipMemsetAsync(cnt.as<void>(), 0, 4, s));
         adj->seg_len = (int64_t)nnz >= kSegLargeNnz ? kSegLenLarge : kSegLenSmall;
         seg_count_kernel<<<blocks_for(N + 1, 256), 256, 0, s>>>(
             adj->order, adj->deg, (uint32_t)N, adj->seg_len, nseg.as<uint32_t>(),
             cnt.as<uint32_t>());
         BG_LAUNCH_CHECK(ctx, "seg_count");
-        DevBuf sws;
+        DevBuf sws(ctx);
         BG_HIP(ctx, sws.alloc(scan_ws_words((uint64_t)N + 1) * 4));
         scan_inplace(nseg.as<uint32_t>(), (uint32_t)N + 1, sws.as<uint32_t>(), s);
         uint32_t n_long = 0, n_long_segs = 0;
-        BG_HIP(ctx, hipMemcpyAsync(&n_long, cnt.p, 4, hipMemcpyDeviceToHost, s));
+        BG_HIP(ctx, hipMemcpyAsync(&n_long, cnt.as<uint32_t>(), 4, hipMemcpyDeviceToHost, s));
         BG_HIP(ctx, hipStreamSynchronize(s));
         if (n_long > 0) {
             BG_HIP(ctx, hipMemcpyAsync(&n_long_segs, nseg.as<uint32_t>() + n_long, 4,
@@ -243,8 +243,8 @@ static int adj_finish(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
                                                                    seg_slot.as<uint32_t>());
             BG_LAUNCH_CHECK(ctx, "seg_slot");
             BG_HIP(ctx, hipStreamSynchronize(s));
-            adj->seg_slot = (uint32_t *)seg_slot.release();
-            adj->seg_ptr = (uint32_t *)nseg.release(); // the first n_long + 1 entries are used
+            adj->seg_slot = seg_slot.give<uint32_t>(adj);
+            adj->seg_ptr = nseg.give<uint32_t>(adj); // the first n_long + 1 entries are used
             adj->device_bytes += ((size_t)N + 1) * 4 + (size_t)n_long_segs * 4;
         }
         adj->n_long = n_long;
@@ -253,12 +253,9 @@ static int adj_finish(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj)
     return BITGNN_OK;
 }
 
-extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *src,
-                                const int32_t *dst, int64_t E, int64_t N, uint32_t flags,
-                                bitgnn_adj **out)
+static int adj_build(bitgnn_ctx *ctx, hipStream_t s, const int32_t *src, const int32_t *dst,
+                     int64_t E, int64_t N, uint32_t flags, bitgnn_adj **out)
 {
-    if (!ctx)
-        return BITGNN_ERR_INVALID_ARG;
     BG_REQUIRE(ctx, out, BITGNN_ERR_INVALID_ARG, "bitgnn_adj_build: out is null");
     BG_REQUIRE(ctx, E >= 0 && N >= 1, BITGNN_ERR_INVALID_ARG, "bitgnn_adj_build: E=%lld N=%lld",
                (long long)E, (long long)N);
@@ -275,7 +272,6 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
                "bitgnn_adj_build: %lld stored pairs + N exceed 32-bit offsets", (long long)nkeys64);
     BG_NEED_DEVICE(ctx);
 
-    hipStream_t s = (hipStream_t)stream;
     BG_HIP(ctx, hipSetDevice(ctx->device));
     const uint32_t nkeys = (uint32_t)nkeys64;
     int cb = 1;
@@ -285,14 +281,14 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     const uint32_t sort_n = nkeys > (uint32_t)N ? nkeys : (uint32_t)N;
     const uint32_t sort_tiles = (sort_n + kSortTile - 1) / kSortTile;
     const uint32_t uniq_tiles = (nkeys + kScanTile - 1) / kScanTile;
-    DevBuf keys_a, keys_b, hist, scan_ws, counts, flag;
+    DevBuf keys_a(ctx), keys_b(ctx), hist(ctx), scan_ws(ctx), counts(ctx), flag(ctx);
     BG_HIP(ctx, keys_a.alloc((size_t)sort_n * 8));
     BG_HIP(ctx, keys_b.alloc((size_t)sort_n * 8));
     BG_HIP(ctx, hist.alloc((size_t)256 * sort_tiles * 4));
     BG_HIP(ctx, scan_ws.alloc(scan_ws_words((uint64_t)256 * sort_tiles) * 4));
     BG_HIP(ctx, counts.alloc(((size_t)uniq_tiles + 1) * 4));
     BG_HIP(ctx, flag.alloc(sizeof(int) + sizeof(DegreeInfo)));
-    BG_HIP(ctx, hipMemsetAsync(flag.p, 0, sizeof(int) + sizeof(DegreeInfo), s));
+    BG_HIP(ctx, hipMemsetAsync(flag.as<void>(), 0, sizeof(int) + sizeof(DegreeInfo), s));
     int *d_err = flag.as<int>();
     DegreeInfo *d_info = (DegreeInfo *)(d_err + 1);
 
@@ -325,13 +321,13 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     BG_REQUIRE(ctx, h_err == 0, BITGNN_ERR_INDEX_RANGE,
                "bitgnn_adj_build: an edge endpoint is outside [0, %lld)", (long long)N);
 
-    DevBuf rowptr, col, deg, order;
+    DevBuf rowptr(ctx), col(ctx), deg(ctx), order(ctx);
     BG_HIP(ctx, rowptr.alloc(((size_t)N + 1) * 4));
     BG_HIP(ctx, col.alloc((size_t)nnz * 4));
     BG_HIP(ctx, deg.alloc((size_t)N * 4));
     BG_HIP(ctx, order.alloc((size_t)N * 4));
     if (nnz == 0) // kernels may read (not use) the first column of an empty graph
-        BG_HIP(ctx, hipMemsetAsync(col.p, 0, 4, s));
+        BG_HIP(ctx, hipMemsetAsync(col.as<void>(), 0, 4, s));
     else
         split_keys_kernel<<<blocks_for(nnz, 256), 256, 0, s>>>(sorted, nnz, cb, col.as<int32_t>());
     rowptr_kernel<<<blocks_for(N + 1, 256), 256, 0, s>>>(sorted, nnz, cb, (uint32_t)N,
@@ -354,15 +350,17 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     bitgnn_adj *adj = (bitgnn_adj *)calloc(1, sizeof(bitgnn_adj));
     BG_REQUIRE(ctx, adj, BITGNN_ERR_INVALID_ARG, "bitgnn_adj_build: out of host memory");
     adj->device = ctx->device;
+    adj->pool = ctx->pool;
+    bg_pool_hold(adj->pool);
     adj->n = N;
     adj->nnz = nnz;
     adj->max_degree = info.max_degree;
     memcpy(adj->n_ge, info.n_ge, sizeof(info.n_ge));
     adj->device_bytes = ((size_t)N + 1) * 4 + (size_t)nnz * 4 + (size_t)N * 8;
-    adj->rowptr = (uint32_t *)rowptr.release();
-    adj->col = (int32_t *)col.release();
-    adj->deg = (int32_t *)deg.release();
-    adj->order = (int32_t *)order.release();
+    adj->rowptr = rowptr.give<uint32_t>(adj);
+    adj->col = col.give<int32_t>(adj);
+    adj->deg = deg.give<int32_t>(adj);
+    adj->order = order.give<int32_t>(adj);
     // dense enough: also build the column-blocked form for the LDS-staged bit-SpMM
     if ((int64_t)nnz >= (int64_t)ctx->min_avg_degree * N) {
         keys_a.reset();
@@ -384,6 +382,19 @@ extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *sr
     }
     *out = adj;
     return BITGNN_OK;
+}
+
+extern "C" int bitgnn_adj_build(bitgnn_ctx *ctx, void *stream, const int32_t *src,
+                                const int32_t *dst, int64_t E, int64_t N, uint32_t flags,
+                                bitgnn_adj **out)
+{
+    if (!ctx)
+        return BITGNN_ERR_INVALID_ARG;
+    const int rc = adj_build(ctx, (hipStream_t)stream, src, dst, E, N, flags, out);
+    // the temporaries are back in the pool: nothing may still run on them, also after an error
+    if (ctx->device >= 0 && rc != BITGNN_OK)
+        (void)hipStreamSynchronize((hipStream_t)stream);
+    return rc;
 }
 
 extern "C" int bitgnn_adj_workspace_bytes(const bitgnn_adj *adj, int32_t C_max, int32_t M_max,
@@ -447,17 +458,26 @@ extern "C" int bitgnn_adj_blocked_info(const bitgnn_adj *adj, int64_t *parts, in
     return BITGNN_OK;
 }
 
+// Waits for the device, as freeing memory would: the arrays go back to the pool, where another
+// build on any stream may take them.  Where waiting is refused (a stream is being recorded) they
+// are freed instead.
 extern "C" void bitgnn_adj_destroy(bitgnn_adj *adj)
 {
     if (!adj)
         return;
-    (void)hipFree(adj->rowptr);
-    (void)hipFree(adj->col);
-    (void)hipFree(adj->deg);
-    (void)hipFree(adj->order);
-    (void)hipFree(adj->col_slot);
-    (void)hipFree(adj->seg_ptr);
-    (void)hipFree(adj->seg_slot);
-    bg_free_blocked(adj->blk);
+    int device = -1;
+    (void)hipGetDevice(&device);
+    const bool idle = (device == adj->device || hipSetDevice(adj->device) == hipSuccess) &&
+                      hipDeviceSynchronize() == hipSuccess;
+    for (int i = 0; i < adj->n_owned; ++i) {
+        if (idle)
+            bg_pool_give(adj->pool, adj->owned[i]);
+        else
+            (void)hipFree(adj->owned[i].p);
+    }
+    if (device >= 0 && device != adj->device)
+        (void)hipSetDevice(device);
+    bg_pool_drop(adj->pool);
+    free(adj->blk);
     free(adj);
 }

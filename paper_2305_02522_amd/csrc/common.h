@@ -31,6 +31,26 @@ struct bg_retired {
     bg_retired *next;
 };
 
+// Device memory of the adjacency builds: their temporaries and the arrays of the handles.  A
+// build needs gigabytes on a dense graph, and memory that goes back to the driver is cleared
+// before it is handed out again, so what a build or a destroyed handle gives back is kept, at
+// most kPoolBytes of it, until a later build of the same context takes it or the context goes.
+// The pool outlives its context while handles hold blocks of it.  Any thread may give back;
+// blocks in the pool have no work pending on them (who gives back has waited for it).
+struct bg_block {
+    void *p;
+    size_t bytes;
+};
+struct bg_pool;
+static const size_t kPoolBytes = (size_t)4 << 30;
+bg_pool *bg_pool_create();
+hipError_t bg_pool_take(bg_pool *pool, size_t bytes, bg_block *out);
+void bg_pool_give(bg_pool *pool, bg_block b);
+void bg_pool_trim(bg_pool *pool);  // frees what is kept
+void bg_pool_hold(bg_pool *pool);  // one more owner
+void bg_pool_drop(bg_pool *pool);  // one owner less: the last one frees the pool
+void bg_pool_close(bg_pool *pool); // the context goes: nothing is kept from now on
+
 struct bitgnn_ctx {
     int device;           // -1: validation-only context
     int n_cus;            // compute units of the device
@@ -40,6 +60,7 @@ struct bitgnn_ctx {
     bg_scratch own;       // the context's scratch
     bg_retired *retired;  // superseded workspaces that recorded graphs hold, freed with the context
     bg_scratch *sc;       // the scratch the current call uses (&own outside such a call)
+    bg_pool *pool;        // device memory of the adjacency builds
     uint32_t fused_spin_limit; // polls of one barrier wait before it is abandoned
     char err[256];
     // tuning of the column-blocked aggregation format (bitgnn_ctx_set_tuning)
@@ -143,6 +164,9 @@ struct bitgnn_adj {
     uint32_t n_long_segs; // their segments
     size_t device_bytes;
     bitgnn_blocked *blk; // null when the graph is too sparse for the blocked path
+    bg_pool *pool;       // where the arrays came from and go back to
+    bg_block owned[16];  // every device array of the handle, its blocked form included
+    int n_owned;
     // bitgnn_adj_tune's verdict for bit aggregations of 1, 2, 3, >= 4 passes of 128 channels:
     // 0 = not measured (the time model decides), 1 = CSR kernel, 2 = column-blocked kernel
     int8_t pref[4];
@@ -218,7 +242,6 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
                          int32_t M, int64_t w_stride, int epilogue, const int32_t *T,
                          const float *alpha, void *out, int64_t out_stride);
 int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj);
-void bg_free_blocked(bitgnn_blocked *b);
 int bg_ws_need(bitgnn_ctx *ctx, hipStream_t s, size_t bytes, const char *who);
 int bg_static_scratch_init(bitgnn_ctx *ctx);
 // Bytes of context workspace the aggregations on `adj` need for up to C aggregated

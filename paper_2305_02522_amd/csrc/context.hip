@@ -1,8 +1,151 @@
 // Context life cycle and error reporting.
 #include "common.h"
 
+#include <pthread.h>
 #include <stdlib.h>
 
+// ---------------------------------------------------------------- pool
+namespace {
+struct PoolNode {
+    bg_block b;
+    PoolNode *next;
+};
+} // namespace
+
+struct bg_pool {
+    pthread_mutex_t lock;
+    PoolNode *kept; // newest first
+    size_t bytes;
+    int owners;
+    bool closed;
+};
+
+bg_pool *bg_pool_create()
+{
+    bg_pool *pool = (bg_pool *)calloc(1, sizeof(bg_pool));
+    if (pool) {
+        pthread_mutex_init(&pool->lock, nullptr);
+        pool->owners = 1;
+    }
+    return pool;
+}
+
+// The smallest kept block that wastes at most a quarter (or 64 KB), else a new one.
+hipError_t bg_pool_take(bg_pool *pool, size_t bytes, bg_block *out)
+{
+    const size_t unit = bytes < ((size_t)1 << 20) ? 512 : (size_t)1 << 21;
+    bytes = ((bytes ? bytes : 1) + unit - 1) / unit * unit;
+    pthread_mutex_lock(&pool->lock);
+    PoolNode **best = nullptr;
+    for (PoolNode **q = &pool->kept; *q; q = &(*q)->next) {
+        const size_t have = (*q)->b.bytes;
+        if (have >= bytes && have <= bytes + bytes / 4 + 65536 &&
+            (!best || have < (*best)->b.bytes))
+            best = q;
+    }
+    if (best) {
+        PoolNode *n = *best;
+        *best = n->next;
+        *out = n->b;
+        pool->bytes -= n->b.bytes;
+        free(n);
+    }
+    pthread_mutex_unlock(&pool->lock);
+    if (best)
+        return hipSuccess;
+    out->bytes = bytes;
+    hipError_t e = hipMalloc(&out->p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        bg_pool_trim(pool);
+        e = hipMalloc(&out->p, bytes);
+    }
+    if (e != hipSuccess)
+        *out = bg_block{};
+    return e;
+}
+
+// Keeps the block; the ones kept longest go where that would exceed the bound.
+void bg_pool_give(bg_pool *pool, bg_block b)
+{
+    if (!b.p)
+        return;
+    PoolNode *n = b.bytes <= kPoolBytes ? (PoolNode *)malloc(sizeof(PoolNode)) : nullptr;
+    PoolNode *gone = nullptr;
+    pthread_mutex_lock(&pool->lock);
+    const bool keep = n && !pool->closed;
+    if (keep) {
+        *n = PoolNode{b, pool->kept};
+        pool->kept = n;
+        pool->bytes += b.bytes;
+        size_t sum = 0;
+        for (PoolNode **q = &pool->kept; *q; q = &(*q)->next) {
+            sum += (*q)->b.bytes;
+            if (sum > kPoolBytes) {
+                gone = *q;
+                *q = nullptr;
+                pool->bytes = sum - gone->b.bytes;
+                break;
+            }
+        }
+    }
+    pthread_mutex_unlock(&pool->lock);
+    if (!keep) {
+        (void)hipFree(b.p);
+        free(n);
+    }
+    while (gone) {
+        PoolNode *next = gone->next;
+        (void)hipFree(gone->b.p);
+        free(gone);
+        gone = next;
+    }
+}
+
+void bg_pool_trim(bg_pool *pool)
+{
+    pthread_mutex_lock(&pool->lock);
+    PoolNode *n = pool->kept;
+    pool->kept = nullptr;
+    pool->bytes = 0;
+    pthread_mutex_unlock(&pool->lock);
+    while (n) {
+        PoolNode *next = n->next;
+        (void)hipFree(n->b.p);
+        free(n);
+        n = next;
+    }
+}
+
+void bg_pool_hold(bg_pool *pool)
+{
+    pthread_mutex_lock(&pool->lock);
+    ++pool->owners;
+    pthread_mutex_unlock(&pool->lock);
+}
+
+void bg_pool_drop(bg_pool *pool)
+{
+    pthread_mutex_lock(&pool->lock);
+    const bool last = --pool->owners == 0;
+    pthread_mutex_unlock(&pool->lock);
+    if (last) {
+        bg_pool_trim(pool);
+        pthread_mutex_destroy(&pool->lock);
+        free(pool);
+    }
+}
+
+void bg_pool_close(bg_pool *pool)
+{
+    pthread_mutex_lock(&pool->lock);
+    pool->closed = true;
+    pthread_mutex_unlock(&pool->lock);
+    bg_pool_trim(pool);
+    bg_pool_drop(pool);
+}
+
+// ---------------------------------------------------------------- life cycle
 extern "C" int bitgnn_ctx_create(bitgnn_ctx **out, int device)
 {
     if (!out || device < -1)
@@ -34,7 +177,11 @@ extern "C" int bitgnn_ctx_create(bitgnn_ctx **out, int device)
             e = hipMalloc((void **)&ctx->own.seed_table, kSeedTableWords * sizeof(uint32_t));
         if (e == hipSuccess)
             e = hipMalloc(&ctx->bgemm_ws, kBgemmScratchBytes);
+        if (e == hipSuccess && !(ctx->pool = bg_pool_create()))
+            e = hipErrorOutOfMemory;
         if (e != hipSuccess) {
+            if (ctx->bgemm_ws)
+                (void)hipFree(ctx->bgemm_ws);
             if (ctx->own.queue)
                 (void)hipFree(ctx->own.queue);
             if (ctx->own.seed_table)
@@ -70,6 +217,8 @@ extern "C" void bitgnn_ctx_destroy(bitgnn_ctx *ctx)
         (void)hipFree(r->p);
         free(r);
     }
+    if (ctx->pool)
+        bg_pool_close(ctx->pool);
     for (int i = 0; i < 2 * kMaxTimed; ++i)
         if (ctx->tev[i])
             (void)hipEventDestroy(ctx->tev[i]);
@@ -130,7 +279,12 @@ extern "C" int bitgnn_ctx_reserve(bitgnn_ctx *ctx, size_t bytes)
         bg_retired *r = (bg_retired *)malloc(sizeof(bg_retired));
         BG_REQUIRE(ctx, r, BITGNN_ERR_INVALID_ARG, "bitgnn_ctx_reserve: out of host memory");
         void *ws = nullptr;
-        const hipError_t e = hipMalloc(&ws, bytes);
+        hipError_t e = hipMalloc(&ws, bytes);
+        if (e == hipErrorOutOfMemory) { // the builds' kept memory first
+            (void)hipGetLastError();
+            bg_pool_trim(ctx->pool);
+            e = hipMalloc(&ws, bytes);
+        }
         if (e != hipSuccess)
             free(r);
         BG_HIP(ctx, e);
@@ -144,7 +298,13 @@ extern "C" int bitgnn_ctx_reserve(bitgnn_ctx *ctx, size_t bytes)
             own.ws = nullptr;
             own.ws_bytes = 0;
         }
-        BG_HIP(ctx, hipMalloc(&own.ws, bytes));
+        hipError_t e = hipMalloc(&own.ws, bytes);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            bg_pool_trim(ctx->pool);
+            e = hipMalloc(&own.ws, bytes);
+        }
+        BG_HIP(ctx, e);
     }
     own.ws_bytes = bytes;
     own.ws_recorded = false;

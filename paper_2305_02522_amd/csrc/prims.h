@@ -8,21 +8,28 @@
 namespace {
 
 // ---------------------------------------------------------------- helpers
+// A block of the context's pool.  Given back when it goes out of scope: the stream must be idle
+// by then, or the next user of the block must be work on the same stream.
 struct DevBuf {
-    void *p = nullptr;
+    bg_pool *pool;
+    bg_block b{};
+    explicit DevBuf(bitgnn_ctx *ctx) : pool(ctx->pool) {}
+    DevBuf(const DevBuf &) = delete;
+    DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf() { reset(); }
     void reset()
     {
-        if (p)
-            (void)hipFree(p);
-        p = nullptr;
+        bg_pool_give(pool, b);
+        b = bg_block{};
     }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 8); }
-    template <typename T> T *as() { return (T *)p; }
-    void *release()
+    hipError_t alloc(size_t bytes) { return bg_pool_take(pool, bytes, &b); }
+    template <typename T> T *as() { return (T *)b.p; }
+    // the handle owns the block from now on
+    template <typename T> T *give(bitgnn_adj *adj)
     {
-        void *q = p;
-        p = nullptr;
+        T *q = (T *)b.p;
+        adj->owned[adj->n_owned++] = b;
+        b = bg_block{};
         return q;
     }
 };

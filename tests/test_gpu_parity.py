@@ -176,6 +176,26 @@ def test_adj_build_sort_edges(B, ctx, n, e):
     adj.close()
 
 
+# Arrays of destroyed handles serve later builds of the same context: smaller, larger and equal
+# ones, while a handle that is kept, and one that outlives its context, stay as they are.
+def test_adj_build_reuses_memory_of_destroyed_handles(B):
+    c = B.Context(0)
+    r = np.random.default_rng(11)
+    made = []
+    for n, e in ((3000, 90000), (3000, 90000), (500, 700), (9000, 400000), (3000, 90000)):
+        src, dst = W.random_graph(r, n, e)
+        made.append((B.adj_build(c, dev(src), dev(dst), e, n, SYM_LOOPS),
+                     orc.adjacency(src, dst, n, SYM_LOOPS)))
+        if len(made) in (2, 4):
+            made.pop(0)[0].close()
+    c.close()
+    for adj, (rp_ref, col_ref) in made:
+        rp, col, deg = _csr_from_gpu(B, adj)
+        assert np.array_equal(rp, rp_ref) and np.array_equal(col, col_ref)
+        assert np.array_equal(deg, orc.degrees(rp_ref))
+        adj.close()
+
+
 def test_tuning_validation(B, ctx):
     for bad in ((63, 512, 32), (10209, 512, 32), (8192, 3, 32), (8192, 1024, 32), (8192, 512, -1)):
         with pytest.raises(B.BitgnnError) as e:
