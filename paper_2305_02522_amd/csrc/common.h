@@ -43,6 +43,7 @@ struct bg_block {
 };
 struct bg_pool;
 static const size_t kPoolBytes = (size_t)4 << 30;
+static const size_t kMailBytes = 4096;
 bg_pool *bg_pool_create();
 hipError_t bg_pool_take(bg_pool *pool, size_t bytes, bg_block *out);
 void bg_pool_give(bg_pool *pool, bg_block b);
@@ -61,6 +62,7 @@ struct bitgnn_ctx {
     bg_retired *retired;  // superseded workspaces that recorded graphs hold, freed with the context
     bg_scratch *sc;       // the scratch the current call uses (&own outside such a call)
     bg_pool *pool;        // device memory of the adjacency builds
+    void *mail;           // pinned host memory that build kernels leave sizes in (kMailBytes)
     uint32_t fused_spin_limit; // polls of one barrier wait before it is abandoned
     char err[256];
     // tuning of the column-blocked aggregation format (bitgnn_ctx_set_tuning)
@@ -241,7 +243,14 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
                          int64_t x_stride, int32_t K, int32_t kwords, const uint64_t *wbits,
                          int32_t M, int64_t w_stride, int epilogue, const int32_t *T,
                          const float *alpha, void *out, int64_t out_stride);
-int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj);
+// What the blocked form takes from the degree order (see OrderArrays in adj_build.hip).
+struct bg_slots {
+    const uint32_t *block_rank; // [n] by node: column block << 16 | position inside
+    const uint32_t *entry_ptr;  // [n + 1] by slot: first entry of the row
+    const uint32_t *part_ptr;   // [n + 1] by slot: first part of the row
+    uint32_t parts, multi;      // row parts, rows with more than one
+};
+int bg_build_blocked(bitgnn_ctx *ctx, hipStream_t s, bitgnn_adj *adj, const bg_slots &slots);
 int bg_ws_need(bitgnn_ctx *ctx, hipStream_t s, size_t bytes, const char *who);
 int bg_static_scratch_init(bitgnn_ctx *ctx);
 // Bytes of context workspace the aggregations on `adj` need for up to C aggregated

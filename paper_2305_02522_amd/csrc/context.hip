@@ -177,9 +177,13 @@ extern "C" int bitgnn_ctx_create(bitgnn_ctx **out, int device)
             e = hipMalloc((void **)&ctx->own.seed_table, kSeedTableWords * sizeof(uint32_t));
         if (e == hipSuccess)
             e = hipMalloc(&ctx->bgemm_ws, kBgemmScratchBytes);
+        if (e == hipSuccess)
+            e = hipHostMalloc(&ctx->mail, kMailBytes, hipHostMallocDefault);
         if (e == hipSuccess && !(ctx->pool = bg_pool_create()))
             e = hipErrorOutOfMemory;
         if (e != hipSuccess) {
+            if (ctx->mail)
+                (void)hipHostFree(ctx->mail);
             if (ctx->bgemm_ws)
                 (void)hipFree(ctx->bgemm_ws);
             if (ctx->own.queue)
@@ -219,6 +223,8 @@ extern "C" void bitgnn_ctx_destroy(bitgnn_ctx *ctx)
     }
     if (ctx->pool)
         bg_pool_close(ctx->pool);
+    if (ctx->mail)
+        (void)hipHostFree(ctx->mail);
     for (int i = 0; i < 2 * kMaxTimed; ++i)
         if (ctx->tev[i])
             (void)hipEventDestroy(ctx->tev[i]);

@@ -176,6 +176,31 @@ def test_adj_build_sort_edges(B, ctx, n, e):
     adj.close()
 
 
+# Ways through the bucket sort: dealt out in one pass or in two, with 32 or 64 bits between them; a
+# bucket's pairs around what half of a CU's LDS (15,360) and all of it (32,768) hold, several tiles
+# of that, and too many for it (the 64-bit keys); as many nodes as one workgroup orders.
+@pytest.mark.parametrize("n,e,hub,flags", [
+    (16383, 40000, 0, SYM_LOOPS), (16384, 40000, 0, SYM_LOOPS), (16385, 40000, 0, SYM_LOOPS),
+    (400000, 1100000, 0, W.ADJ_SYMMETRIZE), (2200000, 1000000, 0, SYM_LOOPS),
+    (2200000, 1000000, 40000, 0), (30000, 2000, 15359, 0), (30000, 2000, 15361, 0),
+    (30000, 2000, 15361, SYM_LOOPS), (60000, 2000, 32768, 0), (60000, 2000, 32769, 0),
+    (60000, 300, 120000, SYM_LOOPS), (250000, 1000, 200000, W.ADJ_SYMMETRIZE)])
+def test_adj_build_buckets(B, ctx, n, e, hub, flags):
+    r = np.random.default_rng(n + e + hub)
+    src, dst = W.random_graph(r, n, e)
+    if hub:  # row n // 2 alone in its bucket but for the random pairs
+        src = np.concatenate([src[(src >> 12) != (n // 2 >> 12)][:e // 2],
+                              np.full(hub, n // 2, dtype=np.int32)])
+        dst = np.concatenate([dst[:len(src) - hub], r.integers(0, n, hub, dtype=np.int32)])
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, flags)
+    rp_ref, col_ref = orc.adjacency(src, dst, n, flags)
+    rp, col, deg = _csr_from_gpu(B, adj)
+    assert np.array_equal(rp, rp_ref) and np.array_equal(col, col_ref)
+    assert np.array_equal(deg, orc.degrees(rp_ref))
+    assert adj.max_degree == orc.degrees(rp_ref).max()
+    adj.close()
+
+
 # Arrays of destroyed handles serve later builds of the same context: smaller, larger and equal
 # ones, while a handle that is kept, and one that outlives its context, stay as they are.
 def test_adj_build_reuses_memory_of_destroyed_handles(B):
