@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0                       # MI355X HBM3E
 VALU_PEAK_TLOPS = 256 * 64 * 2.4e9 / 1e12   # 256 CUs x 64 lanes x 2.4 GHz, 32-bit lane-ops
-MFMA_I8_PEAK_TOPS = 5000.0                  # dense int8 matrix cores
+MFMA_FP4_PEAK_TOPS = 10000.0                # dense FP4 matrix cores
 
 
 def source_stamp():
@@ -454,7 +454,7 @@ def main():
         if "lane_ops" in m:
             f["valu_frac"] = round(m["lane_ops"] / (ms * 1e-3) / 1e12 / VALU_PEAK_TLOPS, 4)
         if "mfma_ops" in m:
-            f["mfma_i8_frac"] = round(m["mfma_ops"] / (ms * 1e-3) / 1e12 / MFMA_I8_PEAK_TOPS, 4)
+            f["mfma_fp4_frac"] = round(m["mfma_ops"] / (ms * 1e-3) / 1e12 / MFMA_FP4_PEAK_TOPS, 4)
         for name, v in f.items():
             assert v <= 1.0, f"{name} = {v} > 1: the op model does not describe the kernel that ran"
         return f
@@ -503,8 +503,8 @@ def main():
     if dm["bound"] == "hbm":
         ach, peak, unit, frac = fr["hbm_frac"] * HBM_PEAK_GBS, HBM_PEAK_GBS, "GB/s", fr["hbm_frac"]
     elif dm["bound"] == "mfma":
-        ach, peak, unit, frac = (fr["mfma_i8_frac"] * MFMA_I8_PEAK_TOPS, MFMA_I8_PEAK_TOPS,
-                                 "TOP/s", fr["mfma_i8_frac"])
+        ach, peak, unit, frac = (fr["mfma_fp4_frac"] * MFMA_FP4_PEAK_TOPS, MFMA_FP4_PEAK_TOPS,
+                                 "TOP/s", fr["mfma_fp4_frac"])
     else:
         ach, peak, unit, frac = (fr["valu_frac"] * VALU_PEAK_TLOPS, round(VALU_PEAK_TLOPS, 2),
                                  "Tlane-op/s", fr["valu_frac"])

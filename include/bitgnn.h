@@ -71,7 +71,7 @@ enum {
 enum { /* kernels of the BMM (Section 2.2), bitgnn_ctx_set_bgemm_path */
     BITGNN_BGEMM_AUTO = 0, /* chosen per shape from measured crossovers */
     BITGNN_BGEMM_VALU = 1, /* xor + popcount on the vector ALUs */
-    BITGNN_BGEMM_MFMA = 2  /* bits widened to bytes, int8 matrix cores */
+    BITGNN_BGEMM_MFMA = 2  /* bits widened to +-1 in FP4, matrix cores */
 };
 
 enum {
@@ -110,8 +110,9 @@ int bitgnn_ctx_set_tuning(bitgnn_ctx *ctx, int32_t cb_nodes, int32_t part_len,
 
 /* Forces one of the two BMM kernels (tests, A/B measurements); BITGNN_BGEMM_MFMA still
  * falls back to the VALU kernel for shapes the matrix-core kernel does not take (rows of
- * more than 16 words; it runs wide outputs in column chunks whose widened weights fit its
- * LDS).  Results never depend on the choice.  Default: BITGNN_BGEMM_AUTO. */
+ * more than 68 words; it runs wide outputs in column chunks whose widened weights fit its
+ * LDS; float rows only where one chunk does).  Results never depend on the choice.
+ * Default: BITGNN_BGEMM_AUTO. */
 int bitgnn_ctx_set_bgemm_path(bitgnn_ctx *ctx, int path);
 /* Which kernel bitgnn_bgemm launches for n rows of kwords 64-bit words against M weight
  * rows under the context's current setting: *kernel <- BITGNN_BGEMM_VALU or _MFMA.  Host

@@ -448,6 +448,9 @@ int bg_launch_bgemm_f32(bitgnn_ctx *ctx, hipStream_t s, const float *x, int64_t 
 {
     if (n == 0)
         return BITGNN_OK;
+    if (bg_bgemm_f32_mfma_applies(ctx, K, M, epilogue))
+        return bg_launch_bgemm_f32_mfma(ctx, s, x, n, K, ldx, tau, wbits, M, w_stride, epilogue, T,
+                                        alpha, out, out_stride);
     BG_REQUIRE(ctx, (n + kWaves * kRowsF - 1) / (kWaves * kRowsF) < (1ll << 31),
                BITGNN_ERR_UNSUPPORTED, "bitgnn_bgemm_f32: n too large");
     const int32_t kw32 = (int32_t)(((int64_t)K + 63) / 64) * 2;

@@ -1,295 +1,570 @@
 // BMM on the matrix cores (Section 2.2: c = n - 2 popc(a xor b); the paper runs it on
-// 1-bit tensor cores, which CDNA4 does not have).  The product is a dense contraction, so
-// the bits are widened to 0/1 bytes on the fly and fed to v_mfma_i32_16x16x64_i8:
-//   D[i][c] = sum_k x_ik w_kc            (x, w in {0,1})
-//   popc(x_i xor w_c) = px_i + pw_c - 2 D[i][c]
-//   Z[i][c] = K - 2 px_i - 2 pw_c + 4 D[i][c]
-// with px, pw the popcounts of the stored rows (pad bits are zero in both operands).
+// 1-bit tensor cores, which CDNA4 does not have).  The narrowest format there is 4-bit floating
+// point (E2M1), which holds +-1 exactly: a stored bit becomes the nibble +1 (0x2) or -1 (0xA)
+// and v_mfma_scale_f32_16x16x128_f8f6f4, with unit scales, adds products of +-1 in float32.
+// Every partial sum is an integer (plus one half, see below) far below 2^23, so the result is
+// the exact integer whatever the order of the additions.  Positions that hold no element (pad
+// bits inside a row and behind it) are zero in both operands, so each adds (-1)(-1) = 1, and a
+// constant takes them off again:
+//   Z[i][c] = sum_k (+-1)(+-1) - (stored positions - K).
 //
 // gfx950 mapping
-//  - the weights, widened once per call to bytes (row stride K' + 16 so that the 16-byte
-//    operand reads of 16 columns fall into different LDS bank groups), stay in LDS for the
-//    whole life of a persistent workgroup (M' (K' + 16) <= 144 KB: wider outputs run as
-//    column chunks of whole 64-bit output words, one launch each);
-//  - a wavefront owns 32 node rows (two operands, widened from their packed words with
-//    three VALU ops per four bytes) and walks column groups of 128: 16 accumulators of
-//    16x16, every weight operand read from LDS feeds two MFMAs;
-//  - the weights are the MFMA's first operand, so a lane ends up with 4 consecutive columns
-//    of one node row: integers and logits leave as runs of 4, thresholded bits are built
-//    in-lane and OR-ed over the 4 lanes that share the row;
-//  - the rows of the next panel are requested while the current one is computed.
-// Against the VALU kernel (2 lane-ops per 32 bit-MACs: 629 T bit-MAC/s at peak, ~310
-// reached) the int8 MFMA peak is 2,500 T MAC/s; this kernel reaches ~740 on 2.4 M x 512 x 256
-// (widening and the epilogue share the issue slots with the MFMAs).  It is chosen when the
-// weights fit in LDS and there are enough rows to repay the set-up.
+//  - a lane's operand is 32 elements = one 32-bit word of a packed row, widened to four
+//    registers with two VALU ops each.  Nibble j of register q is bit 4 j + q of the word: the
+//    elements of a row may be taken in any order that both operands share;
+//  - the weights are widened once per workgroup and stay in LDS for its life, in the order in
+//    which lanes read them (16 consecutive bytes a lane: no bank conflicts).  64 x K / 2 bytes a
+//    64 columns: 256 columns of 1,024 bits fill 128 KB; wider outputs run as column chunks;
+//  - a wavefront owns 16 R node rows and walks column groups of CT tiles of 16: R x CT
+//    accumulators of 16 x 16, every weight operand read from LDS feeds R MFMAs, every widened
+//    row word CT;
+//  - the weights are the MFMA's first operand, so a lane ends up with 4 columns (4 g + j of
+//    every tile) of ONE node row: integers and logits leave as runs of 4.  For thresholded bits
+//    the tiles' columns are dealt so that the 16 values of four tiles are 16 consecutive bits of
+//    an output word: column 16 g + 4 t + j in row 4 g + j of tile t.  The accumulators start at
+//    1/2 - T - (pad positions), so a bit is the complement of the result's sign, one
+//    v_alignbit each;
+//  - row words are requested two K steps ahead, across column groups and panels.
+// Against the bits widened to bytes for the int8 cores (the form before) a MFMA takes twice the
+// elements in half the time, an operand 8 VALU ops per 32 elements instead of 24, and there is no
+// launch that widens the weights: 2.4 M x 512 x 256 to bits 432 -> 177 us, 2.4 M x 200 x 256
+// 291 -> 115, 233 K x 128 x 128 25 -> 9.3, and shapes that the VALU kernel used to win, 89 K x
+// 1000 x 256 79 -> 25, 10 K x 1433 x 64 28 -> 8.5.  What bounds it: 2.4 M x 512 x 256 is 0.64
+// Pop in 177 us, 36 % of the peak; the epilogue's and the widening's VALU ops take about as long
+// as the MFMAs.  Wide integers and logits are bound by writing them (2.4 M x 256: 4.3 TB/s).
 #include "common.h"
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kMfWaves = 8;            // wavefronts per workgroup
-constexpr int kMfRows = 32;            // rows per wavefront (two 16-row operands)
-constexpr int kMfPanel = kMfWaves * kMfRows;
-constexpr int kMfGroup = 8;            // column tiles of 16 per pass (128 columns)
-#ifndef BITGNN_MF_PAD
-#define BITGNN_MF_PAD 16
-#endif
-constexpr int kMfPad = BITGNN_MF_PAD;  // bytes added to a weight row in LDS (bank spreading)
-constexpr size_t kMfLdsLimit = 144 * 1024;
+constexpr size_t kMfLdsLimit = 140 * 1024; // weights; up to 18 KB of staged outputs beside them
 
-// w8[c * ldw + k] = stored bit k of weight row c (0 beyond the kbits stored bits or M);
-// pw[c] = its popcount.  Every stored bit position counts, not only k < K: rows may hold
-// pad bits in the middle (concatenated segments), which are zero in both operands.
-__global__ __launch_bounds__(256) void bgemm_widen_w_kernel(const uint32_t *__restrict__ w32,
-                                                            int64_t w_stride32, int32_t kbits,
-                                                            int32_t M, int32_t ldw,
-                                                            uint8_t *__restrict__ w8,
-                                                            int32_t *__restrict__ pw)
+// 32 bits -> 32 elements of +-1 in four bits each
+__device__ __forceinline__ v8i widen32(uint32_t w)
 {
-    __shared__ int part[4];
-    const int c = blockIdx.x, t = threadIdx.x;
-    int cnt = 0;
-    for (int k = t; k < ldw; k += 256) {
-        int v = 0;
-        if (c < M && k < kbits)
-            v = (w32[(int64_t)c * w_stride32 + (k >> 5)] >> (k & 31)) & 1u;
-        w8[(int64_t)c * ldw + k] = (uint8_t)v;
-        cnt += v;
-    }
+    v8i r = {};
+    const uint32_t m = ~w; // sign bits
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1)
-        cnt += __shfl_xor(cnt, d, 64);
-    if ((t & 63) == 0)
-        part[t >> 6] = cnt;
-    __syncthreads();
-    if (t == 0)
-        pw[c] = part[0] + part[1] + part[2] + part[3];
-}
-
-// 16 bits -> 16 bytes of 0/1 (one MFMA operand of a lane)
-__device__ __forceinline__ v4i widen16(uint32_t bits)
-{
-    v4i r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        r[i] = (int)((((bits >> (4 * i)) & 0xFu) * 0x00204081u) & 0x01010101u);
+    for (int q = 0; q < 4; ++q)
+        r[q] = (int)(((m << (3 - q)) & 0x88888888u) | 0x22222222u);
     return r;
 }
 
-// KS = 64-bit words of a packed row held in registers (K <= 64 KS; 2, 4, 8 or 16).
-template <int EPI, int KS>
-__global__ __launch_bounds__(kMfWaves * 64) void bgemm_mfma_kernel(
-    const uint64_t *__restrict__ xbits, int64_t n, int64_t x_stride, int32_t K, int32_t ksteps,
-    const uint4 *__restrict__ w8g, int32_t ldw, const int32_t *__restrict__ pw, int32_t M,
-    int32_t Mp, const int32_t *__restrict__ T, const float *__restrict__ alpha,
-    void *__restrict__ out, int64_t out_stride)
+__device__ __forceinline__ v4f mfma_pm1(const v8i &a, const v8i &b, const v4f &c)
 {
-    extern __shared__ uint4 wl[]; // Mp rows of ldw bytes
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r = lane & 15, g = lane >> 4;
-    for (int i = tid; i < Mp * (ldw / 16); i += kMfWaves * 64)
-        wl[i] = w8g[i];
-    char *wbytes = (char *)wl;
-    const int64_t last = n - 1;
-    // column constants behind the weights in LDS, fixed for the run:
-    // THRESH: T - K + 2 pw (a column beyond M never passes); else K - 2 pw, and the scale
-    int32_t *colk = (int32_t *)(wbytes + (size_t)Mp * ldw);
-    float *colf = (float *)(colk + Mp);
-    for (int c = tid; c < Mp; c += kMfWaves * 64) {
-        const bool c_ok = c < M;
-        const int pwc = c_ok ? pw[c] : 0;
-        if (EPI == BITGNN_EPI_THRESH_BITS) {
-            // |Z| <= K, so thresholds beyond +-(K + 1) decide nothing more: clamped first,
-            // the folded constant cannot overflow
-            int32_t tc = c_ok ? T[c] : 0;
-            tc = tc > K + 1 ? K + 1 : (tc < -K - 1 ? -K - 1 : tc);
-            colk[c] = c_ok ? tc - K + 2 * pwc : 0x7FFFFFFF;
-        }
-        else
-            colk[c] = K - 2 * pwc;
-        colf[c] = (EPI == BITGNN_EPI_SCALE_F32 && c_ok) ? alpha[c] : 0.0f;
+    // formats 4: E2M1; scales 2^(127 - 127)
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, 0x7F7F7F7F, 0,
+                                                            0x7F7F7F7F);
+}
+
+struct MfArgs {
+    const uint32_t *x;
+    int64_t n, x_stride;   // rows; 32-bit words between them
+    int32_t K, kw32;       // elements and stored 32-bit words of a row
+    const uint32_t *w;
+    int64_t w_stride;
+    int32_t M, tiles;      // columns, tiles of 16 of them
+    int32_t steps;         // of 128 positions
+    const int32_t *T;
+    const float *alpha;
+    void *out;
+    int64_t out_stride;
+};
+
+// Column of row `a` (0..15) of a tile.
+template <int EPI> __device__ __forceinline__ int mf_column(int tile, int a)
+{
+    if (EPI == BITGNN_EPI_THRESH_BITS)
+        return 64 * (tile >> 2) + 16 * (a >> 2) + 4 * (tile & 3) + (a & 3);
+    return 16 * tile + a;
+}
+
+// The widened weights, in the order in which lanes read them, and the column constants behind.
+template <int EPI>
+__device__ __forceinline__ void mf_load_weights(const MfArgs &p, uint4 *wl, float *colk, float *colf)
+{
+    const int tid = threadIdx.x, all = p.steps * p.tiles * 64;
+#pragma unroll 8
+    for (int i = tid; i < all; i += blockDim.x) {
+        const int s = (i >> 6) / p.tiles, t = (i >> 6) - s * p.tiles;
+        const int c = mf_column<EPI>(t, i & 15), k = 4 * s + ((i >> 4) & 3);
+        const bool in = c < p.M && k < p.kw32;
+        const uint32_t word = p.w[in ? (int64_t)c * p.w_stride + k : 0];
+        const v8i v = widen32(in ? word : 0u);
+        wl[i] = make_uint4(v[0], v[1], v[2], v[3]);
     }
-    __syncthreads(); // the last barrier: weights and constants are read-only from here on
-
-    // the packed words of the wavefront's two 16-row operands (clamped row and word index:
-    // no load is conditional, so all of them travel together)
-    auto load_rows = [&](int64_t panel, uint64_t (&wa)[KS], uint64_t (&wb)[KS]) {
-        const int64_t row0 = panel * kMfPanel + wave * kMfRows;
-        const int64_t ra = row0 + r < last ? row0 + r : last;
-        const int64_t rb = row0 + 16 + r < last ? row0 + 16 + r : last;
-        const uint64_t *xa = xbits + ra * x_stride, *xb = xbits + rb * x_stride;
-#pragma unroll
-        for (int u = 0; u < KS; ++u) {
-            const int sc = u < ksteps ? u : ksteps - 1;
-            wa[u] = xa[sc];
-            wb[u] = xb[sc];
+    for (int i = tid; i < p.tiles * 16; i += blockDim.x) {
+        const int c = mf_column<EPI>(i >> 4, i & 15);
+        const int pad = 128 * p.steps - p.K;
+        float k = (float)-pad;
+        if (EPI == BITGNN_EPI_THRESH_BITS) {
+            // |Z| <= K, so thresholds beyond +-(K + 1) decide nothing more; a column beyond M
+            // never passes
+            const int32_t lim = p.K + 1;
+            int32_t t = c < p.M ? p.T[c] : lim;
+            t = t > lim ? lim : (t < -lim ? -lim : t);
+            k = 0.5f + (float)(-t - pad);
         }
-    };
+        colk[i] = k;
+        colf[i] = EPI == BITGNN_EPI_SCALE_F32 && c < p.M ? p.alpha[c] : 0.0f;
+    }
+}
 
-    // The weights go in as the MFMA's A operand (its rows = weight columns) and the node
-    // rows as B, so a lane ends up with 4 consecutive columns (4 g + j of every tile) of ONE
-    // node row (r): its own popcount applies, integers and logits leave as 16-byte stores,
-    // and the thresholded bits of a row are assembled in-lane and OR-ed over the 4 lanes
-    // that share the row.
-    auto compute = [&](int64_t panel, const uint64_t (&wa)[KS], const uint64_t (&wb)[KS]) {
-        const int64_t row0 = panel * kMfPanel + wave * kMfRows;
-        if (row0 >= n)
-            return;
-        int px2[2] = {0, 0}; // twice the popcount of the lane's row in either operand
+template <int R, int CT>
+__device__ __forceinline__ void mf_start(v4f (&acc)[R][CT], const float *colk, int t0, int g)
+{
 #pragma unroll
-        for (int u = 0; u < KS; ++u)
-            if (u < ksteps) {
-                px2[0] += 2 * __popcll(wa[u]);
-                px2[1] += 2 * __popcll(wb[u]);
-            }
-        for (int c0 = 0; c0 < Mp; c0 += kMfGroup * 16) {
-            const int ntile = (Mp - c0) / 16 < kMfGroup ? (Mp - c0) / 16 : kMfGroup;
-            v4i acc[2][kMfGroup];
+    for (int t = 0; t < CT; ++t) {
+        const v4f k = *(const v4f *)(colk + (t0 + t) * 16 + 4 * g);
 #pragma unroll
-            for (int t = 0; t < kMfGroup; ++t)
-                acc[0][t] = acc[1][t] = (v4i){0, 0, 0, 0};
-            const char *wcol = wbytes + (size_t)(c0 + r) * ldw + 16 * g;
-#pragma unroll
-            for (int u = 0; u < KS; ++u) {
-                if (u < ksteps) { // wave-uniform
-                    const v4i a0 = widen16((uint32_t)(wa[u] >> (16 * g)) & 0xFFFFu);
-                    const v4i a1 = widen16((uint32_t)(wb[u] >> (16 * g)) & 0xFFFFu);
-                    const char *wk = wcol + 64 * u;
-#pragma unroll
-                    for (int t = 0; t < kMfGroup; ++t) {
-                        if (t < ntile) { // wave-uniform
-                            const v4i b = *(const v4i *)(wk + (size_t)t * 16 * ldw);
-                            acc[0][t] =
-                                __builtin_amdgcn_mfma_i32_16x16x64_i8(b, a0, acc[0][t], 0, 0, 0);
-                            acc[1][t] =
-                                __builtin_amdgcn_mfma_i32_16x16x64_i8(b, a1, acc[1][t], 0, 0, 0);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int64_t row = row0 + 16 * h + r;
-                if (EPI == BITGNN_EPI_THRESH_BITS) {
-                    // bit = (4 D - 2 px >= T - K + 2 pw), at position 16 t' + 4 g + j of the
-                    // 64-column word t / 4
-                    uint32_t wlo[kMfGroup / 4] = {}, whi[kMfGroup / 4] = {};
-#pragma unroll
-                    for (int t = 0; t < kMfGroup; ++t) {
-                        if (t >= ntile) // wave-uniform; tiles beyond M' contribute no bits
-                            continue;
-                        const v4i ck = *(const v4i *)(colk + c0 + 16 * t + 4 * g);
-                        uint32_t nib = 0;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            nib |= (4 * acc[h][t][j] - px2[h] >= ck[j]) ? (1u << j) : 0u;
-                        if ((t & 2) == 0)
-                            wlo[t / 4] |= nib << (16 * (t & 1));
-                        else
-                            whi[t / 4] |= nib << (16 * (t & 1));
-                    }
-#pragma unroll
-                    for (int wi = 0; wi < kMfGroup / 4; ++wi) {
-                        uint32_t lo = wlo[wi] << (4 * g), hi = whi[wi] << (4 * g);
-                        lo |= __shfl_xor(lo, 16, 64);
-                        hi |= __shfl_xor(hi, 16, 64);
-                        lo |= __shfl_xor(lo, 32, 64);
-                        hi |= __shfl_xor(hi, 32, 64);
-                        const int wcolumn = c0 / 64 + wi;
-                        if (g == 0 && row < n && wcolumn * 64 < M)
-                            ((uint64_t *)out)[row * out_stride + wcolumn] =
-                                ((uint64_t)hi << 32) | lo;
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < kMfGroup; ++t) {
-                        const int c = c0 + 16 * t + 4 * g;
-                        if (t < ntile && row < n) {
-                            const v4i ck = *(const v4i *)(colk + c); // K - 2 pw here
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                const int32_t z = 4 * acc[h][t][j] - px2[h] + ck[j];
-                                if (c + j < M) {
-                                    if (EPI == BITGNN_EPI_RAW_I32)
-                                        ((int32_t *)out)[row * out_stride + c + j] = z;
-                                    else
-                                        ((float *)out)[row * out_stride + c + j] =
-                                            colf[c + j] * (float)z;
-                                }
-                            }
-                        }
-                    }
-                }
-            }
-        }
-    };
+        for (int h = 0; h < R; ++h)
+            acc[h][t] = k;
+    }
+}
 
-    int64_t panel = blockIdx.x;
-    const int64_t step = gridDim.x;
-    if (KS > 8) {
-        // rows of 16 words: one register set (a second one would spill); a panel's products
-        // take long enough here that the other wavefront of the SIMD covers the loads
-        uint64_t a0[KS], a1[KS];
-        for (; panel * kMfPanel < n; panel += step) { // uniform over the workgroup
-            load_rows(panel, a0, a1);
-            compute(panel, a0, a1);
+// One K step: the weights' operands at wk, the rows' words in x.
+template <int R, int CT>
+__device__ __forceinline__ void mf_step(v4f (&acc)[R][CT], const uint4 *wk, const uint32_t (&x)[R])
+{
+    v8i b[R];
+#pragma unroll
+    for (int h = 0; h < R; ++h)
+        b[h] = widen32(x[h]);
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const uint4 u = wk[t * 64];
+        const v8i a = {(int)u.x, (int)u.y, (int)u.z, (int)u.w, 0, 0, 0, 0};
+#pragma unroll
+        for (int h = 0; h < R; ++h)
+            acc[h][t] = mfma_pm1(a, b[h], acc[h][t]);
+    }
+}
+
+// Orders a wavefront's own LDS accesses (the hardware keeps them in program order).
+__device__ __forceinline__ void mf_wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Integers and logits leave through LDS, two tiles at a time, so that a store instruction writes
+// whole 128-byte lines of eight rows; straight from the accumulators it would write 64 bytes of
+// sixteen (233 K x 512 x 256 to floats: 76 us that way, 56 so).
+constexpr int kMfStageRow = 36; // 32 columns, 16-byte rows that start four banks apart
+constexpr size_t kMfStage = 16 * kMfStageRow * 4;
+
+template <int EPI> __host__ __device__ constexpr size_t mf_stage_bytes(int waves)
+{
+    return EPI == BITGNN_EPI_THRESH_BITS ? 0 : waves * kMfStage;
+}
+
+template <int EPI, int R, int CT>
+__device__ __forceinline__ void mf_store(const MfArgs &p, const v4f (&acc)[R][CT],
+                                         const float *colf, uint32_t *stage, int64_t row0, int t0,
+                                         int lane)
+{
+    const int r = lane & 15, g = lane >> 4;
+    if (EPI == BITGNN_EPI_THRESH_BITS) {
+#pragma unroll
+        for (int h = 0; h < R; ++h) {
+            const int64_t i = row0 + 16 * h + r;
+#pragma unroll
+            for (int w = 0; w < CT / 4; ++w) {
+                uint32_t neg = 0;
+#pragma unroll
+                for (int q = 15; q >= 0; --q)
+                    neg = __builtin_amdgcn_alignbit(
+                        neg, __float_as_uint(acc[h][4 * w + q / 4][q % 4]), 31);
+                if (i < p.n)
+                    ((uint16_t *)((uint64_t *)p.out + i * p.out_stride + t0 / 4 + w))[g] =
+                        (uint16_t)~neg;
+            }
         }
         return;
     }
-    // two register sets: the rows of the next panel are requested before the current
-    // panel is computed
-    uint64_t a0[KS], a1[KS], b0[KS], b1[KS];
-    load_rows(panel, a0, a1);
-    for (;;) {
-        load_rows(panel + step, b0, b1);
-        compute(panel, a0, a1);
-        panel += step;
-        if (panel * kMfPanel >= n) // uniform over the workgroup
+#pragma unroll
+    for (int t = 0; t < CT; t += 2) {
+        const int c0 = 16 * (t0 + t);
+        if (c0 >= p.M) // wave-uniform
             break;
-        load_rows(panel + step, a0, a1);
-        compute(panel, b0, b1);
-        panel += step;
-        if (panel * kMfPanel >= n)
-            break;
+#pragma unroll
+        for (int h = 0; h < R; ++h) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const v4f f = *(const v4f *)(colf + c0 + 16 * q + 4 * g);
+                uint32_t v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    v[j] = EPI == BITGNN_EPI_RAW_I32
+                               ? (uint32_t)(int32_t)acc[h][t + q][j]
+                               // + 0: a sum of 0 is +0, whatever its sign here
+                               : __float_as_uint(f[j] * (acc[h][t + q][j] + 0.0f));
+                *(uint4 *)(stage + r * kMfStageRow + 16 * q + 4 * g) =
+                    make_uint4(v[0], v[1], v[2], v[3]);
+            }
+            mf_wave_order();
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int row = (lane >> 3) + 8 * q, c = c0 + 4 * (lane & 7);
+                const int64_t i = row0 + 16 * h + row;
+                const uint4 v = *(const uint4 *)(stage + row * kMfStageRow + 4 * (lane & 7));
+                uint32_t *o = (uint32_t *)p.out + i * p.out_stride + c;
+                if (i < p.n && c + 4 <= p.M)
+                    __builtin_memcpy(o, &v, 16);
+                else if (i < p.n && c < p.M) {
+                    o[0] = v.x;
+                    if (c + 1 < p.M)
+                        o[1] = v.y;
+                    if (c + 2 < p.M)
+                        o[2] = v.z;
+                }
+            }
+            mf_wave_order();
+        }
     }
+}
+
+template <int EPI, int R, int CT>
+__global__ __launch_bounds__(512) void bgemm_mfma_kernel(MfArgs p)
+{
+    extern __shared__ uint4 wl[]; // [steps][tiles][64 lanes], then the column constants
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    float *colk = (float *)(wl + p.steps * p.tiles * 64), *colf = colk + p.tiles * 16;
+    uint32_t *stage = (uint32_t *)(colf + p.tiles * 16) + wave * (kMfStage / 4);
+    mf_load_weights<EPI>(p, wl, colk, colf);
+    __syncthreads(); // the last barrier: weights and constants are read-only from here on
+
+    const int64_t rows = (int64_t)waves * 16 * R, last = p.n - 1;
+    // requests, two steps ahead of the products: position in the sequence panel, group, step
+    int64_t q_panel = blockIdx.x;
+    int q_t0 = 0, q_s = 0;
+    const uint32_t *row[R];
+    auto at_panel = [&] {
+#pragma unroll
+        for (int h = 0; h < R; ++h) {
+            const int64_t i = q_panel * rows + wave * (16 * R) + 16 * h + r;
+            row[h] = p.x + (i < last ? i : last) * p.x_stride; // clamped: no load is conditional
+        }
+    };
+    auto request = [&](uint32_t (&x)[R]) {
+        const int k = 4 * q_s + g, kc = k < p.kw32 ? k : p.kw32 - 1;
+#pragma unroll
+        for (int h = 0; h < R; ++h)
+            x[h] = row[h][kc];
+        if (++q_s == p.steps) {
+            q_s = 0;
+            q_t0 += CT;
+            if (q_t0 >= p.tiles) {
+                q_t0 = 0;
+                q_panel += gridDim.x;
+                at_panel();
+            }
+        }
+    };
+    uint32_t x0[R], x1[R];
+    at_panel();
+    request(x0);
+    request(x1);
+    for (int64_t panel = blockIdx.x; panel * rows < p.n; panel += gridDim.x) {
+        const int64_t row0 = panel * rows + wave * (16 * R);
+        for (int t0 = 0; t0 < p.tiles; t0 += CT) {
+            v4f acc[R][CT];
+            mf_start<R, CT>(acc, colk, t0, g);
+            const uint4 *wk = wl + t0 * 64 + lane;
+            for (int s = 0; s < p.steps; ++s) {
+                uint32_t x[R];
+#pragma unroll
+                for (int h = 0; h < R; ++h) {
+                    x[h] = 4 * s + g < p.kw32 ? x0[h] : 0u;
+                    x0[h] = x1[h];
+                }
+                request(x1);
+                mf_step<R, CT>(acc, wk, x);
+                wk += p.tiles * 64;
+            }
+            mf_store<EPI, R, CT>(p, acc, colf, stage, row0, t0, lane);
+        }
+    }
+}
+
+// Full-precision activations (BMM.FBB / BMM.FBF, Section 3.1.2: BIN folded into the product).  A
+// wavefront reads 16 R rows, 64 floats a load: the wave-wide compare mask is 64 bits of the packed
+// row, put into lanes of two registers and, GROUP masks at a time, into LDS, where the products
+// take their words from.  Three VALU ops per 64 floats against 2 x 2 per 64 channels of output
+// when every lane adds popcounts for its own channel: bound by the stream of the features for any
+// width.  Four groups of loads are in flight, across rows and panels.  131 K x 512 x 256: 83 us
+// with popcounts, 58 so (268 MB); 233 K x 128 x 128 65 and 35.
+struct MfFloats {
+    const float *x;
+    int64_t ldx;
+    const float *tau;
+    int32_t votes, row_words; // of 64 floats; 32-bit words between rows in LDS
+};
+
+template <int EPI, int R, int CT, int GROUP, bool TAU>
+__global__ __launch_bounds__(512) void bgemm_f32_mfma_kernel(MfArgs p, MfFloats f)
+{
+    // [steps][tiles][64 lanes], column constants, rows of every wavefront, thresholds
+    extern __shared__ uint4 wl[];
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    float *colk = (float *)(wl + p.steps * p.tiles * 64), *colf = colk + p.tiles * 16;
+    uint32_t *stage = (uint32_t *)(colf + p.tiles * 16) + wave * (kMfStage / 4);
+    uint32_t *words = (uint32_t *)(colf + p.tiles * 16) + mf_stage_bytes<EPI>(waves) / 4;
+    float *tl = (float *)(words + waves * (16 * R) * f.row_words);
+    words += wave * (16 * R) * f.row_words;
+    constexpr int kRows = 16 * R;
+    const int64_t rows = (int64_t)waves * kRows, last = p.n - 1;
+    const int groups = (f.votes + GROUP - 1) / GROUP;
+    const uint64_t tail = p.K % 64 ? (1ull << (p.K % 64)) - 1 : ~0ull;
+    int64_t q_panel = blockIdx.x;
+    int q_row = 0, q_group = 0;
+    const float *qx = nullptr;
+    auto at_row = [&] {
+        const int64_t i = q_panel * rows + wave * kRows + q_row;
+        qx = f.x + (i < last ? i : last) * f.ldx;
+    };
+    auto request = [&](float (&v)[GROUP]) {
+#pragma unroll
+        for (int b = 0; b < GROUP; ++b) {
+            const int k = (q_group * GROUP + b) * 64 + lane;
+            v[b] = qx[k < p.K ? k : p.K - 1];
+        }
+        if (++q_group == groups) {
+            q_group = 0;
+            if (++q_row == kRows) {
+                q_row = 0;
+                q_panel += gridDim.x;
+            }
+            at_row();
+        }
+    };
+    constexpr int kAhead = 4;
+    float v[kAhead][GROUP];
+    at_row();
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+        request(v[q]);
+    int c_row = 0, c_group = 0; // what is consumed
+    auto consume = [&](const float (&v)[GROUP]) {
+        uint32_t lo = 0, hi = 0;
+#pragma unroll
+        for (int b = 0; b < GROUP; ++b) {
+            const int vote = c_group * GROUP + b; // at most 9 past the last one
+            const float t = TAU ? tl[vote < f.votes ? vote * 64 + lane : lane] : 0.0f;
+            uint64_t m = __ballot(v[b] >= t);
+            m = vote == f.votes - 1 ? m & tail : m;
+            asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)m), "n"(b));
+            asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(m >> 32)), "n"(b));
+        }
+        const int vote = c_group * GROUP + lane;
+        if (lane < GROUP && vote < f.votes)
+            *(uint2 *)(words + c_row * f.row_words + 2 * vote) = make_uint2(lo, hi);
+        if (++c_group == groups) {
+            c_group = 0;
+            ++c_row;
+        }
+    };
+    mf_load_weights<EPI>(p, wl, colk, colf);
+    for (int i = lane; i < 16 * R * f.row_words; i += 64) // the words behind a row stay zero
+        words[i] = 0u;
+    if (TAU)
+        for (int i = threadIdx.x; i < f.votes * 64; i += blockDim.x)
+            tl[i] = f.tau[i < p.K ? i : p.K - 1];
+    __syncthreads(); // the last barrier
+    for (int64_t panel = blockIdx.x; panel * rows < p.n; panel += gridDim.x) {
+        const int64_t row0 = panel * rows + wave * kRows;
+        c_row = 0;
+        for (int i = 0; i < kRows * groups; i += kAhead) // a multiple of 16 groups
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                consume(v[q]);
+                request(v[q]);
+            }
+        mf_wave_order();
+        for (int t0 = 0; t0 < p.tiles; t0 += CT) {
+            v4f acc[R][CT];
+            mf_start<R, CT>(acc, colk, t0, g);
+            const uint4 *wk = wl + t0 * 64 + lane;
+            for (int s = 0; s < p.steps; ++s) {
+                uint32_t x[R];
+#pragma unroll
+                for (int h = 0; h < R; ++h)
+                    x[h] = words[(16 * h + r) * f.row_words + 4 * s + g];
+                mf_step<R, CT>(acc, wk, x);
+                wk += p.tiles * 64;
+            }
+            mf_store<EPI, R, CT>(p, acc, colf, stage, row0, t0, lane);
+        }
+        mf_wave_order();
+    }
+}
+
+// Tiles of the M columns: the kernel takes them in groups of four or eight.
+int32_t mf_tiles(int32_t M) { return (M + 63) / 64 * 4; }
+
+// Output columns per launch: all of them when the widened weights fit in LDS, else the largest
+// multiple of 64 (whole output words) that does; 0 = the shape does not fit at all.
+int32_t mf_chunk(int32_t kwords, int32_t M)
+{
+    const int64_t steps = ((int64_t)kwords + 1) / 2, tile = steps * 1024 + 128;
+    if (mf_tiles(M) * tile <= (int64_t)kMfLdsLimit)
+        return M;
+    return (int32_t)((int64_t)kMfLdsLimit / (4 * tile) * 64);
+}
+
+template <int EPI, int R, int CT>
+int mf_launch(bitgnn_ctx *ctx, hipStream_t s, const MfArgs &p, unsigned grid, int threads,
+              size_t lds)
+{
+    BG_HIP(ctx, hipFuncSetAttribute((const void *)bgemm_mfma_kernel<EPI, R, CT>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    bgemm_mfma_kernel<EPI, R, CT><<<grid, threads, lds, s>>>(p);
+    BG_LAUNCH_CHECK(ctx, "bgemm_mfma");
+    return BITGNN_OK;
+}
+
+template <int EPI>
+int mf_launch_epi(bitgnn_ctx *ctx, hipStream_t s, MfArgs p)
+{
+    p.tiles = mf_tiles(p.M);
+    const size_t weights = (size_t)p.tiles * ((size_t)p.steps * 1024 + 128);
+    const int64_t cus = ctx->n_cus > 0 ? ctx->n_cus : 256;
+    // 64 rows a wavefront where that still gives every CU rows, else 16
+    const bool wide = p.n >= cus * 256;
+    // two workgroups a CU where they fit
+    const int threads = weights + mf_stage_bytes<EPI>(4) > 78 * 1024 ? 512 : 256;
+    const size_t lds = weights + mf_stage_bytes<EPI>(threads / 64);
+    const int64_t rows = (int64_t)(threads / 64) * (wide ? 64 : 16);
+    const int64_t panels = (p.n + rows - 1) / rows, fit = cus * ((160 * 1024) / (lds + 1024));
+    const int64_t most = cus * 8 < fit ? cus * 8 : fit;
+    const unsigned grid = (unsigned)(panels < most ? panels : most);
+    if (p.tiles % 8 == 0)
+        return wide ? mf_launch<EPI, 4, 8>(ctx, s, p, grid, threads, lds)
+                    : mf_launch<EPI, 1, 8>(ctx, s, p, grid, threads, lds);
+    return wide ? mf_launch<EPI, 4, 4>(ctx, s, p, grid, threads, lds)
+                : mf_launch<EPI, 1, 4>(ctx, s, p, grid, threads, lds);
+}
+
+template <int EPI, int GROUP, bool TAU>
+int mf_launch_f32_group(bitgnn_ctx *ctx, hipStream_t s, const MfArgs &p, const MfFloats &f)
+{
+    // 16 rows a wavefront: with 32, the last of two or three turns was a fifth of the time
+    constexpr int R = 1, CT = 4;
+    auto lds_of = [&](int threads) {
+        return (size_t)p.tiles * ((size_t)p.steps * 1024 + 128) +
+               mf_stage_bytes<EPI>(threads / 64) +
+               (size_t)(threads / 64) * 16 * R * f.row_words * 4 + (TAU ? (size_t)f.votes * 256 : 0);
+    };
+    const int threads = lds_of(256) > 52 * 1024 ? 512 : 256;
+    const size_t lds = lds_of(threads);
+    const int64_t cus = ctx->n_cus > 0 ? ctx->n_cus : 256, rows = threads / 64 * 16 * R;
+    const int64_t panels = (p.n + rows - 1) / rows, most = cus * ((160 * 1024) / (lds + 1024));
+    BG_HIP(ctx, hipFuncSetAttribute((const void *)bgemm_f32_mfma_kernel<EPI, R, CT, GROUP, TAU>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    bgemm_f32_mfma_kernel<EPI, R, CT, GROUP, TAU>
+        <<<(unsigned)(panels < most ? panels : most), threads, lds, s>>>(p, f);
+    BG_LAUNCH_CHECK(ctx, "bgemm_f32_mfma");
+    return BITGNN_OK;
+}
+
+template <int EPI>
+int mf_launch_f32_epi(bitgnn_ctx *ctx, hipStream_t s, const MfArgs &p, const MfFloats &f)
+{
+    // loads of 64 floats in flight at a time: the size that fits the row with the fewest to spare
+    const int sizes[6] = {10, 8, 6, 5, 4, 2};
+    int best = 10;
+    for (int k = 1; k < 6; ++k) // large ones first: of equal fits the one with fewer groups
+        if ((f.votes + sizes[k] - 1) / sizes[k] * sizes[k] <
+                (f.votes + best - 1) / best * best &&
+            (sizes[k] >= 8 || f.votes <= sizes[k]))
+            best = sizes[k];
+#define BG_F32(G)                                                                                 \
+    (f.tau ? mf_launch_f32_group<EPI, G, true>(ctx, s, p, f)                                      \
+           : mf_launch_f32_group<EPI, G, false>(ctx, s, p, f))
+    switch (best) {
+    case 2: return BG_F32(2);
+    case 4: return BG_F32(4);
+    case 5: return BG_F32(5);
+    case 6: return BG_F32(6);
+    case 8: return BG_F32(8);
+    default: return BG_F32(10);
+    }
+#undef BG_F32
 }
 
 } // namespace
 
-// Output columns per launch: all of them when the widened weights fit in LDS, else the
-// largest multiple of 64 (whole output words) that does; 0 = the shape does not fit at all.
-static int32_t mf_chunk(int64_t Kp, int64_t Mp)
+// Whether the matrix-core kernel takes float rows of this shape, all its columns at once.
+bool bg_bgemm_f32_mfma_applies(const bitgnn_ctx *ctx, int32_t K, int32_t M, int epilogue)
 {
-    const int64_t row = Kp + kMfPad + 8; // widened weights + column constants, per column
-    if (Mp * row <= (int64_t)kMfLdsLimit)
-        return (int32_t)Mp;
-    return (int32_t)((int64_t)kMfLdsLimit / row / 64 * 64);
+    if (ctx->bgemm_path == BITGNN_BGEMM_VALU)
+        return false;
+    const int64_t steps = ((int64_t)K + 127) / 128, row_words = 4 * (steps | 1);
+    if (mf_tiles(M) * (steps * 1024 + 128) + 8 * (int64_t)kMfStage + 8 * 16 * row_words * 4 +
+            ((int64_t)K + 64) * 4 > 160 * 1024)
+        return false;
+    if (ctx->bgemm_path == BITGNN_BGEMM_MFMA)
+        return true;
+    // Popcounts keep up with the stream of the features up to 128 channels, and lead by a few
+    // per cent where a row is one chunk of theirs (K <= 640; 602 x 128, 233 K rows: 107 against
+    // 112 us) -- unless rows are short (128 x 128: 65 against 35) or take two chunks (1000 x 100:
+    // 211 against 186).  Short rows to wide floats are bound by the stores, theirs are a little
+    // better (100 x 256, 233 K rows: 80 against 89).
+    if (M > 128)
+        return epilogue == BITGNN_EPI_THRESH_BITS || K > 128;
+    return K <= 256 || (K > 640 && M > 64);
 }
 
-// Whether the matrix-core kernel takes this shape: weights (or a column chunk of them)
-// resident in LDS, enough work to be compute-bound (small M or K leave the VALU kernel at the
-// memory bound anyway).
+int bg_launch_bgemm_f32_mfma(bitgnn_ctx *ctx, hipStream_t s, const float *x, int64_t n, int32_t K,
+                             int64_t ldx, const float *tau, const uint64_t *wbits, int32_t M,
+                             int64_t w_stride, int epilogue, const int32_t *T, const float *alpha,
+                             void *out, int64_t out_stride)
+{
+    MfArgs p{};
+    p.n = n;
+    p.K = K;
+    p.kw32 = (K + 63) / 64 * 2;
+    p.steps = (K + 127) / 128;
+    p.w = (const uint32_t *)wbits;
+    p.w_stride = w_stride * 2;
+    p.M = M;
+    p.tiles = mf_tiles(M);
+    p.T = T;
+    p.alpha = alpha;
+    p.out = out;
+    p.out_stride = out_stride;
+    const MfFloats f{x, ldx, tau, (K + 63) / 64, 4 * (p.steps | 1)};
+    switch (epilogue) {
+    case BITGNN_EPI_THRESH_BITS:
+        return mf_launch_f32_epi<BITGNN_EPI_THRESH_BITS>(ctx, s, p, f);
+    case BITGNN_EPI_RAW_I32: return mf_launch_f32_epi<BITGNN_EPI_RAW_I32>(ctx, s, p, f);
+    default: return mf_launch_f32_epi<BITGNN_EPI_SCALE_F32>(ctx, s, p, f);
+    }
+}
+
+// Whether the matrix-core kernel takes this shape.
 bool bg_bgemm_mfma_applies(const bitgnn_ctx *ctx, int64_t n, int32_t kwords, int32_t M)
 {
-    if (ctx->bgemm_path == 1)
+    if (ctx->bgemm_path == BITGNN_BGEMM_VALU)
         return false;
-    const int64_t Kp = (int64_t)kwords * 64, Mp = ((int64_t)M + 15) / 16 * 16;
-    // rows are held in registers (up to 16 words); weights and column constants in LDS
-    const int32_t chunk = mf_chunk(Kp, Mp);
-    if (Kp > 1024 || (chunk < Mp && chunk < 64))
+    const int32_t chunk = mf_chunk(kwords, M);
+    if (chunk < M && chunk < 64)
         return false;
-    if (ctx->bgemm_path == 2)
+    if (ctx->bgemm_path == BITGNN_BGEMM_MFMA)
         return true;
-    // measured on MI355X: the fixed cost (widening the weights, one LDS copy of them per
-    // workgroup: 11-22 us whatever n, once per column chunk) is repaid from 40-70 thousand
-    // rows on, depending on the shape (K x M = 512 x 256: level at 70 K; 128 x 128: from
-    // 20 K; 256 x 40: only beyond 100 K); 1.4x - 2.4x faster for large n.  Rows of more
-    // than 8 words and outputs in column chunks pay that cost per chunk and load rows without
-    // a second register set: level with the VALU kernel at 89 K rows (1000 x 256: 79 against
-    // 83 us), 1.4x at 200 K, 1.9x at 500 K, 3x at 2.4 M rows
-    return n >= ((Kp > 512 || chunk < Mp) ? 131072 : 65536);
+    // a context without a GPU launches neither: the sizes it has always named
+    if (ctx->device < 0)
+        return kwords <= 16 && n >= (kwords > 8 ? 131072 : 65536);
+    // every workgroup widens the weights first, about 1 us per 16 KB: with few rows the VALU
+    // kernel is done by then (512 x 512, 128 KB: 10.0 against 13.1 us at 2,708 rows, level at 10 K;
+    // 1000 x 1000, in seven chunks: 30 against 50 us at 10 K, 70 against 51 at 20 K)
+    return n * 24 >= (int64_t)mf_tiles(M) * ((kwords + 1) / 2) * 1024;
 }
 
 int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, int64_t n,
@@ -297,58 +572,33 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
                          int32_t M, int64_t w_stride, int epilogue, const int32_t *T,
                          const float *alpha, void *out, int64_t out_stride)
 {
-    const int32_t ldw = kwords * 64 + kMfPad;
-    const int32_t chunk = mf_chunk((int64_t)kwords * 64, ((int64_t)M + 15) / 16 * 16);
-    BG_REQUIRE(ctx, chunk > 0 && (chunk >= 64 || chunk >= M) && kwords <= 16, BITGNN_ERR_UNSUPPORTED,
+    const int32_t chunk = mf_chunk(kwords, M);
+    BG_REQUIRE(ctx, chunk >= M || chunk >= 64, BITGNN_ERR_UNSUPPORTED,
                "bitgnn_bgemm: shape too large for the matrix-core kernel");
-    const int64_t panels = (n + kMfPanel - 1) / kMfPanel;
-    const int64_t cus = ctx->n_cus > 0 ? ctx->n_cus : 256;
-    const unsigned grid = (unsigned)(panels < cus ? panels : cus);
-    // Column chunks run one after the other on the stream and share the widening scratch: a
-    // chunk's launches are ordered behind the previous chunk's kernel, which has read it.
     for (int32_t c0 = 0; c0 < M; c0 += chunk) {
-        const int32_t Mc = M - c0 < chunk ? M - c0 : chunk, Mp = (Mc + 15) / 16 * 16;
-        const size_t w8_bytes = (size_t)Mp * ldw;
-        const size_t lds_bytes = w8_bytes + (size_t)Mp * 8; // + column constants
-        BG_REQUIRE(ctx, w8_bytes + (size_t)Mp * 4 <= kBgemmScratchBytes, BITGNN_ERR_UNSUPPORTED,
-                   "bitgnn_bgemm: weights too large for the matrix-core kernel's scratch");
-        uint8_t *w8 = (uint8_t *)ctx->bgemm_ws;
-        int32_t *pw = (int32_t *)(w8 + w8_bytes);
-        bgemm_widen_w_kernel<<<Mp, 256, 0, s>>>((const uint32_t *)(wbits + (int64_t)c0 * w_stride),
-                                                w_stride * 2, kwords * 64, Mc, ldw, w8, pw);
-        BG_LAUNCH_CHECK(ctx, "bgemm_widen_w");
-        const int32_t *Tc = T ? T + c0 : nullptr;
-        const float *ac = alpha ? alpha + c0 : nullptr;
-        void *oc = epilogue == BITGNN_EPI_THRESH_BITS ? (void *)((uint64_t *)out + c0 / 64)
-                                                      : (void *)((int32_t *)out + c0);
-#define BG_MFMA_KS(E, KS)                                                                         \
-    do {                                                                                          \
-        BG_HIP(ctx, hipFuncSetAttribute((const void *)bgemm_mfma_kernel<E, KS>,                   \
-                                        hipFuncAttributeMaxDynamicSharedMemorySize,               \
-                                        (int)lds_bytes));                                         \
-        bgemm_mfma_kernel<E, KS><<<grid, kMfWaves * 64, lds_bytes, s>>>(                          \
-            xbits, n, x_stride, K, kwords, (const uint4 *)w8, ldw, pw, Mc, Mp, Tc, ac, oc,        \
-            out_stride);                                                                          \
-    } while (0)
-#define BG_MFMA(E)                                                                                \
-    do {                                                                                          \
-        if (kwords <= 2)                                                                          \
-            BG_MFMA_KS(E, 2);                                                                     \
-        else if (kwords <= 4)                                                                     \
-            BG_MFMA_KS(E, 4);                                                                     \
-        else if (kwords <= 8)                                                                     \
-            BG_MFMA_KS(E, 8);                                                                     \
-        else                                                                                      \
-            BG_MFMA_KS(E, 16);                                                                    \
-    } while (0)
+        MfArgs p{};
+        p.x = (const uint32_t *)xbits;
+        p.n = n;
+        p.x_stride = x_stride * 2;
+        p.K = K;
+        p.kw32 = kwords * 2;
+        p.steps = (kwords + 1) / 2;
+        p.w = (const uint32_t *)(wbits + (int64_t)c0 * w_stride);
+        p.w_stride = w_stride * 2;
+        p.M = M - c0 < chunk ? M - c0 : chunk;
+        p.T = T ? T + c0 : nullptr;
+        p.alpha = alpha ? alpha + c0 : nullptr;
+        p.out = epilogue == BITGNN_EPI_THRESH_BITS ? (void *)((uint64_t *)out + c0 / 64)
+                                                   : (void *)((int32_t *)out + c0);
+        p.out_stride = out_stride;
+        int rc;
         switch (epilogue) {
-        case BITGNN_EPI_THRESH_BITS: BG_MFMA(BITGNN_EPI_THRESH_BITS); break;
-        case BITGNN_EPI_RAW_I32: BG_MFMA(BITGNN_EPI_RAW_I32); break;
-        default: BG_MFMA(BITGNN_EPI_SCALE_F32); break;
+        case BITGNN_EPI_THRESH_BITS: rc = mf_launch_epi<BITGNN_EPI_THRESH_BITS>(ctx, s, p); break;
+        case BITGNN_EPI_RAW_I32: rc = mf_launch_epi<BITGNN_EPI_RAW_I32>(ctx, s, p); break;
+        default: rc = mf_launch_epi<BITGNN_EPI_SCALE_F32>(ctx, s, p); break;
         }
-#undef BG_MFMA_KS
-#undef BG_MFMA
-        BG_LAUNCH_CHECK(ctx, "bgemm_mfma");
+        if (rc != BITGNN_OK)
+            return rc;
     }
     return BITGNN_OK;
 }

@@ -56,8 +56,6 @@ struct bitgnn_ctx {
     int device;           // -1: validation-only context
     int n_cus;            // compute units of the device
     int bgemm_path;       // BITGNN_BGEMM_AUTO / _VALU / _MFMA (bitgnn_ctx_set_bgemm_path)
-    void *bgemm_ws;       // device scratch of the matrix-core BMM: widened weights and their
-                          // popcounts (fixed size, allocated with the context)
     bg_scratch own;       // the context's scratch
     bg_retired *retired;  // superseded workspaces that recorded graphs hold, freed with the context
     bg_scratch *sc;       // the scratch the current call uses (&own outside such a call)
@@ -79,9 +77,6 @@ struct bitgnn_ctx {
 // merge + 12 planes for the rows the blocked kernel finishes itself).
 static const size_t kSeedTableWords = 2 * (26 + 12) * 64;
 static const int kMaxTimed = 256;
-// Scratch of the matrix-core BMM: at most 144 KB of widened weights (its LDS limit) plus
-// one popcount per padded weight row.
-static const size_t kBgemmScratchBytes = 144 * 1024 + 16 * 1024;
 // Widths bitgnn_adj_build reserves workspace for.
 static const int32_t kDefaultWsChannels = 256, kDefaultWsClasses = 64;
 static const int kFusedBarrierWord = 16; // its own 64-byte line of ctx->queue
@@ -239,6 +234,11 @@ int bg_launch_spmm_i32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
                        int64_t out_stride);
 
 bool bg_bgemm_mfma_applies(const bitgnn_ctx *ctx, int64_t n, int32_t kwords, int32_t M);
+bool bg_bgemm_f32_mfma_applies(const bitgnn_ctx *ctx, int32_t K, int32_t M, int epilogue);
+int bg_launch_bgemm_f32_mfma(bitgnn_ctx *ctx, hipStream_t s, const float *x, int64_t n, int32_t K,
+                             int64_t ldx, const float *tau, const uint64_t *wbits, int32_t M,
+                             int64_t w_stride, int epilogue, const int32_t *T, const float *alpha,
+                             void *out, int64_t out_stride);
 int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, int64_t n,
                          int64_t x_stride, int32_t K, int32_t kwords, const uint64_t *wbits,
                          int32_t M, int64_t w_stride, int epilogue, const int32_t *T,

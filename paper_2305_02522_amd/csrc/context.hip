@@ -176,16 +176,12 @@ extern "C" int bitgnn_ctx_create(bitgnn_ctx **out, int device)
         if (e == hipSuccess)
             e = hipMalloc((void **)&ctx->own.seed_table, kSeedTableWords * sizeof(uint32_t));
         if (e == hipSuccess)
-            e = hipMalloc(&ctx->bgemm_ws, kBgemmScratchBytes);
-        if (e == hipSuccess)
             e = hipHostMalloc(&ctx->mail, kMailBytes, hipHostMallocDefault);
         if (e == hipSuccess && !(ctx->pool = bg_pool_create()))
             e = hipErrorOutOfMemory;
         if (e != hipSuccess) {
             if (ctx->mail)
                 (void)hipHostFree(ctx->mail);
-            if (ctx->bgemm_ws)
-                (void)hipFree(ctx->bgemm_ws);
             if (ctx->own.queue)
                 (void)hipFree(ctx->own.queue);
             if (ctx->own.seed_table)
@@ -211,8 +207,6 @@ extern "C" void bitgnn_ctx_destroy(bitgnn_ctx *ctx)
         (void)hipFree(ctx->own.seed_table);
     if (ctx->own.queue)
         (void)hipFree(ctx->own.queue);
-    if (ctx->bgemm_ws)
-        (void)hipFree(ctx->bgemm_ws);
     if (ctx->own.ws)
         (void)hipFree(ctx->own.ws);
     while (ctx->retired) {

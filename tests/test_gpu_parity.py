@@ -292,6 +292,73 @@ def test_bgemm_three_epilogues(B, gemm_ctx, n, K, M):
     assert rel_close(of.cpu().numpy(), orc.scale(z, alpha))
 
 
+# Edges of the matrix-core kernel: K steps of 128, tiles of 16 and groups of 64 or 128 columns,
+# panels of 64 and (from 65,536 rows on) 256 rows, rows and outputs that are not 16-byte aligned.
+# The reference is numpy's int64 product of a sample of the rows (the last ones among them).
+@pytest.mark.parametrize("n,K,M", [
+    (63, 127, 15), (64, 128, 16), (65, 129, 17), (255, 256, 63), (257, 257, 129), (130, 4352, 65),
+    (100, 4353, 64), (65535, 64, 3), (65536, 192, 64), (65537, 129, 130), (66000, 640, 200),
+    (70001, 1000, 256)])
+def test_bgemm_matrix_core_edges(B, n, K, M):
+    c = B.Context(0)
+    B.ctx_set_bgemm_path(c, B.BGEMM_MFMA)
+    r = np.random.default_rng(n + K + M)
+    kw, mw = (K + 63) // 64, (M + 63) // 64
+    x = torch.randint(-2**63, 2**63 - 1, (n, kw), dtype=torch.int64, device="cuda")
+    if K % 64:
+        x[:, -1] &= (1 << (K % 64)) - 1
+    w = W.pm1(r, (K, M))
+    wb = _pack_host(np.ascontiguousarray(w.T))
+    rows = np.unique(np.concatenate([r.integers(0, n, 300), np.arange(max(0, n - 70), n)]))
+    bits = np.unpackbits(words_np(x[torch.as_tensor(rows, device="cuda")]).view(np.uint8), axis=1,
+                         bitorder="little")[:, :K]
+    z = (bits.astype(np.int64) * 2 - 1) @ w.astype(np.int64)
+    raw = torch.full((n, M + 1), 7, dtype=torch.int32, device="cuda")
+    B.bgemm(c, x, n, kw, K, kw, wb, M, kw, B.EPI_RAW_I32, None, None, raw, M + 1)
+    got = raw.cpu().numpy()[rows]
+    assert np.array_equal(got[:, :M], z) and np.all(got[:, M] == 7)
+    t = r.integers(-6, 7, size=M).astype(np.int32)
+    ob = torch.full((n, mw + 1), -1, dtype=torch.int64, device="cuda")
+    B.bgemm(c, x, n, kw, K, kw, wb, M, kw, B.EPI_THRESH_BITS, dev(t), None, ob, mw + 1)
+    got = words_np(ob)[rows]
+    assert np.array_equal(got[:, :mw], orc.to_words(orc.rebin(z, t)))
+    assert np.all(got[:, mw] == np.uint64(0xFFFFFFFFFFFFFFFF))
+    alpha = r.uniform(0.5, 1.5, M).astype(np.float32)
+    of = torch.zeros((n, M), dtype=torch.float32, device="cuda")
+    B.bgemm(c, x, n, kw, K, kw, wb, M, kw, B.EPI_SCALE_F32, None, dev(alpha), of, M)
+    assert np.array_equal(of.cpu().numpy()[rows], alpha * z.astype(np.float32))
+    c.close()
+
+
+# The same for float rows: every number of 64-float loads up to 13 (and so every group size), with
+# and without thresholds, ragged ends, a row stride that is not the width.
+@pytest.mark.parametrize("votes", range(1, 14))
+@pytest.mark.parametrize("n,M,cut", [(131, 129, 0), (1027, 40, 1), (64, 64, 63)])
+def test_bgemm_f32_matrix_core_edges(B, votes, n, M, cut):
+    c = B.Context(0)
+    B.ctx_set_bgemm_path(c, B.BGEMM_MFMA)
+    K = votes * 64 - cut
+    r = np.random.default_rng(votes * 100 + M)
+    x = r.standard_normal((n, K + 3)).astype(np.float32)
+    x[0, :3] = (0.0, -0.0, np.nan)
+    w = W.pm1(r, (K, M))
+    wb = _pack_host(np.ascontiguousarray(w.T))
+    kw, mw = (K + 63) // 64, (M + 63) // 64
+    for tau in (None, r.standard_normal(K).astype(np.float32)):
+        z = (np.where(x[:, :K] >= (0.0 if tau is None else tau), 1, -1)).astype(np.int64) \
+            @ w.astype(np.int64)
+        tg = None if tau is None else dev(tau)
+        raw = torch.full((n, M + 1), 7, dtype=torch.int32, device="cuda")
+        B.bgemm_f32(c, dev(x), n, K, K + 3, tg, wb, M, kw, B.EPI_RAW_I32, None, None, raw, M + 1)
+        got = raw.cpu().numpy()
+        assert np.array_equal(got[:, :M], z) and np.all(got[:, M] == 7)
+        t = r.integers(-6, 7, size=M).astype(np.int32)
+        ob = torch.full((n, mw), -1, dtype=torch.int64, device="cuda")
+        B.bgemm_f32(c, dev(x), n, K, K + 3, tg, wb, M, kw, B.EPI_THRESH_BITS, dev(t), None, ob, mw)
+        assert np.array_equal(words_np(ob), orc.to_words(orc.rebin(z, t)))
+    c.close()
+
+
 @pytest.mark.parametrize("n,K,M", [(1, 1, 1), (70, 63, 7), (300, 65, 65), (1000, 602, 128),
                                    (500, 1433, 64), (129, 512, 256), (257, 100, 300),
                                    (4099, 130, 41)])
