@@ -89,6 +89,11 @@ __global__ __launch_bounds__(kWaves * 64) void bgemm_kernel(
         for (int r = 0; r < kRows; ++r)
             if (c_ok && row0 + r < n)
                 ((int32_t *)out)[(row0 + r) * out_stride + c] = K - 2 * acc[r];
+    } else if (EPI == kEpiRawI16) {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+            if (c_ok && row0 + r < n)
+                ((int16_t *)out)[(row0 + r) * out_stride + c] = (int16_t)(K - 2 * acc[r]);
     } else {
         const float a = c_ok ? alpha[c] : 0.0f;
 #pragma unroll
@@ -167,6 +172,9 @@ __device__ __forceinline__ void f32_finish_row(int r, int64_t row, bool row_ok, 
         } else if (EPI == BITGNN_EPI_RAW_I32) {
             if (c_ok[t] && row_ok)
                 ((int32_t *)out)[row * out_stride + c] = z;
+        } else if (EPI == kEpiRawI16) {
+            if (c_ok[t] && row_ok)
+                ((int16_t *)out)[row * out_stride + c] = (int16_t)z;
         } else {
             if (c_ok[t] && row_ok)
                 ((float *)out)[row * out_stride + c] = al[t] * (float)z;
@@ -385,6 +393,10 @@ int bg_launch_bgemm(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, int64
         bgemm_kernel<BITGNN_EPI_RAW_I32><<<grid, block, 0, s>>>(
             x32, n, x_stride * 2, K, kw32, w32, M, w_stride * 2, T, alpha, out, out_stride);
         break;
+    case kEpiRawI16:
+        bgemm_kernel<kEpiRawI16><<<grid, block, 0, s>>>(
+            x32, n, x_stride * 2, K, kw32, w32, M, w_stride * 2, T, alpha, out, out_stride);
+        break;
     default:
         bgemm_kernel<BITGNN_EPI_SCALE_F32><<<grid, block, 0, s>>>(
             x32, n, x_stride * 2, K, kw32, w32, M, w_stride * 2, T, alpha, out, out_stride);
@@ -463,6 +475,10 @@ int bg_launch_bgemm_f32(bitgnn_ctx *ctx, hipStream_t s, const float *x, int64_t 
     case BITGNN_EPI_RAW_I32:
         launch_bgemm_f32_tiles<BITGNN_EPI_RAW_I32>(s, n, M, x, K, ldx, tau, kw32, w32,
                                                    w_stride * 2, T, alpha, out, out_stride);
+        break;
+    case kEpiRawI16:
+        launch_bgemm_f32_tiles<kEpiRawI16>(s, n, M, x, K, ldx, tau, kw32, w32, w_stride * 2, T,
+                                           alpha, out, out_stride);
         break;
     default:
         launch_bgemm_f32_tiles<BITGNN_EPI_SCALE_F32>(s, n, M, x, K, ldx, tau, kw32, w32,

@@ -184,6 +184,35 @@ __device__ __forceinline__ void mf_store(const MfArgs &p, const v4f (&acc)[R][CT
         }
         return;
     }
+    if (EPI == kEpiRawI16) { // four tiles are 128 bytes of a row
+#pragma unroll
+        for (int t = 0; t < CT; t += 4) {
+            if (16 * (t0 + t) >= p.M) // wave-uniform
+                break;
+#pragma unroll
+            for (int h = 0; h < R; ++h) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    int16_t v[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        v[j] = (int16_t)(int32_t)acc[h][t + q][j];
+                    __builtin_memcpy(stage + r * kMfStageRow + 8 * q + 2 * g, v, 8);
+                }
+                mf_wave_order();
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int row = (lane >> 3) + 8 * q, c = 16 * (t0 + t) + 8 * (lane & 7);
+                    const int64_t i = row0 + 16 * h + row;
+                    const uint4 v = *(const uint4 *)(stage + row * kMfStageRow + 4 * (lane & 7));
+                    if (i < p.n && c < p.M) // rows are padded to 16 bytes
+                        *(uint4 *)((int16_t *)p.out + i * p.out_stride + c) = v;
+                }
+                mf_wave_order();
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int t = 0; t < CT; t += 2) {
         const int c0 = 16 * (t0 + t);
@@ -544,6 +573,7 @@ int bg_launch_bgemm_f32_mfma(bitgnn_ctx *ctx, hipStream_t s, const float *x, int
     case BITGNN_EPI_THRESH_BITS:
         return mf_launch_f32_epi<BITGNN_EPI_THRESH_BITS>(ctx, s, p, f);
     case BITGNN_EPI_RAW_I32: return mf_launch_f32_epi<BITGNN_EPI_RAW_I32>(ctx, s, p, f);
+    case kEpiRawI16: return mf_launch_f32_epi<kEpiRawI16>(ctx, s, p, f);
     default: return mf_launch_f32_epi<BITGNN_EPI_SCALE_F32>(ctx, s, p, f);
     }
 }
@@ -589,12 +619,14 @@ int bg_launch_bgemm_mfma(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, 
         p.T = T ? T + c0 : nullptr;
         p.alpha = alpha ? alpha + c0 : nullptr;
         p.out = epilogue == BITGNN_EPI_THRESH_BITS ? (void *)((uint64_t *)out + c0 / 64)
+                : epilogue == kEpiRawI16           ? (void *)((int16_t *)out + c0)
                                                    : (void *)((int32_t *)out + c0);
         p.out_stride = out_stride;
         int rc;
         switch (epilogue) {
         case BITGNN_EPI_THRESH_BITS: rc = mf_launch_epi<BITGNN_EPI_THRESH_BITS>(ctx, s, p); break;
         case BITGNN_EPI_RAW_I32: rc = mf_launch_epi<BITGNN_EPI_RAW_I32>(ctx, s, p); break;
+        case kEpiRawI16: rc = mf_launch_epi<kEpiRawI16>(ctx, s, p); break;
         default: rc = mf_launch_epi<BITGNN_EPI_SCALE_F32>(ctx, s, p); break;
         }
         if (rc != BITGNN_OK)

@@ -215,6 +215,11 @@ static inline bool bg_aligned(const void *p, size_t a) { return ((uintptr_t)p % 
                                "arguments valid; context has no GPU");                            \
     } while (0)
 
+// Epilogue of the BMMs beside the public ones: the raw integers as int16 rows (K <= 32767).  Rows
+// are 16-byte aligned (out_stride counts int16 elements); the elements behind the last column of a
+// row are unspecified.
+static const int kEpiRawI16 = 3;
+
 // Internal launchers shared across translation units (arguments already validated).
 int bg_launch_bgemm(bitgnn_ctx *ctx, hipStream_t s, const uint64_t *xbits, int64_t n,
                     int64_t x_stride, int32_t K, int32_t kwords, const uint64_t *wbits, int32_t M,

@@ -1152,6 +1152,46 @@ def test_gcn_out_layer_digit_counts(B, ctx, n, e, K, M, kind):
     adj.close()
 
 
+# Layouts of the int16 rows between product and aggregation: widths around their row sizes, few
+# nodes, scratch that does not start at a cache line, and widths they do not fit.  Must equal the
+# float rows of the scaled product aggregated by the public calls, bit for bit.
+@pytest.mark.parametrize("M", [1, 3, 4, 7, 8, 9, 16, 17, 32, 33, 63, 64, 65, 100, 130])
+@pytest.mark.parametrize("n,e,shift", [(1, 0, 0), (40, 200, 1), (3001, 20000, 0), (3001, 20000, 3)])
+def test_full_precision_rows_between_product_and_aggregation(B, gemm_ctx, M, n, e, shift):
+    ctx = gemm_ctx
+    r = np.random.default_rng(M * 10 + shift)
+    src, dst = W.random_graph(r, n, e)
+    s = dev(src) if e else None
+    adj = B.adj_build(ctx, s, dev(dst) if e else None, e, n, SYM_LOOPS)
+    K, kw = 100, 2
+    x = dev(r.standard_normal((n, K)).astype(np.float32))
+    xb = torch.zeros((n, kw), dtype=torch.int64, device="cuda")
+    B.pack_f32(ctx, x, n, K, K, None, xb, kw)
+    wb = _pack_host(np.ascontiguousarray(W.pm1(r, (K, M)).T))
+    alpha, tau = dev(r.uniform(0.5, 1.5, M).astype(np.float32)), dev(r.standard_normal(M)
+                                                                     .astype(np.float32))
+    d = dev(r.uniform(0.1, 1.0, n).astype(np.float32))
+    z = torch.empty((n, M), device="cuda")
+    B.bgemm(ctx, xb, n, kw, K, kw, wb, M, kw, B.EPI_SCALE_F32, None, alpha, z, M)
+    y = torch.empty((n, M), device="cuda")
+    B.spmm_f32(ctx, adj, z, False, M, M, d, d, B.EPI_SCALE_F32, None, y, M)
+    mw = (M + 63) // 64
+    want = torch.zeros((n, mw), dtype=torch.int64, device="cuda")
+    B.spmm_f32(ctx, adj, z, False, M, M, d, d, B.EPI_THRESH_BITS, tau, want, mw)
+    tmp = torch.empty(n * M + 4, device="cuda")[shift:]
+    got = torch.full((n, M), 7.0, device="cuda")
+    B.gcn_out_layer_weighted(ctx, adj, xb, kw, K, kw, wb, M, kw, alpha, d, d, tmp, got, M)
+    assert torch.equal(got, y)
+    for bits in (False, True):
+        out = torch.full((n, mw), -1, dtype=torch.int64, device="cuda")
+        if bits:
+            B.gcn_layer_full(ctx, adj, xb, kw, K, kw, wb, M, kw, alpha, d, d, tau, tmp, out, mw)
+        else:
+            B.gcn_layer_full_f32(ctx, adj, x, K, K, None, wb, M, kw, alpha, d, d, tau, tmp, out, mw)
+        assert torch.equal(out, want)
+    adj.close()
+
+
 @pytest.mark.parametrize("n,e,K,M", [(300, 2500, 70, 40), (4000, 60000, 128, 128),
                                      (2500, 30000, 200, 65)])
 def test_weighted_layers(B, ctx, n, e, K, M):
