@@ -332,9 +332,9 @@ int bitgnn_gcn_layer_f32(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *adj, c
                          uint64_t *tmp_bits, uint64_t *out_bits, int64_t out_stride);
 /* GCN output layer, BMM.BBF + BSpMM.FBF with one scale at the end:
  *   logits = alpha * (A_hat (xbits W)).  tmp_i32: caller scratch int32 [N][M].
- * No non-linearity sits between the two products, so when the handle has the
- * column-blocked form and K <= 128 the call evaluates (A_hat xbits) W instead: the
- * same integers, aggregated on 1-bit rows. */
+ * No non-linearity sits between the two products, so where the handle has the
+ * column-blocked form and that is expected to be faster the call evaluates
+ * (A_hat xbits) W instead: the same integers, aggregated on 1-bit rows. */
 int bitgnn_gcn_out_layer(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *adj,
                          const uint64_t *xbits, int64_t x_stride, int32_t K, int32_t kwords,
                          const uint64_t *wbits, int32_t M, int64_t w_stride, const float *alpha,

@@ -541,6 +541,109 @@ __global__ __launch_bounds__(kBlock) void spmm_i32_wide_kernel(
     }
 }
 
+// Integer sums of int16 rows, a team of G lanes (8 to 64, a power of two) per virtual row: a lane
+// holds 8 channels (16 bytes), `lr` lanes a neighbour's row, so the team gathers G / lr neighbours
+// per instruction.  A row's time is its chain of loads (order, row pointers, ids, rows) and a
+// wavefront of several rows walks several of them at once; sums stay packed 16-bit adds, which
+// wrap, for `flush` blocks of ids (no partial sum leaves the range by then) and are widened there.
+// R-MAT graph of 131,072 nodes, 3.9 M non-zeros, 40 channels, product and aggregation: int32 rows
+// with a wavefront each 114 us, so 60; Chung-Lu graph of 500,000 nodes, 12.8 M: 439 and 207.
+template <bool SCALE>
+__global__ __launch_bounds__(kBlock) void spmm_i16_sum_kernel(
+    const uint32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+    const int32_t *__restrict__ order, uint32_t N, const char *__restrict__ Z, int32_t M,
+    uint32_t row_bytes, const float *__restrict__ alpha, float *__restrict__ out,
+    int64_t out_stride, int g_log2, int lr, uint32_t flush, RowSegments seg)
+{
+    typedef uint16_t half_t __attribute__((ext_vector_type(8)));
+    const uint64_t v = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> g_log2;
+    if (v >= (uint64_t)seg.n_long_segs + (N - seg.n_long)) // team-uniform
+        return;
+    const int G = 1 << g_log2, sub = threadIdx.x & (G - 1), first = (threadIdx.x & 63) - sub;
+    const bool part = v < seg.n_long_segs;
+    uint32_t slot, k = 0;
+    if (part) {
+        slot = seg.seg_slot[v];
+        k = (uint32_t)v - seg.seg_ptr[slot];
+    } else {
+        slot = seg.n_long + (uint32_t)(v - seg.n_long_segs);
+    }
+    const uint32_t row = (uint32_t)order[slot];
+    const uint32_t rend = rowptr[row + 1];
+    const uint32_t beg = rowptr[row] + k * seg.seg_len;
+    const uint32_t end = part && rend - beg > seg.seg_len ? beg + seg.seg_len : rend;
+    const int Q = G / lr; // neighbour slots of the team
+    const int q = sub / lr, r = sub - q * lr;
+    const char *zr = Z + r * 16;
+    int32_t acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        acc[i] = 0;
+    half_t packed = 0;
+    uint32_t held = 0; // blocks summed in `packed`
+    auto widen = [&] {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            acc[i] += (int16_t)packed[i];
+        packed = 0;
+        held = 0;
+    };
+    auto ids_of = [&](uint32_t e0) {
+        const uint32_t e = e0 + (uint32_t)sub;
+        return col[e < end ? e : end - 1];
+    };
+    int32_t ids = beg < end ? ids_of(beg) : 0;
+    for (uint32_t e0 = beg; e0 < end; e0 += (uint32_t)G) {
+        const int cnt = end - e0 < (uint32_t)G ? (int)(end - e0) : G;
+        const int32_t next = ids_of(e0 + (uint32_t)G); // (past the end: its last id again)
+        for (int t0 = 0; t0 < cnt; t0 += 4 * Q) {
+            half_t z[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { // clamped loads, masked below
+                const int t = t0 + u * Q + q;
+                const uint32_t j = (uint32_t)__shfl(ids, first + (t < cnt ? t : cnt - 1), 64);
+                z[u] = *(const half_t *)(zr + (uint64_t)j * row_bytes);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q < Q && t0 + u * Q + q < cnt)
+                    packed += z[u];
+        }
+        if (++held == flush)
+            widen();
+        ids = next;
+    }
+    widen();
+    // the slots' sums are folded in halves until slot 0 holds the total
+    for (int active = Q; active > 1;) {
+        const int half = (active + 1) / 2;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int32_t other = __shfl(acc[i], (threadIdx.x & 63) + half * lr, 64);
+            if (q + half < active)
+                acc[i] += other;
+        }
+        active = half;
+    }
+    if (q != 0)
+        return;
+    const int c0 = r * 8;
+    int32_t *o = part ? (int32_t *)seg.partial + (size_t)v * M + c0
+                      : (int32_t *)out + (int64_t)row * out_stride + c0;
+    if (SCALE && !part)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            acc[i] = __float_as_int(alpha[c0 + i < M ? c0 + i : M - 1] * (float)acc[i]);
+    if (c0 + 8 <= M) {
+        __builtin_memcpy(o, acc, sizeof(acc)); // (4-byte aligned)
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (c0 + i < M)
+                o[i] = acc[i];
+    }
+}
+
 template <bool SCALE>
 __global__ __launch_bounds__(kBlock) void spmm_i32_long_rows_kernel(
     const int32_t *__restrict__ order, int32_t M, const float *__restrict__ alpha,
@@ -1675,21 +1778,76 @@ static double blocked_pass_us(const bitgnn_blocked *b)
 // CSR kernel is bound by its gather traffic or by the serial walk of the longest row;
 // the blocked kernel by its id stream or, on small graphs, by the chain of LDS refills a
 // workgroup walks through, and it pays that once per 128-channel pass.
+static bool prefer_blocked_over(const bitgnn_adj *adj, int passes, double csr_us)
+{
+    const bitgnn_blocked *b = adj->blk;
+    return b && (b->forced || passes * (blocked_pass_us(b) + 30.0) < csr_us);
+}
 bool bg_prefer_blocked(const bitgnn_adj *adj, int passes, int64_t bytes_per_nnz,
                        double chain_us_per_nnz, int64_t longest_chain)
 {
-    const bitgnn_blocked *b = adj->blk;
-    if (!b)
-        return false;
-    if (b->forced)
-        return true;
     // a gathered row costs its cache line plus its bytes: ~11 us per million 32-byte rows
     // (config 5), ~27 us per million 160-byte rows (the integer rows of an output layer)
     const double csr_traffic = (double)adj->nnz * (8.0 + 0.12 * (double)bytes_per_nnz) / 1e6;
     const double csr_chain = (double)longest_chain * chain_us_per_nnz;
-    const double csr = (csr_traffic > csr_chain ? csr_traffic : csr_chain) + 10.0;
-    const double blk = passes * (blocked_pass_us(b) + 30.0);
-    return blk < csr;
+    return prefer_blocked_over(adj, passes,
+                               (csr_traffic > csr_chain ? csr_traffic : csr_chain) + 10.0);
+}
+
+// Lanes per row of spmm_i16_sum_kernel for rows of M channels with |z| <= K, and what product and
+// aggregation are expected to take in microseconds.  Few rows leave the chip idle and take the
+// longest row's time, which more lanes cut; many rows fill it, and lanes beyond those that a row's
+// neighbours need are wavefronts for nothing.  40 channels, 8 / 16 / 32 / 64 lanes: Chung-Lu of
+// 10,007 nodes, mean degree 10: 24.6 / 17.1 / 13.9 / 14.7 us; R-MAT of 131,072, mean degree 30:
+// 60 / 64 / 73 / 100; block graph of 300,000, mean degree 6: 63 / 66 / 88 / 154.
+struct I16SumPlan {
+    int lanes; // 0: rows of more than 512 channels, or sums that leave 16 bits in one block of ids
+    double us;
+};
+static I16SumPlan i16_sum_plan(const bitgnn_adj *adj, int32_t M, int32_t K)
+{
+    I16SumPlan best{0, 0};
+    if (M > 512)
+        return best;
+    const int lr = (M + 7) / 8;
+    const int64_t vrows = (int64_t)adj->n_long_segs + (adj->n - adj->n_long);
+    const double longest = (double)(adj->max_degree < (int64_t)adj->seg_len
+                                        ? adj->max_degree
+                                        : (int64_t)adj->seg_len);
+    for (int g = 8; g <= 64; g *= 2) {
+        const int slots = g / lr;
+        if (slots == 0 || (int64_t)K * ((g + slots - 1) / slots) > 32767 || vrows * g >= 1ll << 31)
+            continue;
+        const double us =
+            10.0 + (adj->n_long ? 6.0 : 0.0) +
+            std::hypot(0.1 * longest / slots, (double)adj->nnz * (3e-6 + 0.14e-6 * M) +
+                                                  (double)vrows * g * 6e-6);
+        if (best.lanes == 0 || us < best.us)
+            best = I16SumPlan{g, us};
+    }
+    return best;
+}
+
+bool bg_spmm_i16_sum_applies(const bitgnn_adj *adj, int32_t M, int32_t K)
+{
+    return i16_sum_plan(adj, M, K).lanes != 0;
+}
+
+bool bg_prefer_blocked_out(const bitgnn_adj *adj, int32_t K, int32_t M)
+{
+    const int passes = (K + 127) / 128;
+    const double longest = (double)(adj->max_degree < (int64_t)adj->seg_len
+                                        ? adj->max_degree
+                                        : (int64_t)adj->seg_len);
+    const I16SumPlan p = i16_sum_plan(adj, M, K);
+    // (the class projection of a pass takes 0.2 ns a row)
+    const double project = passes * (double)adj->n * 0.2e-3;
+    if (p.lanes && M >= 4)
+        return prefer_blocked_over(adj, passes, p.us - project);
+    if (M < 4) // int32 rows of 4 to 12 bytes: a lane per channel (30,000 nodes, 5.7 M, 3: 38 us)
+        return prefer_blocked_over(adj, passes, std::hypot((double)adj->nnz * 5.5e-6,
+                                                           0.06 * longest) + 10.0 - project);
+    return bg_prefer_blocked(adj, passes, 4 * (int64_t)M, 0.25, (int64_t)longest);
 }
 
 // Which form a bit aggregation of C channels takes: a measured preference of bitgnn_adj_tune
@@ -2039,6 +2197,41 @@ int bg_launch_spmm_i32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
         BG_SPMM_I32(false);
 #undef BG_SPMM_I32
     BG_LAUNCH_CHECK(ctx, "bitgnn_spmm_i32");
+    return BITGNN_OK;
+}
+
+// alpha .* (A Z) of int16 rows with |z| <= K; rows start at multiples of 16 bytes and hold M
+// rounded up to 8 values.
+int bg_launch_spmm_i16_sum(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const int16_t *Z,
+                           int32_t M, int32_t K, int64_t ldz, const float *alpha, float *out,
+                           int64_t out_stride)
+{
+    const int g = i16_sum_plan(adj, M, K).lanes, lr = (M + 7) / 8;
+    const int64_t vrows = (int64_t)adj->n_long_segs + (adj->n - adj->n_long);
+    const int64_t grid = (vrows * g + kBlock - 1) / kBlock;
+    if (adj->n_long_segs) {
+        const int rc = bg_ws_need(ctx, s, (size_t)adj->n_long_segs * M * 4, "bitgnn_spmm_i32");
+        if (rc != BITGNN_OK)
+            return rc;
+    }
+    if (adj->n == 0)
+        return BITGNN_OK;
+    const RowSegments seg{adj->seg_ptr, adj->seg_slot, adj->n_long, adj->n_long_segs,
+                          adj->seg_len, 0,             (uint32_t *)ctx->sc->ws};
+    const int32_t per_block = (g + g / lr - 1) / (g / lr);
+    const uint32_t flush = 32767u / (uint32_t)(K * per_block);
+    spmm_i16_sum_kernel<true><<<(unsigned)grid, kBlock, 0, s>>>(
+        adj->rowptr, adj->col, adj->order, (uint32_t)adj->n, (const char *)Z, M,
+        (uint32_t)(ldz * 2), alpha, out, out_stride, __builtin_ctz(g), lr, flush, seg);
+    if (adj->n_long) {
+        int lpr_log2 = 0;
+        while ((1 << lpr_log2) < M && lpr_log2 < 6)
+            ++lpr_log2;
+        spmm_i32_long_rows_kernel<true>
+            <<<(unsigned)((((uint64_t)adj->n_long << lpr_log2) + kBlock - 1) / kBlock), kBlock, 0,
+               s>>>(adj->order, M, alpha, out, out_stride, lpr_log2, seg);
+    }
+    BG_LAUNCH_CHECK(ctx, "bitgnn_gcn_out_layer");
     return BITGNN_OK;
 }
 

@@ -237,6 +237,9 @@ double bg_bspmm_scaled_us(const bitgnn_adj *adj, int32_t C, bool bits_out);
 int bg_launch_spmm_i32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const int32_t *Z,
                        int32_t M, int64_t z_stride, const float *alpha, void *out,
                        int64_t out_stride);
+int bg_launch_spmm_i16_sum(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const int16_t *Z,
+                           int32_t M, int32_t K, int64_t ldz, const float *alpha, float *out,
+                           int64_t out_stride);
 
 bool bg_bgemm_mfma_applies(const bitgnn_ctx *ctx, int64_t n, int32_t kwords, int32_t M);
 bool bg_bgemm_f32_mfma_applies(const bitgnn_ctx *ctx, int32_t K, int32_t M, int epilogue);
@@ -266,6 +269,10 @@ size_t bg_adj_workspace_bytes(const bitgnn_adj *adj, int32_t C, int32_t M);
 // `longest_chain`: neighbours the CSR kernel in question walks serially at most.
 bool bg_prefer_blocked(const bitgnn_adj *adj, int passes, int64_t bytes_per_nnz,
                        double chain_us_per_nnz, int64_t longest_chain);
+// The same for an output layer of M classes, against the sums of int16 (where the product's sums
+// do not fit or rows are narrower, int32) rows.
+bool bg_prefer_blocked_out(const bitgnn_adj *adj, int32_t K, int32_t M);
+bool bg_spmm_i16_sum_applies(const bitgnn_adj *adj, int32_t M, int32_t K);
 int bg_launch_agg_project_blocked(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
                                   const uint64_t *hbits, int32_t K, int64_t h_stride,
                                   const uint64_t *wbits, int32_t M, int64_t w_stride,

@@ -4,6 +4,29 @@
 // only validate and enqueue the kernels of the other files on one stream.
 #include "common.h"
 
+// int16 rows of M columns for n nodes in a scratch of n * M floats, as the BMM writes them: a row
+// starts where a cache line does, or shares one with whole rows only (41 channels gathered
+// 110.6 M times: 164-byte rows, as narrowed in place, 2,101 us, 82 bytes 2,010, 128 bytes 1,673).
+// False where they do not fit (fewer than four columns, a scratch that is not aligned).
+struct Int16Rows {
+    int16_t *z;
+    int64_t ld; // elements
+};
+static bool int16_rows(float *scratch, int64_t n, int32_t M, Int16Rows *out)
+{
+    const int64_t bytes = 2 * (int64_t)M;
+    const int64_t line = bytes > 64 ? 128 : bytes > 32 ? 64 : bytes > 16 ? 32 : 16;
+    for (int64_t unit = line; unit >= 16; unit = unit > 16 ? 16 : 0) {
+        const int64_t row = (bytes + unit - 1) / unit * unit;
+        const uintptr_t at = ((uintptr_t)scratch + unit - 1) / unit * unit;
+        if ((int64_t)(at - (uintptr_t)scratch) + n * row <= n * 4 * (int64_t)M) {
+            *out = Int16Rows{(int16_t *)at, row / 2};
+            return true;
+        }
+    }
+    return false;
+}
+
 extern "C" int bitgnn_gcn_layer(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *adj,
                                 const uint64_t *xbits, int64_t x_stride, int32_t K, int32_t kwords,
                                 const uint64_t *wbits, int32_t M, int64_t w_stride,
@@ -89,12 +112,18 @@ extern "C" int bitgnn_gcn_out_layer(bitgnn_ctx *ctx, void *stream, const bitgnn_
     // staged in LDS (128 channels per pass), and the class projection is fused into its
     // merge step (tmp_i32 chains the integer sums of the passes when K > 128); otherwise
     // the int32 rows of x W are aggregated directly.
-    if ((int64_t)K * adj->max_degree < (1ll << 29) &&
-        bg_prefer_blocked(adj, (K + 127) / 128, 4 * (int64_t)M, 0.25,
-                          adj->max_degree < (int64_t)adj->seg_len ? adj->max_degree
-                                                                  : (int64_t)adj->seg_len))
+    if ((int64_t)K * adj->max_degree < (1ll << 29) && bg_prefer_blocked_out(adj, K, M))
         return bg_launch_agg_project_blocked(ctx, s, adj, xbits, K, x_stride, wbits, M, w_stride,
                                              alpha, tmp_i32, logits, ldo);
+    // the product's rows in 16 bits where its sums allow it: half of what the gathers read
+    Int16Rows h;
+    if (bg_spmm_i16_sum_applies(adj, M, K) && int16_rows((float *)tmp_i32, n, M, &h)) {
+        rc = bg_launch_bgemm(ctx, s, xbits, n, x_stride, K, kwords, wbits, M, w_stride, kEpiRawI16,
+                             nullptr, nullptr, h.z, h.ld);
+        if (rc != BITGNN_OK)
+            return rc;
+        return bg_launch_spmm_i16_sum(ctx, s, adj, h.z, M, K, h.ld, alpha, logits, ldo);
+    }
     rc = bg_launch_bgemm(ctx, s, xbits, n, x_stride, K, kwords, wbits, M, w_stride,
                          BITGNN_EPI_RAW_I32, nullptr, nullptr, tmp_i32, M);
     if (rc != BITGNN_OK)
@@ -180,29 +209,6 @@ static int aggregate_scaled_integers(bitgnn_ctx *ctx, hipStream_t s, const bitgn
         return rc;
     return bg_launch_spmm_f32(ctx, s, adj, scratch, 0, M, 2 * (int64_t)M, r, f, epilogue, tau, out,
                               ldo, alpha);
-}
-
-// int16 rows of M columns for n nodes in a scratch of n * M floats, as the BMM writes them: a row
-// starts where a cache line does, or shares one with whole rows only (41 channels gathered
-// 110.6 M times: 164-byte rows, as narrowed in place, 2,101 us, 82 bytes 2,010, 128 bytes 1,673).
-// False where they do not fit (fewer than four columns, a scratch that is not aligned).
-struct Int16Rows {
-    int16_t *z;
-    int64_t ld; // elements
-};
-static bool int16_rows(float *scratch, int64_t n, int32_t M, Int16Rows *out)
-{
-    const int64_t bytes = 2 * (int64_t)M;
-    const int64_t line = bytes > 64 ? 128 : bytes > 32 ? 64 : bytes > 16 ? 32 : 16;
-    for (int64_t unit = line; unit >= 16; unit = unit > 16 ? 16 : 0) {
-        const int64_t row = (bytes + unit - 1) / unit * unit;
-        const uintptr_t at = ((uintptr_t)scratch + unit - 1) / unit * unit;
-        if ((int64_t)(at - (uintptr_t)scratch) + n * row <= n * 4 * (int64_t)M) {
-            *out = Int16Rows{(int16_t *)at, row / 2};
-            return true;
-        }
-    }
-    return false;
 }
 
 // The same two layers with a weighted adjacency, diag(r) A diag(f) (Section 3.1.1: a

@@ -1111,6 +1111,47 @@ def test_gcn_out_layer_both_orders(B, ctx, tuned, n, e, K, M):
     adj.close()
 
 
+@pytest.mark.parametrize("M", [3, 4, 7, 8, 9, 16, 17, 40, 41, 64, 65, 100, 256, 257, 512, 513])
+@pytest.mark.parametrize("n,e,K,hub,shift", [
+    (1, 0, 5, 0, 0), (301, 900, 256, 0, 1), (3001, 20000, 2047, 300, 0), (20011, 60000, 64, 0, 2),
+    (1500, 3000, 3000, 1200, 3)])
+def test_gcn_out_layer_sums_of_int16_rows(B, ctx, M, n, e, K, hub, shift):
+    """The output layer through the sums of the product's int16 rows, at the edges of their lanes
+    (8 channels each), with rows without neighbours, rows of several segments, sums that are
+    widened after every block of ids or no longer fit, and scratch off the 16-byte grid: integers
+    up to 2^24, so exactly alpha times the 64-bit sum, rounded once."""
+    r = np.random.default_rng(7000 + M + n)
+    src, dst = r.integers(0, n, e).astype(np.int32), r.integers(0, n, e).astype(np.int32)
+    if hub:
+        src = np.concatenate([src, np.zeros(hub, np.int32)])
+        dst = np.concatenate([dst, np.arange(1, hub + 1, dtype=np.int32)])
+    B.ctx_set_tuning(ctx, *TUNINGS["csr-only"])
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, W.ADJ_SYMMETRIZE)
+    B.ctx_set_tuning(ctx, *TUNINGS["default"])
+    rp, col = orc.adjacency(src, dst, n, W.ADJ_SYMMETRIZE)
+    # nearly the same rows everywhere, so that sums come close to degree * K
+    w = np.where(r.random((K, M)) < 0.01, -1, 1).astype(np.int8)
+    x = np.where(r.random((n, K)) < 0.01, -1, 1).astype(np.int8)
+    z = (x.astype(np.float64) @ w.astype(np.float64)).astype(np.int64)
+    sums = np.zeros((n, M), np.int64)
+    np.add.at(sums, np.repeat(np.arange(n), np.diff(rp)), z[col])
+    assert np.abs(sums).max() < 1 << 24
+    kw = B.words(K)
+    xb, wb = (torch.zeros((k, kw), dtype=torch.int64, device="cuda") for k in (n, M))
+    B.pack_i8(ctx, dev(x), n, K, K, xb, kw)
+    B.pack_weights_i8(ctx, dev(w), K, M, M, wb, kw)
+    alpha = (r.random(M) + 0.5).astype(np.float32)
+    B.ctx_reserve(ctx, B.adj_workspace_bytes(ctx, adj, 128, M))
+    tmp = torch.full((n * M + 8,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    out = torch.full((n, M + 3), -7.0, device="cuda")
+    B.gcn_out_layer(ctx, adj, xb, kw, K, kw, wb, M, kw, dev(alpha), tmp[shift:], out, M + 3)
+    torch.cuda.synchronize()
+    assert np.array_equal(out[:, :M].cpu().numpy(), alpha * sums.astype(np.float32))
+    assert (out[:, M:] == -7.0).all() and (tmp[:shift] == 0x5A5A5A5A).all()
+    assert (tmp[shift + n * M:] == 0x5A5A5A5A).all()
+    adj.close()
+
+
 @pytest.mark.parametrize("n,e,K,M,kind", [
     (120, 500, 33, 5, "sparse"),          # max degree < 2^7: one 7-bit digit
     (20001, 30000, 128, 41, "star"),      # a row of 20,001: three digits
