@@ -295,10 +295,21 @@ int bg_check_bgemm(bitgnn_ctx *ctx, const uint64_t *xbits, int64_t n, int64_t x_
 int bg_check_spmm_f32(bitgnn_ctx *ctx, const bitgnn_adj *adj, const void *x, int x_is_bits,
                       int32_t C, int64_t ldx, const float *r, const float *f, int epilogue,
                       const float *tau, const void *out, int64_t ldo);
+// Byte rows in place of int16 rows (see spmm_f32.hip): 64, 128 or 256 bytes each, on a multiple of
+// the line or of half of it.
+struct bg_byte_rows {
+    void *z;
+    int64_t row_bytes;
+    const uint32_t *wide; // set where the int16 rows have to be taken; null: never
+    bool has_factor;
+};
+bool bg_byte_rows_pay(const bitgnn_adj *adj, int32_t C, int32_t K, bool has_f);
+int bg_launch_byte_rows(bitgnn_ctx *ctx, hipStream_t s, const int16_t *z, int64_t n, int32_t C,
+                        int64_t ld, const float *f, uint32_t *wide, bg_byte_rows *b);
 int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const void *x,
                        int x_is_bits, int32_t C, int64_t ldx, const float *r, const float *f,
                        int epilogue, const float *tau, void *out, int64_t ldo,
-                       const float *xscale);
+                       const float *xscale, const bg_byte_rows *bytes);
 int bg_launch_narrow_rows(bitgnn_ctx *ctx, hipStream_t s, int32_t *z, int64_t n, int32_t M,
                           int64_t ld32);
 int bg_check_bspmm(bitgnn_ctx *ctx, const bitgnn_adj *adj, const uint64_t *hbits, int32_t C,

@@ -208,7 +208,52 @@ static int aggregate_scaled_integers(bitgnn_ctx *ctx, hipStream_t s, const bitgn
     if (rc != BITGNN_OK)
         return rc;
     return bg_launch_spmm_f32(ctx, s, adj, scratch, 0, M, 2 * (int64_t)M, r, f, epilogue, tau, out,
-                              ldo, alpha);
+                              ldo, alpha, nullptr);
+}
+
+// Where the rows are gathered often enough, every value fits a byte or nearly always does, and the
+// scratch has the room, a launch after the product writes byte rows too: a 128-channel row is then
+// one cache line instead of two.  K <= 254: |z| / 2 <= 127.  Wider products may hold values without
+// a byte (|z| > 254: 10 standard deviations of random bits at K = 602); a word says so and the
+// aggregation then takes the int16 rows.
+struct ProductRows {
+    Int16Rows h;
+    bool bytes;
+    bg_byte_rows b;
+    uint32_t *wide;
+};
+static bool product_rows(const bitgnn_adj *adj, float *scratch, int32_t K, int32_t M,
+                         const float *f, ProductRows *p)
+{
+    const int64_t n = adj->n, total = n * 4 * (int64_t)M;
+    p->bytes = false;
+    p->b.row_bytes = 64;
+    while (p->b.row_bytes < M)
+        p->b.row_bytes *= 2;
+    const int64_t row16 = (2 * (int64_t)M + 15) / 16 * 16;
+    const uintptr_t at = ((uintptr_t)scratch + 127) / 128 * 128;
+    const int64_t z16 = (int64_t)(at - (uintptr_t)scratch) + n * p->b.row_bytes;
+    if (z16 + n * row16 + 4 <= total && n * row16 < (1ll << 32) && bg_byte_rows_pay(adj, M, K, f != nullptr)) {
+        p->bytes = true;
+        p->b.z = (void *)at;
+        p->h = Int16Rows{(int16_t *)((char *)scratch + z16), row16 / 2};
+        p->wide = K > 254 ? (uint32_t *)((char *)scratch + z16 + n * row16) : nullptr;
+        return true;
+    }
+    return int16_rows(scratch, n, M, &p->h);
+}
+static int aggregate_product_rows(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj,
+                                  ProductRows &p, int32_t M, const float *alpha, const float *r,
+                                  const float *f, int epilogue, const float *tau, void *out,
+                                  int64_t ldo)
+{
+    if (p.bytes) {
+        const int rc = bg_launch_byte_rows(ctx, s, p.h.z, adj->n, M, p.h.ld, f, p.wide, &p.b);
+        if (rc != BITGNN_OK)
+            return rc;
+    }
+    return bg_launch_spmm_f32(ctx, s, adj, p.h.z, 0, M, p.h.ld, r, f, epilogue, tau, out, ldo,
+                              alpha, p.bytes ? &p.b : nullptr);
 }
 
 // The same two layers with a weighted adjacency, diag(r) A diag(f) (Section 3.1.1: a
@@ -243,7 +288,7 @@ extern "C" int bitgnn_gcn_layer_weighted(bitgnn_ctx *ctx, void *stream, const bi
     if (rc != BITGNN_OK)
         return rc;
     return bg_launch_spmm_f32(ctx, s, adj, tmp_bits, 1, M, mw, r, f, BITGNN_EPI_THRESH_BITS,
-                              tau_agg, out_bits, out_stride, nullptr);
+                              tau_agg, out_bits, out_stride, nullptr, nullptr);
 }
 
 extern "C" int bitgnn_sage_layer_weighted(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *adj,
@@ -272,7 +317,7 @@ extern "C" int bitgnn_sage_layer_weighted(bitgnn_ctx *ctx, void *stream, const b
     BG_NEED_DEVICE(ctx);
     hipStream_t s = (hipStream_t)stream;
     rc = bg_launch_spmm_f32(ctx, s, adj, cat_bits, 1, K_in, 2 * kw, r, f, BITGNN_EPI_THRESH_BITS,
-                            tau_agg, cat_bits + kw, 2 * kw, nullptr);
+                            tau_agg, cat_bits + kw, 2 * kw, nullptr, nullptr);
     if (rc != BITGNN_OK)
         return rc;
     return bg_launch_bgemm(ctx, s, cat_bits, n, 2 * kw, 2 * K_in, 2 * kw, wbits, M, w_stride,
@@ -303,14 +348,14 @@ extern "C" int bitgnn_gcn_out_layer_weighted(bitgnn_ctx *ctx, void *stream, cons
         return rc;
     BG_NEED_DEVICE(ctx);
     hipStream_t s = (hipStream_t)stream;
-    Int16Rows h;
-    if (K <= kNarrowMaxK && int16_rows(tmp_f32, n, M, &h)) {
+    ProductRows p;
+    if (K <= kNarrowMaxK && product_rows(adj, tmp_f32, K, M, f, &p)) {
         rc = bg_launch_bgemm(ctx, s, xbits, n, x_stride, K, kwords, wbits, M, w_stride, kEpiRawI16,
-                             nullptr, nullptr, h.z, h.ld);
+                             nullptr, nullptr, p.h.z, p.h.ld);
         if (rc != BITGNN_OK)
             return rc;
-        return bg_launch_spmm_f32(ctx, s, adj, h.z, 0, M, h.ld, r, f, BITGNN_EPI_SCALE_F32, nullptr,
-                                  logits, ldo, alpha);
+        return aggregate_product_rows(ctx, s, adj, p, M, alpha, r, f, BITGNN_EPI_SCALE_F32, nullptr,
+                                      logits, ldo);
     }
     if (K <= kNarrowMaxK) {
         rc = bg_launch_bgemm(ctx, s, xbits, n, x_stride, K, kwords, wbits, M, w_stride,
@@ -325,7 +370,7 @@ extern "C" int bitgnn_gcn_out_layer_weighted(bitgnn_ctx *ctx, void *stream, cons
     if (rc != BITGNN_OK)
         return rc;
     return bg_launch_spmm_f32(ctx, s, adj, tmp_f32, 0, M, M, r, f, BITGNN_EPI_SCALE_F32, nullptr,
-                              logits, ldo, nullptr);
+                              logits, ldo, nullptr, nullptr);
 }
 
 // GCN hidden layer of the full-precision-aggregation recipe (Table 3's "Ours (full)": the
@@ -338,7 +383,7 @@ static int gcn_layer_full_tail(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj 
                                const float *tau_agg, uint64_t *out_bits, int64_t out_stride)
 {
     return bg_launch_spmm_f32(ctx, s, adj, tmp_f32, 0, M, M, r, f, BITGNN_EPI_THRESH_BITS,
-                              tau_agg, out_bits, out_stride, nullptr);
+                              tau_agg, out_bits, out_stride, nullptr, nullptr);
 }
 
 extern "C" int bitgnn_gcn_layer_full(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *adj,
@@ -362,14 +407,14 @@ extern "C" int bitgnn_gcn_layer_full(bitgnn_ctx *ctx, void *stream, const bitgnn
         return rc;
     BG_NEED_DEVICE(ctx);
     hipStream_t s = (hipStream_t)stream;
-    Int16Rows h;
-    if (K <= kNarrowMaxK && int16_rows(tmp_f32, n, M, &h)) {
+    ProductRows p;
+    if (K <= kNarrowMaxK && product_rows(adj, tmp_f32, K, M, f, &p)) {
         rc = bg_launch_bgemm(ctx, s, xbits, n, x_stride, K, kwords, wbits, M, w_stride, kEpiRawI16,
-                             nullptr, nullptr, h.z, h.ld);
+                             nullptr, nullptr, p.h.z, p.h.ld);
         if (rc != BITGNN_OK)
             return rc;
-        return bg_launch_spmm_f32(ctx, s, adj, h.z, 0, M, h.ld, r, f, BITGNN_EPI_THRESH_BITS,
-                                  tau_agg, out_bits, out_stride, alpha);
+        return aggregate_product_rows(ctx, s, adj, p, M, alpha, r, f, BITGNN_EPI_THRESH_BITS,
+                                      tau_agg, out_bits, out_stride);
     }
     if (K <= kNarrowMaxK) {
         rc = bg_launch_bgemm(ctx, s, xbits, n, x_stride, K, kwords, wbits, M, w_stride,
@@ -407,14 +452,14 @@ extern "C" int bitgnn_gcn_layer_full_f32(bitgnn_ctx *ctx, void *stream, const bi
         return rc;
     BG_NEED_DEVICE(ctx);
     hipStream_t s = (hipStream_t)stream;
-    Int16Rows h;
-    if (K <= kNarrowMaxK && int16_rows(tmp_f32, n, M, &h)) {
+    ProductRows p;
+    if (K <= kNarrowMaxK && product_rows(adj, tmp_f32, K, M, f, &p)) {
         rc = bg_launch_bgemm_f32(ctx, s, x, n, K, ldx, tau_in, wbits, M, w_stride, kEpiRawI16,
-                                 nullptr, nullptr, h.z, h.ld);
+                                 nullptr, nullptr, p.h.z, p.h.ld);
         if (rc != BITGNN_OK)
             return rc;
-        return bg_launch_spmm_f32(ctx, s, adj, h.z, 0, M, h.ld, r, f, BITGNN_EPI_THRESH_BITS,
-                                  tau_agg, out_bits, out_stride, alpha);
+        return aggregate_product_rows(ctx, s, adj, p, M, alpha, r, f, BITGNN_EPI_THRESH_BITS,
+                                      tau_agg, out_bits, out_stride);
     }
     if (K <= kNarrowMaxK) {
         rc = bg_launch_bgemm_f32(ctx, s, x, n, K, ldx, tau_in, wbits, M, w_stride,

@@ -33,6 +33,7 @@ constexpr int kTeam = 16;              // lanes of a team: one DPP row
 constexpr int kHubProd = 7;            // producer wavefronts of a hub workgroup
 constexpr int kHubPer = 16;            // neighbours a producer takes per stage (4 per team)
 constexpr int kHubStage = kHubProd * kHubPer;
+constexpr uint32_t kFactorAt = 60;     // where a 64-byte row of bytes holds its factor
 constexpr size_t kHubLds = 2ull * kHubStage * 64 * sizeof(float); // two stages of products
 
 // One rounded multiply, one rounded add: contraction is off, so the pair is never fused.
@@ -71,7 +72,9 @@ template <int B, int E, class F> __device__ __forceinline__ void static_for(F &&
 // V consecutive values of a row of x as a lane loads them.
 // XKIND: 0 float rows, 1 packed +-1 rows, 2 int16 rows with a per-channel scale (the raw
 // integers of a BMM and its SCL: the value alpha_c * (float)z is formed here, with the same
-// single rounding as the BMM's own scale epilogue, from half the gathered bytes)
+// single rounding as the BMM's own scale epilogue, from half the gathered bytes), 3 the same in
+// bytes (z / 2 + 128: the integers of a product of even length are even), 4 byte rows of 64 bytes
+// whose last four are the row's factor
 template <int XKIND, int V> struct x_piece;
 template <int V> struct x_piece<0, V> {
     float v[V];
@@ -82,6 +85,38 @@ template <int V> struct x_piece<1, V> {
 template <int V> struct x_piece<2, V> {
     int16_t v[V];
 };
+
+template <int V> struct x_piece<3, V> {
+    uint32_t v; // V <= 4
+};
+template <int V> struct x_piece<4, V> : x_piece<3, V> {};
+
+// alpha * z, rounded once, for the integer z in the low or high half of `h`: the half is converted
+// on the way in.  (-0 is what leaves every product, and the sign of a zero, as it is.)
+template <int HI> __device__ __forceinline__ float mul_half(float alpha, uint32_t h)
+{
+    float p;
+    if (HI)
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
+            : "=v"(p)
+            : "v"(alpha), "v"(h), "s"(0x80000000u));
+    else
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,1,0]"
+            : "=v"(p)
+            : "v"(alpha), "v"(h), "s"(0x80000000u));
+    return p;
+}
+// Bytes 2 HI and 2 HI + 1 of a word as a pair of halves holding z = 2 (byte - 128): behind 0x64 a
+// byte is the half 1024 + byte.
+template <int HI> __device__ __forceinline__ uint32_t even_pair(uint32_t w)
+{
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    const uint32_t biased =
+        __builtin_amdgcn_perm(0x64646464u, w, HI ? 0x04030402u : 0x04010400u);
+    const h2 z = __builtin_elementwise_fma(__builtin_bit_cast(h2, biased), (h2)(_Float16)2,
+                                           (h2)(_Float16)-2304);
+    return __builtin_bit_cast(uint32_t, z);
+}
 
 struct SpmmArgs {
     const uint32_t *rowptr;
@@ -100,6 +135,10 @@ struct SpmmArgs {
     uint32_t windows;      // channel windows of a row
     uint32_t group;        // windows of a row that are taken side by side
     uint32_t group_blocks; // workgroups per group of windows
+    // byte rows: where *wide is set some value has no byte, and these int16 rows are taken
+    const uint32_t *wide;
+    const void *x16;
+    int64_t row_bytes16;
 };
 
 // The sign a packed bit gives f: bit set -> +f, clear -> -f.  `inv` holds the inverted bit at
@@ -128,7 +167,9 @@ template <int XKIND, int V> struct x_lane {
             off = (uint32_t)(dw < last ? dw : last) * 4u;
             bsh = (uint32_t)(c & 31);
         } else {
-            off = (uint32_t)cs * (XKIND == 2 ? 2u : 4u);
+            off = (uint32_t)cs * (XKIND == 2 ? 2u : XKIND >= 3 ? 1u : 4u);
+            if (XKIND == 4 && c == 15 * V)
+                off = kFactorAt; // the team's last lane brings the factor
         }
     }
     // the piece of neighbour number K of the 16 whose ids the team's lanes hold
@@ -156,6 +197,18 @@ template <int XKIND, int V> struct x_lane {
 #pragma unroll
             for (int v = 0; v < V; ++v)
                 p[v] = signed_f(inv, 31u - (uint32_t)v, f);
+        } else if constexpr (XKIND >= 3) {
+            static_for<0, (V + 1) / 2>([&](auto ii) {
+                constexpr int I = decltype(ii)::value;
+                const uint32_t z = even_pair<I>(x.v);
+                p[2 * I] = mul_half<0>(sc[2 * I], z);
+                if constexpr (2 * I + 1 < V)
+                    p[2 * I + 1] = mul_half<1>(sc[2 * I + 1], z);
+            });
+            if (HASF)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    p[v] = mul_rounded(f, p[v]);
         } else {
 #pragma unroll
             for (int v = 0; v < V; ++v) {
@@ -198,7 +251,7 @@ __device__ __forceinline__ void spmm_hub_row(const SpmmArgs &a, uint32_t slot, u
         float sc[V];
 #pragma unroll
         for (int v = 0; v < V; ++v)
-            sc[v] = XKIND == 2 ? a.xscale[xl.cs + v] : 1.0f;
+            sc[v] = XKIND >= 2 ? a.xscale[xl.cs + v] : 1.0f;
         // A team's 16 lanes hold the ids of its neighbours of four stages (four per stage).
         auto ids_of = [&](uint32_t b) -> uint32_t {
             const uint32_t k =
@@ -311,6 +364,7 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
     // window and row of this team: a group of windows of a row side by side (one instruction then
     // covers adjacent pieces of a row), one group of all rows after the other
     // (the divisions are latency that every row waits for, so what needs none goes without)
+    constexpr bool GATHERF = HASF && XKIND != 4; // else the rows bring their factors
     const uint32_t grp = a.group < a.windows ? tb / a.group_blocks : 0u;
     const uint32_t team = (tb - grp * a.group_blocks) * (kThreads / kTeam) + threadIdx.x / kTeam;
     const uint32_t team_row = a.group == 1 ? team : team / a.group;
@@ -334,7 +388,7 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         acc[v] = 0.0f;
-        sc[v] = XKIND == 2 ? a.xscale[xl.cs + v] : 1.0f;
+        sc[v] = XKIND >= 2 ? a.xscale[xl.cs + v] : 1.0f;
     }
     typedef x_piece<XKIND, V> piece;
     // rows in flight: two sets of 8 (4 where a piece is 16 bytes: two sets of 8 spill)
@@ -359,7 +413,11 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
         constexpr int K0 = decltype(first)::value;
         static_for<0, (int)(sizeof(x) / sizeof(x[0]))>([&](auto kk) {
             constexpr int K = decltype(kk)::value;
-            const float fk = HASF ? row_bcast_f<K0 + K>(fl) : 1.0f;
+            float fk = 1.0f;
+            if constexpr (HASF && XKIND == 4)
+                fk = row_bcast_f<15>(__int_as_float((int)x[K].v));
+            else if constexpr (HASF)
+                fk = row_bcast_f<K0 + K>(fl);
             if (decltype(full)::value || t + K0 + K < deg) {
                 float p[V];
                 xl.template products<HASF>(x[K], sc, fk, p);
@@ -373,7 +431,7 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
     // (54,198 nodes, 265 K non-zeros, int16 rows of 192 channels 36 us with the loop alone, 23 so).
     auto short_rows = [&](auto count) {
         const uint32_t id = ids_of(0);
-        const float fl = HASF ? a.f[id] : 1.0f;
+        const float fl = GATHERF ? a.f[id] : 1.0f;
         piece x[decltype(count)::value];
         load(id, const_int<0>{}, x);
         consume(fl, const_int<0>{}, x, 0, std::false_type{});
@@ -386,12 +444,12 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
         // The ids of a block of 16 neighbours are requested two blocks ahead, the factors one
         // block ahead, the rows kAhead neighbours ahead.
         uint32_t id0 = ids_of(0), id1 = ids_of(16);
-        float f0 = HASF ? a.f[id0] : 1.0f;
+        float f0 = GATHERF ? a.f[id0] : 1.0f;
         piece x[2][kAhead];
         __builtin_amdgcn_sched_barrier(0); // ids and factors stay older than the rows
         load(id0, const_int<0>{}, x[0]);
         auto step = [&](uint32_t t, auto full) {
-            const float f1 = HASF ? a.f[id1] : 1.0f;
+            const float f1 = GATHERF ? a.f[id1] : 1.0f;
             const uint32_t id2 = ids_of(t + 32);
             static_for<0, 16 / kAhead>([&](auto qq) {
                 constexpr int Q = decltype(qq)::value;
@@ -467,22 +525,36 @@ __device__ __forceinline__ void spmm_team_rows(const SpmmArgs &a, uint32_t tb)
 // HUBS: the launch starts with hub workgroups; their registers and LDS halve the wavefronts of the other rows,
 // so launches without hubs take a kernel of their own.
 template <int XKIND, bool BITS_OUT, bool HASF, int V, bool BIG, bool HUBS>
-__global__ __launch_bounds__(HUBS ? kHubBlock : kSpBlock, 4) void spmm_f32_kernel(
-    const SpmmArgs a)
+__device__ __forceinline__ void spmm_f32_rows(const SpmmArgs &a, float *prod)
 {
     constexpr int kThreads = HUBS ? kHubBlock : kSpBlock;
     uint32_t tb = blockIdx.x;
     if constexpr (HUBS) {
-        extern __shared__ float prod[];
         const uint32_t hub_blocks = a.n_hub * a.hub_tiles;
         if (tb < hub_blocks) { // workgroup-uniform; the longest rows start first
-            spmm_hub_row<XKIND, BITS_OUT, HASF, V == 1 ? 1 : 4, BIG>(a, tb / a.hub_tiles,
-                                                                     tb % a.hub_tiles, prod);
+            spmm_hub_row<XKIND == 4 ? 3 : XKIND, BITS_OUT, HASF, V == 1 ? 1 : 4, BIG>(
+                a, tb / a.hub_tiles, tb % a.hub_tiles, prod);
             return;
         }
         tb -= hub_blocks;
     }
     spmm_team_rows<XKIND, BITS_OUT, HASF, V, BIG, kThreads>(a, tb);
+}
+template <int XKIND, bool BITS_OUT, bool HASF, int V, bool BIG, bool HUBS>
+__global__ __launch_bounds__(HUBS ? kHubBlock : kSpBlock, 4) void spmm_f32_kernel(
+    const SpmmArgs a)
+{
+    extern __shared__ float prod[];
+    if constexpr (XKIND >= 3) {
+        if (a.wide && *a.wide) { // (the same for the whole launch)
+            SpmmArgs b = a;
+            b.x = a.x16;
+            b.row_bytes = a.row_bytes16;
+            spmm_f32_rows<2, BITS_OUT, HASF, V, BIG, HUBS>(b, prod);
+            return;
+        }
+    }
+    spmm_f32_rows<XKIND, BITS_OUT, HASF, V, BIG, HUBS>(a, prod);
 }
 
 } // namespace
@@ -536,7 +608,7 @@ double team_us(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool 
     else if (xkind == 1)
         chain = V == 8 ? 54 : 33, gather = V == 4 || large ? 0.005 : 0.0075,
         row = V == 8 && bits_out ? 0.2 : 0.09;
-    else if (xkind == 2)
+    else if (xkind >= 2)
         chain = 42, gather = 0.0085, row = 0.14;
     else
         chain = large ? 65 : 35, gather = large ? 0.0075 : 0.0095, row = 0.13;
@@ -574,10 +646,10 @@ struct Plan {
 // nodes, 111 K non-zeros, longest row 1,526, packed rows of 100 channels with factors: 104 us
 // without hubs, 13 at 2^7; Chung-Lu graph of 22,106 nodes, 7.7 M, 2,538, 256 floats: 498 without,
 // 845 at 2^7, 563 at 2^10.
-Plan choose_plan(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large)
+Plan choose_plan(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, bool large, int V)
 {
     Plan best{0, 0, 0};
-    const int Vs[2] = {xkind != 1 && C <= 16 ? 1 : 4, 8};
+    const int Vs[2] = {V ? V : xkind != 1 && C <= 16 ? 1 : 4, 8};
     for (int q = 0; q < (xkind == 1 && C > 64 ? 2 : 1); ++q)
         for (int k = 6; k < 31; ++k) {
             const int kk = k == 6 ? -1 : k; // 6: no hubs
@@ -604,7 +676,7 @@ Plan choose_plan(const bitgnn_adj *adj, int xkind, int32_t C, bool bits_out, boo
 int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, const void *x,
                        int x_is_bits, int32_t C, int64_t ldx, const float *r, const float *f,
                        int epilogue, const float *tau, void *out, int64_t ldo,
-                       const float *xscale)
+                       const float *xscale, const bg_byte_rows *bytes)
 {
     if (adj->n == 0)
         return BITGNN_OK;
@@ -615,6 +687,20 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     a.order = adj->order;
     a.x = x;
     a.row_bytes = ldx * (xscale ? 2 : x_is_bits ? 8 : 4);
+    a.wide = nullptr;
+    a.x16 = x;
+    a.row_bytes16 = a.row_bytes;
+    // Channels per lane of byte rows: 3 where 15 lanes then hold all of them, a fifth less
+    // arithmetic (their bits would straddle words, so bits take 4, like wider rows: with 8 a row's
+    // walk is longer; 30,000 nodes, 5.7 M non-zeros, 128 channels to bits: int16 rows 133 us, bytes
+    // with 8 per lane 173, with 4 123; 150,000 nodes, 43.5 M: 950, 659 and 680).
+    int byte_v = 0;
+    if (bytes) {
+        a.wide = bytes->wide;
+        a.x = bytes->z;
+        a.row_bytes = bytes->row_bytes;
+        byte_v = f && C > 32 && C <= 45 && !bits_out ? 3 : 4;
+    }
     a.xscale = xscale;
     a.C = C;
     a.r = r;
@@ -625,7 +711,8 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     a.hub_tiles = ((uint32_t)C + 63) / 64;
     const uint64_t table = (uint64_t)adj->n * (uint64_t)a.row_bytes;
     const bool large = table > (4u << 20); // than an L2
-    const Plan plan = choose_plan(adj, xscale ? 2 : x_is_bits ? 1 : 0, C, bits_out, large);
+    const Plan plan =
+        choose_plan(adj, xscale ? 2 : x_is_bits ? 1 : 0, C, bits_out, large, byte_v);
     // +-1 rows without factors: the float sum of a row is its integer sum, exact while partial
     // sums stay below 2^24, so the bit aggregation's counters give it.  It needs the workspace
     // (without it the floats are added here) and is taken where it is priced lower; which is
@@ -656,7 +743,7 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     // Packed rows are short.
     a.group = a.windows;
     if (!x_is_bits && adj->nnz >= 24 * adj->n) {
-        if (!f && a.row_bytes % 128 == 0 && bg_aligned(x, 128) && table > (8u << 20))
+        if (!f && a.row_bytes % 128 == 0 && bg_aligned(a.x, 128) && table > (8u << 20))
             a.group = 1;
         else if (large && a.windows > 4 &&
                  adj->nnz * (int64_t)a.windows >= 16000 * adj->max_degree)
@@ -668,8 +755,11 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
     auto launch = [&](auto xk, auto v) {
         constexpr int XK = decltype(xk)::value, VV = decltype(v)::value;
         auto go = [&](auto bo, auto hf, auto bg) {
-            constexpr bool BO = decltype(bo)::value, HF = decltype(hf)::value,
-                           BG = decltype(bg)::value;
+            // (forms that are not launched are not built: bits of 3 channels per lane, offsets
+            // of byte rows beyond 32 bits, factors in rows without them)
+            constexpr bool BO = decltype(bo)::value && VV != 3,
+                           HF = decltype(hf)::value || XK == 4,
+                           BG = decltype(bg)::value && XK < 3;
             if (a.n_hub)
                 spmm_f32_kernel<XK, BO, HF, VV, BG, true>
                     <<<grid, threads, kHubLds, s>>>(a);
@@ -694,7 +784,14 @@ int bg_launch_spmm_f32(bitgnn_ctx *ctx, hipStream_t s, const bitgnn_adj *adj, co
         const uint32_t teams = threads / kTeam; // of a workgroup
         a.group_blocks = ((uint32_t)rows * a.group + teams - 1) / teams;
         grid = a.n_hub * a.hub_tiles + groups * a.group_blocks;
-        if (xscale) {
+        if (bytes) {
+            if (V == 3)
+                launch(const_int<4>{}, const_int<3>{});
+            else if (bytes->has_factor)
+                launch(const_int<4>{}, const_int<4>{});
+            else
+                launch(const_int<3>{}, const_int<4>{});
+        } else if (xscale) {
             if (V == 1)
                 launch(const_int<2>{}, const_int<1>{});
             else
@@ -726,7 +823,7 @@ extern "C" int bitgnn_spmm_f32(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *
         return rc;
     BG_NEED_DEVICE(ctx);
     return bg_launch_spmm_f32(ctx, (hipStream_t)stream, adj, x, x_is_bits, C, ldx, r, f, epilogue,
-                              tau, out, ldo, nullptr);
+                              tau, out, ldo, nullptr, nullptr);
 }
 
 int bg_check_spmm_i16(bitgnn_ctx *ctx, const bitgnn_adj *adj, const int16_t *z, int32_t C,
@@ -753,7 +850,78 @@ extern "C" int bitgnn_spmm_i16(bitgnn_ctx *ctx, void *stream, const bitgnn_adj *
         return rc;
     BG_NEED_DEVICE(ctx);
     return bg_launch_spmm_f32(ctx, (hipStream_t)stream, adj, z, 0, C, ldz, r, f, epilogue, tau,
-                              out, ldo, alpha);
+                              out, ldo, alpha, nullptr);
+}
+
+namespace {
+
+// int16 rows -> byte rows z / 2 + 128, eight channels per thread; of rows that bring their factor
+// a thread behind the channels writes it.  Sets *wide (if there is one) where a value has no byte.
+// Bound by the 2 + 1 bytes per channel that it moves (232,965 rows of 128: 16 us).
+__global__ __launch_bounds__(256) void byte_rows_kernel(const int16_t *z, int64_t n, int32_t C,
+                                                        int64_t ld, int groups_log2, uint8_t *out,
+                                                        const float *f, uint32_t *wide)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, i = t >> groups_log2;
+    if (i >= n)
+        return;
+    const int32_t g = (int32_t)(t & ((1 << groups_log2) - 1)), c0 = 8 * g;
+    uint32_t w[2] = {0, 0};
+    bool out_of_range = false;
+    if (c0 < C) {
+        typedef int16_t i16x8 __attribute__((ext_vector_type(8)));
+        const i16x8 v = *(const i16x8 *)(z + i * ld + c0); // rows are padded to 16 bytes
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int32_t b = (v[k] >> 1) + 128;
+            out_of_range |= c0 + k < C && (uint32_t)b > 255u;
+            w[k / 4] |= (uint32_t)(b & 255) << (8 * (k % 4));
+        }
+    } else if (f && c0 + 4 == (int32_t)kFactorAt) {
+        w[1] = (uint32_t)__float_as_int(f[i]);
+    }
+    *(uint2 *)(out + (i << (groups_log2 + 3)) + c0) = make_uint2(w[0], w[1]);
+    if (out_of_range && wide)
+        *wide = 1u;
+}
+
+__global__ void clear_word_kernel(uint32_t *p) { *p = 0u; }
+
+} // namespace
+
+// Whether byte rows pay: microseconds that the aggregation is expected to save against those of
+// writing them and, where a value may have no byte (K > 254), of clearing the word that says so.
+// Rows of up to 32 channels are a line or less either way.  With a factor in the row (up to 56
+// channels) the factors' gathers go too: 41 channels, 89,250 nodes, 1 M non-zeros 46 -> 40 us,
+// 300,000 and 23.8 M 386 -> 263, 8,192 and 0.4 M 26.5 either way.  Wider rows gain where the table
+// is larger than an L2: 128 channels, 300,000 nodes, 23.8 M 663 -> 435; 5,000 and 1.7 M 43 -> 46.
+bool bg_byte_rows_pay(const bitgnn_adj *adj, int32_t C, int32_t K, bool has_f)
+{
+    if (K % 2 != 0 || C <= 32 || C > 256)
+        return false;
+    const double nnz = (double)adj->nnz, n = (double)adj->n;
+    const double cost = 4.5 + (K > 254 ? 10.0 : 0.0) + n * C * 0.5e-6;
+    double gain = 4.5e-6 * nnz + 4.0;
+    if (!has_f || C > 56)
+        gain = (C > 64 ? 6e-6 * ((C + 63) / 64) : 2.5e-6) * nnz *
+               (n * 2 * C > (double)(4 << 20) ? 1.0 : 0.2);
+    return gain > 1.3 * cost;
+}
+
+int bg_launch_byte_rows(bitgnn_ctx *ctx, hipStream_t s, const int16_t *z, int64_t n, int32_t C,
+                        int64_t ld, const float *f, uint32_t *wide, bg_byte_rows *b)
+{
+    b->has_factor = f && C <= 56;
+    b->wide = wide;
+    int groups_log2 = 3;
+    while ((8 << groups_log2) < b->row_bytes)
+        ++groups_log2;
+    if (wide)
+        clear_word_kernel<<<1, 1, 0, s>>>(wide);
+    byte_rows_kernel<<<(unsigned)(((n << groups_log2) + 255) / 256), 256, 0, s>>>(
+        z, n, C, ld, groups_log2, (uint8_t *)b->z, b->has_factor ? f : nullptr, wide);
+    BG_LAUNCH_CHECK(ctx, "byte_rows_kernel");
+    return BITGNN_OK;
 }
 
 namespace {

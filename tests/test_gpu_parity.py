@@ -1233,6 +1233,64 @@ def test_full_precision_rows_between_product_and_aggregation(B, gemm_ctx, M, n, 
     adj.close()
 
 
+@pytest.mark.parametrize("n,e,K,M,hub,wide", [
+    (3000, 1000000, 128, 37, 0, False), (3000, 1000000, 254, 41, 2500, False),
+    (3001, 1000000, 64, 45, 0, False), (3000, 1000000, 2, 46, 0, False),
+    (3000, 1000000, 100, 56, 0, False), (3000, 2500000, 256, 40, 0, False),
+    (3000, 2500000, 256, 40, 0, True), (40007, 2000000, 200, 57, 0, False),
+    (40007, 2000000, 200, 64, 9000, False), (30001, 2000000, 602, 128, 0, False),
+    (30001, 2000000, 602, 100, 9000, True), (16000, 2000000, 602, 193, 0, False),
+    (16000, 2000000, 512, 256, 0, True)])
+def test_byte_rows_between_product_and_aggregation(B, ctx, n, e, K, M, hub, wide):
+    """Graphs whose rows are gathered often enough for byte rows: at the edges of their widths,
+    with and without factors in the rows, with hub rows, with factors and scales of either sign,
+    zero, denormal and infinite; and with one product that has no byte, where the int16 rows are
+    taken.  The oracle's floats exactly, and the bytes lie in the scratch."""
+    r = np.random.default_rng(31 * n + K + M)
+    src, dst = r.integers(0, n, e).astype(np.int32), r.integers(0, n, e).astype(np.int32)
+    src = np.concatenate([src, np.full(hub, 5, np.int32)])
+    dst = np.concatenate([dst, r.choice(n, hub, replace=False).astype(np.int32)])
+    adj = B.adj_build(ctx, dev(src), dev(dst), len(src), n, SYM_LOOPS)
+    rp, col = orc.adjacency(src, dst, n, SYM_LOOPS)
+    v, w = W.pm1(r, (n, K)), W.pm1(r, (K, M))
+    w[0] = 1
+    if wide:
+        v[n // 2] = w[:, M - 1]
+    z = (v.astype(np.float32) @ w.astype(np.float32)).astype(np.int64)
+    no_byte = bool((z // 2 < -128).any() or (z // 2 > 127).any())
+    assert no_byte == wide
+    alpha = r.uniform(-1.5, 1.5, M).astype(np.float32)
+    alpha[:3] = 0.0, -1e-40, 3e38
+    rv = r.uniform(0.5, 1.5, n).astype(np.float32)
+    f = r.uniform(-1.0, 1.0, n).astype(np.float32)
+    f[:3] = 0.0, 1e-41, np.inf
+    tau = r.standard_normal(M).astype(np.float32)
+    with np.errstate(over="ignore", invalid="ignore"):
+        x = orc.scale(z, alpha)
+    kw, mw = B.words(K), B.words(M)
+    xb, wb = _pack_host(v), _pack_host(np.ascontiguousarray(w.T))
+    fv, rd, al = dev(f), dev(rv), dev(alpha)
+    tmp = torch.zeros((n, M), dtype=torch.float32, device="cuda")
+    for fd, fh in ((fv, f), (None, np.ones(n, np.float32))):
+        want = orc.spmm_weighted_f32(rp, col, x, rv, fh)
+        out = torch.full((n, M), -7.0, device="cuda")
+        tmp.zero_()
+        B.gcn_out_layer_weighted(ctx, adj, xb, kw, K, kw, wb, M, kw, al, rd, fd, tmp, out, M)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), want, equal_nan=True)
+        if fd is not None:
+            stride = 64 if M <= 64 else 128 if M <= 128 else 256
+            got = tmp.view(torch.uint8).flatten()[:n * stride].reshape(n, stride)[:, :M]
+            assert np.array_equal(got.cpu().numpy(), ((z >> 1) + 128).astype(np.uint8))
+        bits = torch.full((n, mw), -1, dtype=torch.int64, device="cuda")
+        B.gcn_layer_full(ctx, adj, xb, kw, K, kw, wb, M, kw, al, rd, fd, dev(tau), tmp, bits, mw)
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            assert np.array_equal(words_np(bits),
+                                  orc.to_words(np.where(want >= tau, 1, -1).astype(np.int8)))
+    adj.close()
+
+
 @pytest.mark.parametrize("n,e,K,M", [(300, 2500, 70, 40), (4000, 60000, 128, 128),
                                      (2500, 30000, 200, 65)])
 def test_weighted_layers(B, ctx, n, e, K, M):
