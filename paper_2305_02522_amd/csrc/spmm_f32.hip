@@ -897,7 +897,9 @@ __global__ void clear_word_kernel(uint32_t *p) { *p = 0u; }
 // is larger than an L2: 128 channels, 300,000 nodes, 23.8 M 663 -> 435; 5,000 and 1.7 M 43 -> 46.
 bool bg_byte_rows_pay(const bitgnn_adj *adj, int32_t C, int32_t K, bool has_f)
 {
-    if (K % 2 != 0 || C <= 32 || C > 256)
+    // (products of random bits have a deviation of sqrt(K): above 1,800 the range of a byte is
+    // less than six of them, and some value of a large table has none)
+    if (K % 2 != 0 || K > 1800 || C <= 32 || C > 256)
         return false;
     const double nnz = (double)adj->nnz, n = (double)adj->n;
     const double cost = 4.5 + (K > 254 ? 10.0 : 0.0) + n * C * 0.5e-6;

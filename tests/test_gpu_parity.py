@@ -1240,7 +1240,7 @@ def test_full_precision_rows_between_product_and_aggregation(B, gemm_ctx, M, n, 
     (3000, 2500000, 256, 40, 0, True), (40007, 2000000, 200, 57, 0, False),
     (40007, 2000000, 200, 64, 9000, False), (30001, 2000000, 602, 128, 0, False),
     (30001, 2000000, 602, 100, 9000, True), (16000, 2000000, 602, 193, 0, False),
-    (16000, 2000000, 512, 256, 0, True)])
+    (16000, 2000000, 512, 256, 0, True), (30001, 2000000, 1800, 70, 0, False)])
 def test_byte_rows_between_product_and_aggregation(B, ctx, n, e, K, M, hub, wide):
     """Graphs whose rows are gathered often enough for byte rows: at the edges of their widths,
     with and without factors in the rows, with hub rows, with factors and scales of either sign,
